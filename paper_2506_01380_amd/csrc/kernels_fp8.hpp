@@ -70,21 +70,4 @@ kvcache_append_fp8(const __bf16* __restrict__ kn, const __bf16* __restrict__ vn,
     }
 }
 
-// Move n_keys keys of every feature row between two row-major byte tensors, either of which may be in the
-// V cache's permuted key order (perm_*; feature of a row = (row_base + row) % 64) or in plain order (staging).
-// blockIdx.y = row (strided), x over keys.
-__global__ void __launch_bounds__(256)
-v8t_move_keys(unsigned char* __restrict__ dst, const unsigned char* __restrict__ src, int64_t rows, int64_t dst_stride,
-              int64_t src_stride, int64_t dst_key0, int64_t src_key0, int64_t n_keys, int perm_dst, int perm_src,
-              int64_t row_base) {
-    for (int64_t row = blockIdx.y; row < rows; row += gridDim.y) {
-        const int s = (int)(((row_base + row) >> 4) & 1);
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_keys; i += (int64_t)gridDim.x * blockDim.x) {
-            const int64_t sp = perm_src ? v8t_position(src_key0 + i, s) : src_key0 + i;
-            const int64_t dp = perm_dst ? v8t_position(dst_key0 + i, s) : dst_key0 + i;
-            dst[row * dst_stride + dp] = src[row * src_stride + sp];
-        }
-    }
-}
-
 }  // namespace nfd

@@ -68,6 +68,16 @@ size_t elem_size(nfd_dtype_t dt) { return dt == NFD_BF16 ? 2 : 4; }
 // frames up to and including its own).
 int64_t kmax_rows(int64_t r_last, int T, int P) { return ((int64_t)P + r_last / T + 1) * T; }
 
+unsigned shift_blocks(const nfd::ShiftRun& r) { return (unsigned)((r.rows * r.d + 255) / 256); }
+
+// A chain of the one-pass move is walked by one thread.  Past this many links (very many frames kept for each one dropped)
+// the walk takes longer than copying the kept frames out to the workspace and back: 16 heads, 16 tokens a frame, one
+// frame dropped: 7.1 against 9.6 us at 63 links, 11.5 against 9.5 at 127, 37 against 22 at 511.
+constexpr int64_t kMaxShiftChain = 96;
+bool shift_staged(const nfd_attn_t* h, const nfd::ShiftRun& r, size_t unit_bytes, int tensors) {
+    return r.len > kMaxShiftChain * r.d && (size_t)(r.rows * r.len) * unit_bytes * tensors <= h->workspace_bytes;
+}
+
 }  // namespace
 
 extern "C" {
@@ -568,34 +578,8 @@ static void launch_frame_copy(nfd_attn_t* h, size_t es, void* kd, void* vd, cons
                                len / f, BH);
     };
     if (vec) go(nfd::u32x4{}, (int64_t)(16 / es));
-    else if (es == 1) go((unsigned char)0, 1);
     else if (es == 2) go((uint16_t)0, 1);
     else go((uint32_t)0, 1);
-}
-
-// Move frames n_drop .. kv_frames-1 of every head to frames 0 .. of the same tensors (two of equal geometry,
-// or one when b == nullptr): heads of head elements each, fe elements per frame, es bytes per element.
-static void shift_frames(nfd_attn_t* h, size_t es, void* a, void* b, int64_t heads, int64_t head, int64_t fe,
-                         int kv_frames, int n_drop, hipStream_t st) {
-    const int keep = kv_frames - n_drop;
-    const size_t half = ((size_t)(heads * keep * fe) * es + 255) / 256 * 256;  // staging bytes per tensor
-    if (keep <= n_drop) {
-        // source and destination frames are disjoint: one copy inside the tensors
-        launch_frame_copy(h, es, a, b, a, b, heads, head, head, 0, (int64_t)n_drop * fe, keep * fe, st);
-    } else if ((b ? 2 : 1) * half <= h->workspace_bytes) {
-        // overlapping ranges: through the workspace (out, then back)
-        void* as = h->workspace;
-        void* bs = b ? (char*)h->workspace + half : nullptr;
-        launch_frame_copy(h, es, as, bs, a, b, heads, keep * fe, head, 0, (int64_t)n_drop * fe, keep * fe, st);
-        launch_frame_copy(h, es, a, b, as, bs, heads, head, keep * fe, 0, 0, keep * fe, st);
-    } else {
-        // workspace too small: runs of n_drop frames, oldest first; within a run source and destination are disjoint
-        for (int f = n_drop; f < kv_frames; f += n_drop) {
-            const int n = std::min(n_drop, kv_frames - f);
-            launch_frame_copy(h, es, a, b, a, b, heads, head, head, (int64_t)(f - n_drop) * fe, (int64_t)f * fe,
-                              (int64_t)n * fe, st);
-        }
-    }
 }
 
 int nfd_kvcache_append(nfd_attn_t* h, void* k_cache, void* v_cache, const void* k_new, const void* v_new, int B,
@@ -623,8 +607,25 @@ int nfd_kvcache_shift(nfd_attn_t* h, void* k_cache, void* v_cache, int B, int H,
     if (kv_frames > F) return fail(h, NFD_ERR_CAPACITY, "kv_frames exceeds the cache capacity F");
     if (n_drop == 0 || kv_frames == n_drop) return NFD_OK;
     if (const int dc = check_device(h)) return dc;
-    shift_frames(h, elem_size(h->dtype), k_cache, v_cache, (int64_t)B * H, (int64_t)F * T * D, (int64_t)T * D, kv_frames,
-                 n_drop, (hipStream_t)stream);
+    const size_t es = elem_size(h->dtype);
+    const int64_t frame = (int64_t)T * D, BH = (int64_t)B * H;
+    const bool vec = ((size_t)frame * es) % 16 == 0 && ((uintptr_t)k_cache | (uintptr_t)v_cache) % 16 == 0;
+    const int64_t f = vec ? (int64_t)(16 / es) : 1;  // elements per unit
+    const int64_t stride = (int64_t)F * frame / f, d = n_drop * frame / f, len = (kv_frames - n_drop) * frame / f;
+    const nfd::ShiftRun rk{k_cache, stride, BH, d, len}, rv{v_cache, stride, BH, d, len};
+    hipStream_t st = (hipStream_t)stream;
+    if (shift_staged(h, rk, f * es, 2)) {
+        void* ks = h->workspace;
+        void* vs = (char*)h->workspace + (size_t)(BH * len * f) * es;
+        launch_frame_copy(h, es, ks, vs, k_cache, v_cache, BH, len * f, stride * f, 0, d * f, len * f, st);
+        launch_frame_copy(h, es, k_cache, v_cache, ks, vs, BH, stride * f, len * f, 0, 0, len * f, st);
+        return check_hip(h, hipGetLastError(), "kvcache shift launch");
+    }
+    const unsigned nb = shift_blocks(rk);
+    const dim3 grid(2 * nb), block(256);
+    if (vec) hipLaunchKernelGGL(nfd::kvcache_shift_inplace<nfd::u32x4>, grid, block, 0, st, rk, rv, nb);
+    else if (es == 2) hipLaunchKernelGGL(nfd::kvcache_shift_inplace<uint16_t>, grid, block, 0, st, rk, rv, nb);
+    else hipLaunchKernelGGL(nfd::kvcache_shift_inplace<uint32_t>, grid, block, 0, st, rk, rv, nb);
     return check_hip(h, hipGetLastError(), "kvcache shift launch");
 }
 
@@ -645,25 +646,25 @@ int nfd_kvcache_shift_fp8(nfd_attn_t* h, void* k8, void* v8t, int B, int H, int 
         return fail(h, NFD_ERR_ALLOC, "the workspace cannot stage one feature row of the 8-bit V cache");
     if (const int dc = check_device(h)) return dc;
     hipStream_t st = (hipStream_t)stream;
-    // K codes: BH heads of Spad rows x 64 bytes, a frame = T rows; V codes: BH * 64 feature rows of Spad bytes,
-    // a frame = T bytes of each.  (One tensor at a time: the geometries differ.)
-    shift_frames(h, 1, k8, nullptr, BH, Spad * D, (int64_t)T * D, kv_frames, n_drop, st);
-    if (T % 16 == 0) {  // whole 16-key groups move: the permuted order inside them is untouched
-        shift_frames(h, 1, v8t, nullptr, BH * D, Spad, (int64_t)T, kv_frames, n_drop, st);
+    // K codes: BH heads of Spad rows x 64 bytes, a frame = T rows; V codes: BH * 64 feature rows of Spad bytes, a frame =
+    // T bytes of each.  When T is a multiple of 16 whole 16-key groups of V move (the order inside them is untouched).
+    const bool vec = ((uintptr_t)k8 | (uintptr_t)v8t) % 16 == 0;
+    const int64_t f = vec ? 16 : 1;  // bytes per unit
+    const nfd::ShiftRun rk{k8, Spad * D / f, BH, (int64_t)n_drop * T * D / f, keep_keys * D / f};
+    const bool staged = vec && shift_staged(h, rk, 16, 1);
+    if (staged) {
+        launch_frame_copy(h, 16, h->workspace, nullptr, k8, nullptr, BH, rk.len, rk.stride, 0, rk.d, rk.len, st);
+        launch_frame_copy(h, 16, k8, nullptr, h->workspace, nullptr, BH, rk.stride, rk.len, 0, 0, rk.len, st);
+    }
+    const unsigned nb = staged ? 0 : shift_blocks(rk);
+    const dim3 grid(nb + (unsigned)(BH * D)), block(256);
+    if (vec && T % 16 == 0) {
+        const nfd::ShiftRun rv{v8t, Spad / 16, BH * D, (int64_t)n_drop * T / 16, keep_keys / 16};
+        hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<nfd::u32x4, nfd::u32x4, false>), grid, block, 0, st, rk, rv, nb);
     } else {
-        // key by key through the workspace (plain order there), as many feature rows at a time as fit
-        const int64_t rows = BH * D;
-        const int64_t fit = (int64_t)(h->workspace_bytes / (size_t)keep_keys);  // >= 1, checked above
-        unsigned char* v = (unsigned char*)v8t;
-        unsigned char* ws = (unsigned char*)h->workspace;
-        for (int64_t r0 = 0; r0 < rows; r0 += fit) {
-            const int64_t nr = std::min(fit, rows - r0);
-            const dim3 grid((unsigned)std::min<int64_t>((keep_keys + 255) / 256, 1024), (unsigned)std::min<int64_t>(nr, 65535));
-            hipLaunchKernelGGL(nfd::v8t_move_keys, grid, dim3(256), 0, st, ws, v + r0 * Spad, nr, keep_keys, Spad, (int64_t)0,
-                               (int64_t)n_drop * T, keep_keys, 0, 1, r0);
-            hipLaunchKernelGGL(nfd::v8t_move_keys, grid, dim3(256), 0, st, v + r0 * Spad, ws, nr, Spad, keep_keys, (int64_t)0,
-                               (int64_t)0, keep_keys, 1, 0, r0);
-        }
+        const nfd::ShiftRun rv{v8t, Spad, BH * D, (int64_t)n_drop * T, keep_keys};
+        if (vec) hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<nfd::u32x4, unsigned char, true>), grid, block, 0, st, rk, rv, nb);
+        else hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<unsigned char, unsigned char, true>), grid, block, 0, st, rk, rv, nb);
     }
     return check_hip(h, hipGetLastError(), "8-bit kvcache shift launch");
 }
