@@ -143,8 +143,7 @@ int nfd_block_causal_attn_fwd_lse(nfd_attn_t* h, const void* q, const void* k, c
  * dv only the first kv_frames*T rows of every head are written.  No atomics: results are
  * bit-reproducible.  Uses the handle's workspace (8 bytes per query row on the matrix-core path, 4 on the general one).
  * Supported: as the forward - bf16 with D = 64 on the matrix-core path (tensors 16-byte aligned there),
- * every other D <= 256 and all fp32 shapes on a general fp32-arithmetic path (one wavefront per row, not
- * tuned).
+ * every other D <= 256 and all fp32 shapes on a general fp32-arithmetic path.
  * Errors, in this order: NFD_ERR_NULL, NFD_ERR_SHAPE, NFD_ERR_CAPACITY, NFD_ERR_UNSUPPORTED,
  * NFD_ERR_ALLOC (workspace too small), NFD_ERR_HIP.
  */

@@ -1,0 +1,419 @@
+// General path: fp32 storage at any head width D <= 256, and bf16 storage at widths other than 64.  All arithmetic in
+// fp32, the products on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: 32 cycles for 2048 operations, twice the
+// rate of the vector unit's fused multiply-adds, and one operand register feeds 16 rows).
+//
+// Bound by the fp32 matrix pipe at sizes that fill the chip, by the length of a wavefront's chain of key blocks below.
+// No LDS in the loops: operands go from global memory (L2) to registers, so the wavefronts of a workgroup need no
+// barrier, and the four of them SPLIT THE KEYS of the same 16 CQ query rows (blocks w, w + 4, ...): calls on this path
+// are short clips in full precision with few rows, which one row range per wavefront would leave most of the chip out
+// of.  They merge once, through LDS, at the end; the merge order is fixed, so results are bit-reproducible.
+// Measured, 12 heads, 4 frames of 336 tokens, fp32, D = 64 (before: one wavefront per row, operands one element at a
+// time): forward 562 -> 45 us, backward 2173 -> 163 us; at 32 heads, 8 frames the forward reaches 108 TFLOP/s and the
+// backward 101 TFLOP/s of executed products (matrix pipe busy 62-68 % of the cycles) of the 157 of the instruction.
+//
+// Lane = (j, g), j = lane % 16, g = lane / 16.  A[i][k] and B[k][j] of the instruction sit in lane i (or j) + 16 k, one
+// register each; D[i][j] in lane j + 16 (i / 4), element i % 4.
+//   S^T[key, query] = K . Q^T        step (m, e) contracts features 16 m + 4 k + e: one 16-byte load per m and lane
+//                                    D: query j, keys 4 g + e of the 16-key block
+//   O^T[f, query] += V^T . P^T       step e contracts keys 4 k + e: B = the accumulators as they are; A row i of block
+//                                    (c, b) is feature 16 NF c + NF i + b: one load of NF features per lane and e
+//                                    D: query j, features 16 NF c + NF (4 g + e) + b
+// The gradients use the same two patterns.  DP: head width rounded up to 32, 64, 128 or 256; VEC: D == DP and rows
+// 16-byte aligned, otherwise features are loaded one by one and those past D are zero.
+#pragma once
+#include "nfd_common.hpp"
+
+namespace nfd {
+namespace general {
+
+constexpr int kWaves = 4;
+constexpr int kMaxD = 256;
+
+template <typename T> __device__ __forceinline__ T from_f32(float x) { return (T)x; }  // RNE for bf16
+
+template <typename T, bool VEC, int N>
+__device__ __forceinline__ void load_features(const T* row, int f, int D, float (&x)[N]) {
+    if constexpr (VEC) {
+        typedef __attribute__((ext_vector_type(N))) T vec_t;
+        const vec_t v = *(const vec_t*)(row + f);
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[e] = (float)v[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[e] = f + e < D ? (float)row[f + e] : 0.f;
+    }
+}
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int DP>
+struct Shape {
+    static constexpr int M = DP / 16;              // 16-feature groups
+    static constexpr int NF = DP >= 64 ? 4 : DP / 16;
+    static constexpr int NC = DP / (16 * NF);
+};
+
+// 16 rows as an operand of the first pattern: lane (i, g) holds row i, features 16 m + 4 g + e.
+template <typename T, int DP, bool VEC>
+struct RowFrag {
+    float x[Shape<DP>::M][4];
+    __device__ __forceinline__ void load(const T* row, int g, int D) {
+#pragma unroll
+        for (int m = 0; m < Shape<DP>::M; ++m) load_features<T, VEC, 4>(row, 16 * m + 4 * g, D, x[m]);
+    }
+};
+// 16 rows as an operand of the second pattern: lane (i, g) holds rows 4 g + e, features 16 NF c + NF i + b.
+template <typename T, int DP, bool VEC>
+struct ColFrag {
+    float x[4][Shape<DP>::NC][Shape<DP>::NF];
+    template <typename RowPtr>
+    __device__ __forceinline__ void load(RowPtr row_ptr, int i, int D) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const T* row = row_ptr(e);
+#pragma unroll
+            for (int c = 0; c < Shape<DP>::NC; ++c)
+                load_features<T, VEC, Shape<DP>::NF>(row, 16 * Shape<DP>::NF * c + Shape<DP>::NF * i, D, x[e][c]);
+        }
+    }
+};
+template <int DP>
+struct Acc {
+    f32x4 x[Shape<DP>::NC][Shape<DP>::NF];
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+        for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+            for (int b = 0; b < Shape<DP>::NF; ++b) x[c][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void scale(float a) {
+#pragma unroll
+        for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+            for (int b = 0; b < Shape<DP>::NF; ++b) x[c][b] *= a;
+    }
+    template <typename Frag>
+    __device__ __forceinline__ void mac(const Frag& a, const f32x4& p) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+                for (int b = 0; b < Shape<DP>::NF; ++b) x[c][b] = mfma4(a.x[e][c][b], p[e], x[c][b]);
+    }
+    // into column j of a [16][DP] block in LDS
+    __device__ __forceinline__ void store(float* col, int g) const {
+#pragma unroll
+        for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int b = 0; b < Shape<DP>::NF; ++b)
+                    col[16 * Shape<DP>::NF * c + Shape<DP>::NF * (4 * g + e) + b] = x[c][b][e];
+    }
+};
+template <int DP, typename FragA, typename FragB>
+__device__ __forceinline__ f32x4 dot_block(const FragA& a, const FragB& b, f32x4 acc) {
+#pragma unroll
+    for (int m = 0; m < Shape<DP>::M; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = mfma4(a.x[m][e], b.x[m][e], acc);
+    return acc;
+}
+
+// Sum of the four wavefronts' [16 C][DP] blocks in LDS, times `factor(row)`, to rows row0 .. (below `limit`) of `dst`.
+template <typename T, int DP, int C, typename Factor>
+__device__ __forceinline__ void write_sum(const float* s, T* dst, int row0, int limit, int D, Factor factor) {
+    for (int x = threadIdx.x; x < 16 * C * DP; x += kWaves * 64) {
+        const int r = x / DP, f = x % DP;
+        if (row0 + r < limit && f < D) {
+            float a = s[x];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) a += s[w * 16 * C * DP + x];
+            dst[(int64_t)(row0 + r) * D + f] = from_f32<T>(a * factor(r));
+        }
+    }
+}
+
+// C = columns (query rows, or keys in the dk/dv kernel) per workgroup in units of 16.  Two where the registers of two
+// wavefronts per SIMD hold them (DP <= 64): an operand register then feeds two matrix instructions.  One otherwise, and
+// where two would give the chip less than a workgroup per CU.
+__host__ __device__ constexpr int padded_width(int D) { return D <= 32 ? 32 : D <= 64 ? 64 : D <= 128 ? 128 : 256; }
+__host__ __forceinline__ int cols_per_workgroup(int64_t rows, int64_t BH, int D, int num_cus) {
+    return padded_width(D) <= 64 && BH * ((rows + 31) / 32) >= 4 * num_cus ? 2 : 1;
+}
+
+template <typename T, int DP, bool VEC, int CQ>
+__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
+attn_fwd_general(FwdParams p) {
+    __shared__ float o_s[kWaves * 16 * CQ * DP];
+    __shared__ float m_s[kWaves][16 * CQ], l_s[kWaves][16 * CQ], inv_s[16 * CQ];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int bh = (int)(blockIdx.x % (unsigned)p.BH);
+    const int r0 = (p.n_q_tiles - 1 - (int)(blockIdx.x / (unsigned)p.BH)) * 16 * CQ;  // latest (heaviest) rows first
+    const int D = p.D;
+    const T* qg = (const T*)p.q + (int64_t)bh * p.Sq * D;
+    const T* kg = (const T*)p.k + (int64_t)bh * p.Scap * D;
+    const T* vg = (const T*)p.v + (int64_t)bh * p.Scap * D;
+    RowFrag<T, DP, VEC> qf[CQ];
+    Acc<DP> o[CQ];
+    float m[CQ], l[CQ];
+    int kmax_lane[CQ];
+#pragma unroll
+    for (int c = 0; c < CQ; ++c) {
+        const int rc = min(r0 + 16 * c + j, p.Sq - 1);  // ragged tail: a duplicate row, never stored
+        qf[c].load(qg + (int64_t)rc * D, g, D);
+        o[c].zero();
+        m[c] = kNegBig;
+        l[c] = 0.f;
+        kmax_lane[c] = kmax_of_row(rc, p.T, p.P);
+    }
+    const int kmin = kmax_of_row(min(r0, p.Sq - 1), p.T, p.P);
+    const int n_blk = (kmax_of_row(min(r0 + 16 * CQ, p.Sq) - 1, p.T, p.P) + 15) / 16;
+    // The next block's keys are requested before this block's products where that costs no resident wavefront (wide
+    // heads: 726 against 778 us at 32 heads, 8 frames of 336, D = 128), behind them otherwise (D = 64: 314 against 318).
+    constexpr bool PREFETCH = DP > 64;
+    RowFrag<T, DP, VEC> kf;
+    if (wave < n_blk) kf.load(kg + (int64_t)min(16 * wave + j, p.Sk - 1) * D, g, D);
+    for (int b = wave; b < n_blk; b += kWaves) {
+        const int j0 = 16 * b;
+        ColFrag<T, DP, VEC> vf;
+        vf.load([&](int e) { return vg + (int64_t)min(j0 + 4 * g + e, p.Sk - 1) * D; }, j, D);
+        RowFrag<T, DP, VEC> kn = kf;
+        if (PREFETCH && b + kWaves < n_blk) kn.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
+        f32x4 s[CQ];
+#pragma unroll
+        for (int c = 0; c < CQ; ++c) s[c] = dot_block<DP>(kf, qf[c], f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int c = 0; c < CQ; ++c) {
+            if (j0 + 16 > kmin) {
+                const int left = kmax_lane[c] - (j0 + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e >= left) s[c][e] = -INFINITY;
+            }
+            s[c] *= p.scale_log2e;
+            float a = fmaxf(fmaxf(s[c][0], s[c][1]), fmaxf(s[c][2], s[c][3]));
+            a = fmaxf(a, __shfl_xor(a, 16));
+            a = fmaxf(a, __shfl_xor(a, 32));
+            const float m_new = fmaxf(m[c], a);
+            const float alpha = __builtin_amdgcn_exp2f(m[c] - m_new);
+            m[c] = m_new;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[c][e] = __builtin_amdgcn_exp2f(s[c][e] - m_new);
+            l[c] = l[c] * alpha + ((s[c][0] + s[c][1]) + (s[c][2] + s[c][3]));
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) o[c].scale(alpha);
+        }
+#pragma unroll
+        for (int c = 0; c < CQ; ++c) o[c].mac(vf, s[c]);
+        if constexpr (PREFETCH) kf = kn;
+        else if (b + kWaves < n_blk) kf.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
+    }
+#pragma unroll
+    for (int c = 0; c < CQ; ++c) {
+        l[c] += __shfl_xor(l[c], 16);
+        l[c] += __shfl_xor(l[c], 32);
+        if (g == 0) {
+            m_s[wave][16 * c + j] = m[c];
+            l_s[wave][16 * c + j] = l[c];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CQ; ++c) {
+        float mm = m_s[0][16 * c + j];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) mm = fmaxf(mm, m_s[w][16 * c + j]);
+        o[c].scale(__builtin_amdgcn_exp2f(m[c] - mm));
+        o[c].store(o_s + (wave * 16 * CQ + 16 * c + j) * DP, g);
+    }
+    if ((int)threadIdx.x < 16 * CQ) {  // one thread per row: the merged row sum
+        const int r = threadIdx.x;
+        float mm = m_s[0][r], ll = 0.f;
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) mm = fmaxf(mm, m_s[w][r]);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) ll += l_s[w][r] * __builtin_amdgcn_exp2f(m_s[w][r] - mm);
+        inv_s[r] = 1.0f / ll;
+        if (p.lse && r0 + r < p.Sq) p.lse[(int64_t)bh * p.Sq + r0 + r] = (mm + log2f(ll)) * kLn2;
+    }
+    __syncthreads();
+    write_sum<T, DP, CQ>(o_s, (T*)p.out + (int64_t)bh * p.Sq * D, r0, p.Sq, D, [&](int r) { return inv_s[r]; });
+}
+
+// Backward.  With p_ij = exp(scale <q_i, k_j> - lse_i) over the visible keys of row i and delta_i = <dout_i, out_i>:
+// ds_ij = p_ij (<dout_i, v_j> - delta_i), dq_i = scale sum_j ds_ij k_j, dk_j = scale sum_i ds_ij q_i,
+// dv_j = sum_i p_ij dout_i.  Two kernels, neither with atomics; the dq kernel first (it writes delta).
+struct BwdParams {
+    const void *q, *k, *v, *out, *dout;
+    const float* lse;
+    float* delta;  // [BH, Sq], written by the dq kernel, read by the dk/dv kernel
+    void *dq, *dk, *dv;
+    int BH, Sq, Sk, Scap, T, P, D;
+    int n_q_tiles, n_k_tiles;
+    float scale, scale_log2e;
+};
+
+template <typename T, int DP, bool VEC, int CQ>
+__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
+attn_bwd_dq_general(BwdParams p) {
+    __shared__ float o_s[kWaves * 16 * CQ * DP];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int bh = (int)(blockIdx.x % (unsigned)p.BH);
+    const int r0 = (p.n_q_tiles - 1 - (int)(blockIdx.x / (unsigned)p.BH)) * 16 * CQ;
+    const int D = p.D;
+    const T* kg = (const T*)p.k + (int64_t)bh * p.Scap * D;
+    const T* vg = (const T*)p.v + (int64_t)bh * p.Scap * D;
+    RowFrag<T, DP, VEC> qf[CQ], gf[CQ];
+    Acc<DP> dq[CQ];
+    float lse2[CQ], delta[CQ];
+    int kmax_lane[CQ];
+#pragma unroll
+    for (int c = 0; c < CQ; ++c) {
+        const int row = r0 + 16 * c + j, rc = min(row, p.Sq - 1);
+        const int64_t at = ((int64_t)bh * p.Sq + rc) * D;
+        qf[c].load((const T*)p.q + at, g, D);
+        gf[c].load((const T*)p.dout + at, g, D);
+        RowFrag<T, DP, VEC> of;
+        of.load((const T*)p.out + at, g, D);
+        float a = 0.f;
+#pragma unroll
+        for (int m = 0; m < Shape<DP>::M; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a = fmaf(gf[c].x[m][e], of.x[m][e], a);
+        a += __shfl_xor(a, 16);
+        delta[c] = a + __shfl_xor(a, 32);
+        if (wave == 0 && g == 0 && row < p.Sq) p.delta[(int64_t)bh * p.Sq + row] = delta[c];
+        lse2[c] = p.lse[(int64_t)bh * p.Sq + rc] * kLog2e;
+        dq[c].zero();
+        kmax_lane[c] = kmax_of_row(rc, p.T, p.P);
+    }
+    const int kmin = kmax_of_row(min(r0, p.Sq - 1), p.T, p.P);
+    const int n_blk = (kmax_of_row(min(r0 + 16 * CQ, p.Sq) - 1, p.T, p.P) + 15) / 16;
+    for (int b = wave; b < n_blk; b += kWaves) {
+        const int j0 = 16 * b;
+        RowFrag<T, DP, VEC> kf, vf;
+        const int64_t at = (int64_t)min(j0 + j, p.Sk - 1) * D;
+        kf.load(kg + at, g, D);
+        vf.load(vg + at, g, D);
+        ColFrag<T, DP, VEC> kt;
+        kt.load([&](int e) { return kg + (int64_t)min(j0 + 4 * g + e, p.Sk - 1) * D; }, j, D);
+        f32x4 s[CQ], dp[CQ];
+#pragma unroll
+        for (int c = 0; c < CQ; ++c) {
+            s[c] = dp[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int m = 0; m < Shape<DP>::M; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c = 0; c < CQ; ++c) {
+                    s[c] = mfma4(kf.x[m][e], qf[c].x[m][e], s[c]);
+                    dp[c] = mfma4(vf.x[m][e], gf[c].x[m][e], dp[c]);
+                }
+#pragma unroll
+        for (int c = 0; c < CQ; ++c) {
+            const int left = j0 + 16 > kmin ? kmax_lane[c] - (j0 + 4 * g) : 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float pr = __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2[c]);
+                dp[c][e] = e < left ? pr * (dp[c][e] - delta[c]) : 0.f;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CQ; ++c) dq[c].mac(kt, dp[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CQ; ++c) dq[c].store(o_s + (wave * 16 * CQ + 16 * c + j) * DP, g);
+    __syncthreads();
+    write_sum<T, DP, CQ>(o_s, (T*)p.dq + (int64_t)bh * p.Sq * D, r0, p.Sq, D, [&](int) { return p.scale; });
+}
+
+// dk, dv: a workgroup owns 16 CK keys, its wavefronts split the 16-row blocks of queries that see them.  A lane holds
+// key column j and rows 4 g + e of a block.  Key j is visible to row i iff i >= (floor(j/T) - P) T.
+template <typename T, int DP, bool VEC, int CK>
+__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
+attn_bwd_dkdv_general(BwdParams p) {
+    __shared__ float o_s[kWaves * 16 * CK * DP];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int bh = (int)(blockIdx.x % (unsigned)p.BH);
+    const int k0 = (int)(blockIdx.x / (unsigned)p.BH) * 16 * CK;  // earliest keys (seen by most rows) first
+    const int D = p.D;
+    const T* qg = (const T*)p.q + (int64_t)bh * p.Sq * D;
+    const T* gg = (const T*)p.dout + (int64_t)bh * p.Sq * D;
+    const float* lse = p.lse + (int64_t)bh * p.Sq;
+    const float* delta = p.delta + (int64_t)bh * p.Sq;
+    RowFrag<T, DP, VEC> kf[CK], vf[CK];
+    Acc<DP> dk[CK], dv[CK];
+    int rmin_lane[CK];
+#pragma unroll
+    for (int c = 0; c < CK; ++c) {
+        const int kc = min(k0 + 16 * c + j, p.Sk - 1);
+        const int64_t at = ((int64_t)bh * p.Scap + kc) * D;
+        kf[c].load((const T*)p.k + at, g, D);
+        vf[c].load((const T*)p.v + at, g, D);
+        dk[c].zero();
+        dv[c].zero();
+        rmin_lane[c] = (kc / p.T - p.P) * p.T;
+    }
+    const int b0 = max(0, (k0 / p.T - p.P) * p.T) / 16, b1 = (p.Sq + 15) / 16;
+    for (int b = b0 + wave; b < b1; b += kWaves) {
+        const int i0 = 16 * b;
+        f32x4 s[CK], dp[CK];
+        {
+            RowFrag<T, DP, VEC> qa, ga;
+            const int64_t at = (int64_t)min(i0 + j, p.Sq - 1) * D;
+            qa.load(qg + at, g, D);
+            ga.load(gg + at, g, D);
+#pragma unroll
+            for (int c = 0; c < CK; ++c) s[c] = dp[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int m = 0; m < Shape<DP>::M; ++m)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c = 0; c < CK; ++c) {
+                        s[c] = mfma4(qa.x[m][e], kf[c].x[m][e], s[c]);
+                        dp[c] = mfma4(ga.x[m][e], vf[c].x[m][e], dp[c]);
+                    }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = i0 + 4 * g + e, ic = min(i, p.Sq - 1);
+            const float lse2 = lse[ic] * kLog2e, dl = delta[ic];
+#pragma unroll
+            for (int c = 0; c < CK; ++c) {
+                const bool seen = i >= rmin_lane[c] && i < p.Sq;
+                const float pr = seen ? __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2) : 0.f;
+                s[c][e] = pr;
+                dp[c][e] = pr * (dp[c][e] - dl);
+            }
+        }
+        ColFrag<T, DP, VEC> t;
+        auto row_of = [&](const T* base) { return [=](int e) { return base + (int64_t)min(i0 + 4 * g + e, p.Sq - 1) * D; }; };
+        t.load(row_of(gg), j, D);
+#pragma unroll
+        for (int c = 0; c < CK; ++c) dv[c].mac(t, s[c]);
+        t.load(row_of(qg), j, D);
+#pragma unroll
+        for (int c = 0; c < CK; ++c) dk[c].mac(t, dp[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CK; ++c) dk[c].store(o_s + (wave * 16 * CK + 16 * c + j) * DP, g);
+    __syncthreads();
+    write_sum<T, DP, CK>(o_s, (T*)p.dk + (int64_t)bh * p.Scap * D, k0, p.Sk, D, [&](int) { return p.scale; });
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CK; ++c) dv[c].store(o_s + (wave * 16 * CK + 16 * c + j) * DP, g);
+    __syncthreads();
+    write_sum<T, DP, CK>(o_s, (T*)p.dv + (int64_t)bh * p.Scap * D, k0, p.Sk, D, [](int) { return 1.0f; });
+}
+
+}  // namespace general
+}  // namespace nfd

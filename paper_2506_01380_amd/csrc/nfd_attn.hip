@@ -15,10 +15,11 @@
 #include <mutex>
 #include <new>
 
-#include "kernels_generic.hpp"
+#include "kernels_general.hpp"
 #include "kernels_mfma.hpp"
 #include "kernels_mfma16.hpp"
 #include "kernels_mfma_bwd.hpp"
+#include "kernels_stream.hpp"
 
 struct nfd_attn {
     nfd_dtype_t dtype;
@@ -68,6 +69,33 @@ size_t elem_size(nfd_dtype_t dt) { return dt == NFD_BF16 ? 2 : 4; }
 // frames up to and including its own).
 int64_t kmax_rows(int64_t r_last, int T, int P) { return ((int64_t)P + r_last / T + 1) * T; }
 
+// Call f with the instance of the general kernels for these arguments: (element type, padded width, 16-byte loads, 16-column
+// blocks per workgroup).
+template <typename Launch>
+void general_dispatch(nfd_dtype_t dtype, int D, bool vec, int cols, Launch f) {
+    auto width = [&](auto e, auto dp) {
+        typedef std::integral_constant<int, 1> C1;
+        typedef std::integral_constant<int, decltype(dp)::value <= 64 ? 2 : 1> C2;
+        constexpr bool never_vec = sizeof(e) == 2 && decltype(dp)::value == 64;  // bf16 with D = 64 takes the other path
+        if constexpr (!never_vec) {
+            if (vec && cols == 1) return f(e, dp, std::true_type{}, C1{});
+            if (vec) return f(e, dp, std::true_type{}, C2{});
+        }
+        if (cols == 1) f(e, dp, std::false_type{}, C1{});
+        else f(e, dp, std::false_type{}, C2{});
+    };
+    auto type = [&](auto e) {
+        switch (nfd::general::padded_width(D)) {
+            case 32: return width(e, std::integral_constant<int, 32>{});
+            case 64: return width(e, std::integral_constant<int, 64>{});
+            case 128: return width(e, std::integral_constant<int, 128>{});
+            default: return width(e, std::integral_constant<int, 256>{});
+        }
+    };
+    if (dtype == NFD_FP32) type(0.f);
+    else type((__bf16)0.f);
+}
+
 unsigned shift_blocks(const nfd::ShiftRun& r) { return (unsigned)((r.rows * r.d + 255) / 256); }
 
 // A chain of the one-pass move is walked by one thread.  Past this many links (very many frames kept for each one dropped)
@@ -93,7 +121,7 @@ int nfd_attn_check_args(nfd_dtype_t dtype, int B, int H, int F, int T, int D, in
     if (q_frames > kv_frames) return NFD_ERR_SHAPE;
     if (kv_frames > F) return NFD_ERR_CAPACITY;
     if (dtype != NFD_BF16 && dtype != NFD_FP32) return NFD_ERR_UNSUPPORTED;
-    if (D > nfd::kGenericMaxD) return NFD_ERR_UNSUPPORTED;
+    if (D > nfd::general::kMaxD) return NFD_ERR_UNSUPPORTED;
     // 32-bit row indexing inside the kernels
     if ((int64_t)F * T > (int64_t)1 << 30 || (int64_t)B * H > (int64_t)1 << 24) return NFD_ERR_UNSUPPORTED;
     return NFD_OK;
@@ -171,16 +199,17 @@ int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_f
         pl.workspace_bytes = splits > 1 ? (size_t)(BH * Sq) * splits * kPartialRowBytes : 0;
     } else {
         pl.kernel = 0;
-        pl.block_m = nfd::kGenericWaves;  // one row per wavefront
-        pl.block_n = 64;
+        pl.block_m = 16 * nfd::general::cols_per_workgroup(Sq, BH, D, num_cus);
+        pl.block_n = 16;
         pl.n_q_tiles = (int)((Sq + pl.block_m - 1) / pl.block_m);
         pl.n_splits = 1;
-        if ((BH * Sq + nfd::kGenericWaves - 1) / nfd::kGenericWaves > (int64_t)0x7fffffff) return NFD_ERR_UNSUPPORTED;
-        pl.n_workgroups = (int)((BH * Sq + nfd::kGenericWaves - 1) / nfd::kGenericWaves);
+        if (BH * pl.n_q_tiles > (int64_t)0x7fffffff) return NFD_ERR_UNSUPPORTED;
+        pl.n_workgroups = (int)(BH * pl.n_q_tiles);
         int64_t visited = 0;
-        for (int64_t i = 0; i < Sq; ++i) visited += (kmax_rows(i, T, P) + 63) / 64;
+        for (int64_t qt = 0; qt < pl.n_q_tiles; ++qt)
+            visited += (kmax_rows(std::min<int64_t>((qt + 1) * pl.block_m, Sq) - 1, T, P) + 15) / 16;
         pl.key_tiles_visited = visited * BH;
-        pl.key_tiles_dense = Sq * (((int64_t)kv_frames * T + 63) / 64) * BH;
+        pl.key_tiles_dense = (int64_t)pl.n_q_tiles * (((int64_t)kv_frames * T + 15) / 16) * BH;
         pl.workspace_bytes = 0;
     }
     *plan = pl;
@@ -347,10 +376,12 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
             const int64_t total = (int64_t)p.BH * p.Sq * (nfd::mfma::kD / 4);
             hipLaunchKernelGGL(nfd::mfma::attn_combine_d64, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);
         }
-    } else if (h->dtype == NFD_FP32) {
-        hipLaunchKernelGGL(nfd::attn_fwd_generic<float>, dim3(pl.n_workgroups), dim3(nfd::kGenericWaves * 64), 0, st, p);
     } else {
-        hipLaunchKernelGGL(nfd::attn_fwd_generic<__bf16>, dim3(pl.n_workgroups), dim3(nfd::kGenericWaves * 64), 0, st, p);
+        const bool vec = D == nfd::general::padded_width(D) && ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) % 16 == 0;
+        general_dispatch(h->dtype, D, vec, pl.block_m / 16, [&](auto e, auto dp, auto v16, auto cols) {
+            hipLaunchKernelGGL((nfd::general::attn_fwd_general<decltype(e), decltype(dp)::value, decltype(v16)::value, decltype(cols)::value>),
+                               dim3(pl.n_workgroups), dim3(nfd::general::kWaves * 64), 0, st, p);
+        });
     }
     return check_hip(h, hipGetLastError(), "attention launch");
 }
@@ -501,12 +532,13 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
         // general path: fp32 arithmetic, one wavefront per row
         if ((size_t)(BH * Sq) * sizeof(float) > h->workspace_bytes)
             return fail(h, NFD_ERR_ALLOC, "the per-row workspace of the backward exceeds the handle's workspace");
-        const int64_t gq = (BH * Sq + nfd::kGenericWaves - 1) / nfd::kGenericWaves;
-        const int64_t gk = (BH * Sk + nfd::kGenericWaves - 1) / nfd::kGenericWaves;
-        if (gq > (int64_t)0x7fffffff || gk > (int64_t)0x7fffffff)
+        nfd::general::BwdParams g{};
+        const int cq = nfd::general::cols_per_workgroup(Sq, BH, D, h->num_cus), ck = nfd::general::cols_per_workgroup(Sk, BH, D, h->num_cus);
+        g.n_q_tiles = (int)((Sq + 16 * cq - 1) / (16 * cq));
+        g.n_k_tiles = (int)((Sk + 16 * ck - 1) / (16 * ck));
+        if (BH * g.n_q_tiles > (int64_t)0x7fffffff || BH * g.n_k_tiles > (int64_t)0x7fffffff)
             return fail(h, NFD_ERR_UNSUPPORTED, "too many rows for one launch of the general backward");
         if (!(scale > 0.f)) scale = 1.0f / std::sqrt((float)D);
-        nfd::BwdGenericParams g{};
         g.q = q; g.k = k; g.v = v; g.out = out; g.dout = dout; g.lse = lse;
         g.delta = (float*)h->workspace;
         g.dq = dq; g.dk = dk; g.dv = dv;
@@ -514,14 +546,17 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
         g.scale = scale;
         g.scale_log2e = scale * nfd::kLog2e;
         hipStream_t gs = (hipStream_t)stream;
-        const dim3 blk(nfd::kGenericWaves * 64);
-        if (h->dtype == NFD_BF16) {
-            hipLaunchKernelGGL(nfd::attn_bwd_dq_generic<__bf16>, dim3((unsigned)gq), blk, 0, gs, g);
-            hipLaunchKernelGGL(nfd::attn_bwd_dkdv_generic<__bf16>, dim3((unsigned)gk), blk, 0, gs, g);
-        } else {
-            hipLaunchKernelGGL(nfd::attn_bwd_dq_generic<float>, dim3((unsigned)gq), blk, 0, gs, g);
-            hipLaunchKernelGGL(nfd::attn_bwd_dkdv_generic<float>, dim3((unsigned)gk), blk, 0, gs, g);
-        }
+        const dim3 blk(nfd::general::kWaves * 64);
+        const bool vec = D == nfd::general::padded_width(D) &&
+                         ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)dout) % 16 == 0;
+        general_dispatch(h->dtype, D, vec, cq, [&](auto e, auto dp, auto v16, auto cols) {
+            hipLaunchKernelGGL((nfd::general::attn_bwd_dq_general<decltype(e), decltype(dp)::value, decltype(v16)::value, decltype(cols)::value>),
+                               dim3((unsigned)(BH * g.n_q_tiles)), blk, 0, gs, g);
+        });
+        general_dispatch(h->dtype, D, vec, ck, [&](auto e, auto dp, auto v16, auto cols) {
+            hipLaunchKernelGGL((nfd::general::attn_bwd_dkdv_general<decltype(e), decltype(dp)::value, decltype(v16)::value, decltype(cols)::value>),
+                               dim3((unsigned)(BH * g.n_k_tiles)), blk, 0, gs, g);
+        });
         return check_hip(h, hipGetLastError(), "general backward launch");
     }
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk |
