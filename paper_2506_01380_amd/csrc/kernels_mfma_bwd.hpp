@@ -9,6 +9,9 @@
 //                          delta_i = <do_i, o_i> of its rows (dout is in its registers anyway) and stores -delta_i
 //                          and lse_i log2(e), the two per-row values in the form the dk/dv kernel consumes them
 //   attn_bwd_dkdv_bf16_d64 key-major: a wavefront owns 48 keys and walks over the query tiles that see them
+// or, where those would not fill the chip for long (the rule and its figures are at bwd_form on the host):
+//   attn_bwd_delta         the two per-row values alone
+//   attn_bwd_merged        work items of both kinds in one launch, in two sizes
 // Both matrix kernels recompute the weights from the stored log-sum-exp, so no online softmax is
 // needed, and both keep the operand whose rows they own in registers for the whole kernel.  Tiles
 // of the other operand go global -> LDS directly into the same XOR-swizzled ring as in the forward
@@ -16,7 +19,7 @@
 // operand unchanged (the contraction index is permuted identically on the A side by the transposing
 // LDS read), so neither P nor dS ever touches LDS.
 //
-// Register budget: both kernels run two wavefronts per SIMD - the dq kernel by forming the scores of
+// Register budget: the separate kernels run two wavefronts per SIMD - the dq kernel by forming the scores of
 // 32 keys and 16 queries at a time, the dk/dv kernel by owning 48 keys per wavefront.  S and dP are formed in both
 // kernels (seven products for the five of the mathematics): the price of having no atomics on dq.
 #pragma once
@@ -90,19 +93,17 @@ __device__ __forceinline__ void dma_tile_pair(const __bf16* a, const __bf16* b, 
 // exponent's fma, and dP^T starts from -delta (a four-register C operand per column block, kept for the whole kernel),
 // so dP - delta costs no instruction.  The four column blocks are worked one after the other on the same K, V and K^T
 // fragments: a quarter of the scores live at a time.
-__global__ void __launch_bounds__(256, 2)
-attn_bwd_dq_bf16_d64(BwdParams p) {
-    __shared__ SmemRing sm;
-    const BwdItem wi = decode_bwd(p.BH, p.n_q_tiles);
-    if (!wi.valid) return;
+template <int NCQ, bool DELTA, typename Ring>
+__device__ __forceinline__ void bwd_dq_item(const BwdParams& p, const BwdItem& wi, Ring& sm) {
+    constexpr int kWaveRows = 16 * NCQ;
     const int q_tile = p.n_q_tiles - 1 - wi.item;  // heaviest (latest frames) first
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
     auto sg = [](int x) { return (0x78 >> (2 * x)) & 3; };  // 0, 2, 3, 1
-    const int r0 = q_tile * kBM;
-    const int r_last = min(r0 + kBM, p.Sq) - 1;
+    const int r0 = q_tile * 4 * kWaveRows;
+    const int r_last = min(r0 + 4 * kWaveRows, p.Sq) - 1;
     const int n_tiles = (kmax_of_row(r_last, p.T, p.P) + kBN - 1) / kBN;
 
     const __bf16* qg = (const __bf16*)p.q + (int64_t)wi.bh * p.Sq * kD;
@@ -111,20 +112,30 @@ attn_bwd_dq_bf16_d64(BwdParams p) {
     const __bf16* kg = (const __bf16*)p.k + (int64_t)wi.bh * p.Scap * kD;
     const __bf16* vg = (const __bf16*)p.v + (int64_t)wi.bh * p.Scap * kD;
 
-    const int rw0 = r0 + wave * 64;
-    float lse2[4];
-    f32x4 ndl[4];            // [cq] -delta of the lane's query in all four elements: the C operand dP^T starts from
-    bf16x8 qf[4][2], gf[4][2];  // [cq][ks]
+    const int rw0 = r0 + wave * kWaveRows;
+    float lse2[NCQ];
+    f32x4 ndl[NCQ];          // [cq] -delta of the lane's query in all four elements: the C operand dP^T starts from
+    bf16x8 qf[NCQ][2], gf[NCQ][2];  // [cq][ks]
 #pragma unroll
-    for (int cq = 0; cq < 4; ++cq) {
+    for (int cq = 0; cq < NCQ; ++cq) {
         const int row = rw0 + 16 * cq + j;
         const int rc = min(row, p.Sq - 1);  // ragged tail: compute a duplicate, never store it
-        lse2[cq] = p.lse[(int64_t)wi.bh * p.Sq + rc] * kLog2e;
-        float part = 0.f;  // this lane's quarter of <dout_i, out_i>: the features it holds of dout
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             qf[cq][ks] = *(const bf16x8*)(qg + (int64_t)rc * kD + 32 * ks + 8 * g);
             gf[cq][ks] = *(const bf16x8*)(gg + (int64_t)rc * kD + 32 * ks + 8 * g);
+        }
+        if constexpr (!DELTA) {
+            const float nd = p.neg_delta[(int64_t)wi.bh * p.Sq + rc];
+            lse2[cq] = p.lse2[(int64_t)wi.bh * p.Sq + rc];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ndl[cq][e] = nd;
+            continue;
+        }
+        lse2[cq] = p.lse[(int64_t)wi.bh * p.Sq + rc] * kLog2e;
+        float part = 0.f;  // this lane's quarter of <dout_i, out_i>: the features it holds of dout
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
             const bf16x8 of = *(const bf16x8*)(og_ + (int64_t)rc * kD + 32 * ks + 8 * g);
 #pragma unroll
             for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)gf[cq][ks][e], (float)of[e], part);
@@ -139,12 +150,12 @@ attn_bwd_dq_bf16_d64(BwdParams p) {
         }
     }
     const int kmin_wave = kmax_of_row(min(rw0, p.Sq - 1), p.T, p.P);
-    const int kmax_wave = kmax_of_row(min(rw0 + 63, p.Sq - 1), p.T, p.P);
+    const int kmax_wave = kmax_of_row(min(rw0 + kWaveRows - 1, p.Sq - 1), p.T, p.P);
     const bool wave_active = rw0 < p.Sq;
 
-    f32x4 dq_acc[4][4];  // [cq][fb]: query 16 cq + j, features 16 fb + 4 g + e
+    f32x4 dq_acc[NCQ][4];  // [cq][fb]: query 16 cq + j, features 16 fb + 4 g + e
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NCQ; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -211,7 +222,7 @@ attn_bwd_dq_bf16_d64(BwdParams p) {
                     kt[fb] = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 }
 #pragma unroll
-                for (int cq = 0; cq < 4; ++cq) {  // one column block of queries at a time: a quarter of the scores live
+                for (int cq = 0; cq < NCQ; ++cq) {  // one column block of queries at a time: a quarter of the scores live
                     f32x4 s_acc[2], dp_acc[2];    // [key block]
 #pragma unroll
                     for (int b2 = 0; b2 < 2; ++b2) {
@@ -260,7 +271,7 @@ attn_bwd_dq_bf16_d64(BwdParams p) {
 
     if (!wave_active) return;
 #pragma unroll
-    for (int cq = 0; cq < 4; ++cq) {
+    for (int cq = 0; cq < NCQ; ++cq) {
         const int row = rw0 + 16 * cq + j;
         if (row >= p.Sq) continue;
         __bf16* og = (__bf16*)p.dq + ((int64_t)wi.bh * p.Sq + row) * kD;
@@ -272,8 +283,16 @@ attn_bwd_dq_bf16_d64(BwdParams p) {
     }
 }
 
+__global__ void __launch_bounds__(256, 2)
+attn_bwd_dq_bf16_d64(BwdParams p) {
+    __shared__ SmemRing sm;
+    const BwdItem wi = decode_bwd(p.BH, p.n_q_tiles);
+    if (!wi.valid) return;
+    bwd_dq_item<4, true>(p, wi, sm);
+}
+
 // ---------------------------------------------------------------------------------------------
-// dk, dv: a workgroup owns 192 keys (4 wavefronts x 48, two wavefronts per SIMD) and walks over the 64-row query
+// dk, dv: a workgroup owns 192 keys (4 wavefronts x 48, two wavefronts per SIMD; NCK = 3 column blocks a wavefront) and walks over the 64-row query
 // tiles that can see them (all rows from the first frame that sees the block's first key).
 //   S = Q.K^T, dP = dO.V^T (A = Q / dO rows from LDS, B = K^T / V^T in registers)
 //   dV^T += dO^T.P, dK^T += Q^T.dS (A by transposing reads of the dO / Q tile, B = P / dS accumulators)
@@ -309,19 +328,16 @@ constexpr int kBwdKvSlots = 4;
 // two wavefronts per SIMD leave room for: 252 VGPRs, no spills (two blocks: 178; four: 118 spilled dwords).  Measured
 // on one box, whole backward at 16 frames of 336 tokens: 0.776 ms with two blocks, 0.742 with three.
 constexpr int kBwdColBlocks = 3;
-constexpr int kBwdKeysPerWorkgroup = 4 * 16 * kBwdColBlocks;
+template <int SLOTS>
 struct __attribute__((aligned(16))) SmemBwdKv {
-    __bf16 q[kBwdKvSlots][kTileElems];
-    __bf16 g[kBwdKvSlots][kTileElems];
-    float ld[kBwdKvSlots][4][64];  // per slot: [0] lse * log2e, [1] -delta, [2], [3] the other two wavefronts' copies
+    __bf16 q[SLOTS][kTileElems];
+    __bf16 g[SLOTS][kTileElems];
+    float ld[SLOTS][4][64];  // per slot: [0] lse * log2e, [1] -delta, [2], [3] the other two wavefronts' copies
 };
 
-__global__ void __launch_bounds__(256, 2)
-attn_bwd_dkdv_bf16_d64(BwdParams p) {
-    constexpr int NCK = kBwdColBlocks, kWaveKeys = 16 * NCK;
-    __shared__ SmemBwdKv sm;
-    const BwdItem wi = decode_bwd(p.BH, p.n_k_blocks);
-    if (!wi.valid) return;
+template <int NCK, int SLOTS>
+__device__ __forceinline__ void bwd_dkdv_item(const BwdParams& p, const BwdItem& wi, SmemBwdKv<SLOTS>& sm) {
+    constexpr int kWaveKeys = 16 * NCK;
     const int k_block = wi.item;  // block 0 is seen by every row: heaviest first
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -411,19 +427,19 @@ attn_bwd_dkdv_bf16_d64(BwdParams p) {
     };
 
 #pragma unroll
-    for (int i = 0; i < kBwdKvSlots - 1; ++i)
+    for (int i = 0; i < SLOTS - 1; ++i)
         if (t_begin + i < t_end) load_tile(t_begin + i, i);
     wait_vmem_all();
 
-    int slot = 0, slot_load = kBwdKvSlots - 1;
+    int slot = 0, slot_load = SLOTS - 1;
     for (int t = t_begin; t < t_end; ++t) {
         __builtin_amdgcn_sched_barrier(0);
-        if (kBwdKvSlots > 3 && t + 2 < t_end) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+        if (SLOTS > 3 && t + 2 < t_end) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
         else if (t + 1 < t_end) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        if (t + kBwdKvSlots - 1 < t_end) load_tile(t + kBwdKvSlots - 1, slot_load);
+        if (t + SLOTS - 1 < t_end) load_tile(t + SLOTS - 1, slot_load);
         const int i0 = t * 64;
         if (wave_active && i0 + 64 > rmin_wave) {
             const __bf16* qs_ = sm.q[slot];
@@ -500,8 +516,8 @@ attn_bwd_dkdv_bf16_d64(BwdParams p) {
                 }
             }
         }
-        slot = slot == kBwdKvSlots - 1 ? 0 : slot + 1;
-        slot_load = slot_load == kBwdKvSlots - 1 ? 0 : slot_load + 1;
+        slot = slot == SLOTS - 1 ? 0 : slot + 1;
+        slot_load = slot_load == SLOTS - 1 ? 0 : slot_load + 1;
     }
 
     if (!wave_active) return;
@@ -516,6 +532,57 @@ attn_bwd_dkdv_bf16_d64(BwdParams p) {
             *(bf16x4*)(dkg + 16 * fb + 4 * g) = __builtin_convertvector(xk, bf16x4);
             *(bf16x4*)(dvg + 16 * fb + 4 * g) = __builtin_convertvector(dv_acc[fb][ck], bf16x4);
         }
+    }
+}
+
+__global__ void __launch_bounds__(256, 2)
+attn_bwd_dkdv_bf16_d64(BwdParams p) {
+    __shared__ SmemBwdKv<kBwdKvSlots> sm;
+    const BwdItem wi = decode_bwd(p.BH, p.n_k_blocks);
+    if (!wi.valid) return;
+    bwd_dkdv_item<kBwdColBlocks>(p, wi, sm);
+}
+
+// -delta_i = -<dout_i, out_i> and lse_i log2(e) of every query row, eight lanes a row.
+__global__ void __launch_bounds__(256)
+attn_bwd_delta(BwdParams p) {
+    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x, row = x >> 3;
+    if (row >= (int64_t)p.BH * p.Sq) return;
+    const bf16x8 a = ((const bf16x8*)p.dout)[x], b = ((const bf16x8*)p.out)[x];
+    float d = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d = __builtin_fmaf((float)a[e], (float)b[e], d);
+    d += __shfl_xor(d, 1);
+    d += __shfl_xor(d, 2);
+    d += __shfl_xor(d, 4);
+    if ((threadIdx.x & 7) == 0) {
+        p.neg_delta[row] = -d;
+        p.lse2[row] = p.lse[row] * kLog2e;
+    }
+}
+
+// Both kinds of work items in one launch, dealt in proportion so that both start with their longest chains.
+// <4, 3, 4, 2> holds the items of the separate kernels (254 VGPRs); <2, 1, 3, 3> items of 128 query rows or 64 keys at
+// three workgroups per CU (166 VGPRs, 52 KB LDS).  Also measured: 128 rows with 128 keys at two workgroups per CU (71 us
+// where the small one takes 66, 12 heads x 11 frames of 247), at three (spills: 85), 64 rows with 64 keys (as the small one).
+template <int NCQ, int NCK, int SLOTS, int OCC>
+__global__ void __launch_bounds__(256, OCC)
+attn_bwd_merged(BwdParams p) {
+    __shared__ union Smem {
+        SmemRing dq;
+        SmemBwdKv<SLOTS> kv;
+        __device__ Smem() {}
+    } sm;
+    const int n = p.n_q_tiles + p.n_k_blocks;
+    BwdItem wi = decode_bwd(p.BH, n);
+    if (!wi.valid) return;
+    const int kv0 = (int)((int64_t)wi.item * p.n_k_blocks / n), kv1 = (int)((int64_t)(wi.item + 1) * p.n_k_blocks / n);
+    if (kv1 > kv0) {
+        wi.item = kv0;
+        bwd_dkdv_item<NCK>(p, wi, sm.kv);
+    } else {
+        wi.item -= kv0;
+        bwd_dq_item<NCQ, false>(p, wi, sm.dq);
     }
 }
 

@@ -69,6 +69,42 @@ size_t elem_size(nfd_dtype_t dt) { return dt == NFD_BF16 ? 2 : 4; }
 // frames up to and including its own).
 int64_t kmax_rows(int64_t r_last, int T, int P) { return ((int64_t)P + r_last / T + 1) * T; }
 
+// How the matrix-core backward is launched.  A workgroup's time is a chain of 64-row steps (key tiles for dq, query tiles
+// for dk/dv; a frame boundary's triangle makes their lengths differ), and per step the two kinds cost about the same:
+//   kSeparate     dq kernel, then dk/dv kernel: each launch ends on its own tail of few running workgroups
+//   kMerged       one launch holds both kinds (the per-row values come from a small launch before it): one tail
+//   kMergedSmall  the same with 128 query rows / 64 keys per workgroup: links of 0.97 us instead of 1.57, three workgroups
+//                 per CU instead of two, but more steps and more LDS traffic per product (1.93 / 3 against 2.7 / 2 us of
+//                 CU time per step when the chip is full)
+// Total steps over the workgroup slots, plus half of the longest chain, orders the last two; once the launch is more than
+// three chains deep the tails no longer matter and the separate kernels win, whose workgroups share their tiles in L2.
+// Measured, backward of 16 frames of 336 tokens (us; separate / merged / merged small): 12 heads 280 / 175 / 188, 24 heads
+// 340 / 302 / 341, 48 heads 590 / 574 / 705, 64 heads 763 / 777 / 943; 12 heads, 11 frames of 247: 156 / 85 / 66;
+// 192 heads, 20 frames of 40: 116 / 100 / 94; 32 heads, 64 frames of 576: 16 180 / 17 040 / 22 900.
+enum class BwdForm { kSeparate, kMerged, kMergedSmall };
+BwdForm bwd_form(int64_t BH, int64_t Sq, int64_t Sk, int T, int P, int num_cus) {
+    int64_t longest = 0;
+    auto steps = [&](int rows, int keys, int fixed) {  // of all heads, `fixed` more per workgroup
+        int64_t n = 0;
+        for (int64_t r = 0; r < Sq; r += rows) {
+            const int64_t t = (kmax_rows(std::min(r + rows, Sq) - 1, T, P) + 63) / 64;
+            longest = std::max(longest, t);
+            n += t + fixed;
+        }
+        for (int64_t k = 0; k < Sk; k += keys) {
+            const int64_t t = (Sq + 63) / 64 - std::max<int64_t>(0, (k / T - P) * T) / 64;
+            longest = std::max(longest, t);
+            n += t + fixed;
+        }
+        return (double)(n * BH);
+    };
+    if (steps(256, 192, 0) / (2.0 * num_cus) > 3.0 * longest) return BwdForm::kSeparate;
+    // a workgroup's first loads and final write cost about three steps
+    const double w = steps(256, 192, 3) / (2.0 * num_cus), ws = steps(128, 64, 3) / (3.0 * num_cus);
+    const double merged = std::max(2.7 * w + 0.5 * 1.57 * longest, 1.57 * longest);
+    return std::max(1.93 * ws + 0.5 * 0.97 * longest, 0.97 * longest) < merged ? BwdForm::kMergedSmall : BwdForm::kMerged;
+}
+
 // Call f with the instance of the general kernels for these arguments: (element type, padded width, 16-byte loads, 16-column
 // blocks per workgroup).
 template <typename Launch>
@@ -572,18 +608,26 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
     p.lse2 = p.neg_delta + BH * Sq;
     p.dq = dq; p.dk = dk; p.dv = dv;
     p.BH = (int)BH; p.Sq = (int)Sq; p.Sk = (int)Sk; p.Scap = F * T; p.T = T; p.P = kv_frames - q_frames;
-    p.n_q_tiles = (int)((Sq + nfd::mfma::kBM - 1) / nfd::mfma::kBM);
-    p.n_k_blocks = (int)((Sk + nfd::mfma::kBwdKeysPerWorkgroup - 1) / nfd::mfma::kBwdKeysPerWorkgroup);
+    const BwdForm pick = bwd_form(BH, Sq, Sk, T, kv_frames - q_frames, h->num_cus);
+    const int rows = pick == BwdForm::kMergedSmall ? 128 : 256, keys = pick == BwdForm::kMergedSmall ? 64 : 192;
+    p.n_q_tiles = (int)((Sq + rows - 1) / rows);
+    p.n_k_blocks = (int)((Sk + keys - 1) / keys);
     p.scale = scale;
     p.scale_log2e = scale * nfd::kLog2e;
-    if (BH * p.n_q_tiles > (int64_t)0x7fffffff || BH * p.n_k_blocks > (int64_t)0x7fffffff)
+    if (BH * ((int64_t)p.n_q_tiles + p.n_k_blocks) > (int64_t)0x7fffffff)
         return fail(h, NFD_ERR_UNSUPPORTED, "too many workgroups for one launch of the backward");
     if (const int dc = check_device(h)) return dc;
     hipStream_t st = (hipStream_t)stream;
-    const unsigned heads8 = (unsigned)BH;  // one workgroup per (head, item)
-    // the dq kernel first: it writes the two per-row vectors that the dk/dv kernel reads
-    hipLaunchKernelGGL(nfd::mfma::attn_bwd_dq_bf16_d64, dim3(heads8 * p.n_q_tiles), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(nfd::mfma::attn_bwd_dkdv_bf16_d64, dim3(heads8 * p.n_k_blocks), dim3(256), 0, st, p);
+    if (pick == BwdForm::kSeparate) {
+        // the dq kernel first: it writes the two per-row vectors that the dk/dv kernel reads
+        hipLaunchKernelGGL(nfd::mfma::attn_bwd_dq_bf16_d64, dim3((unsigned)(BH * p.n_q_tiles)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL(nfd::mfma::attn_bwd_dkdv_bf16_d64, dim3((unsigned)(BH * p.n_k_blocks)), dim3(256), 0, st, p);
+    } else {
+        hipLaunchKernelGGL(nfd::mfma::attn_bwd_delta, dim3((unsigned)((BH * Sq * 8 + 255) / 256)), dim3(256), 0, st, p);
+        const dim3 grid((unsigned)(BH * (p.n_q_tiles + p.n_k_blocks)));
+        if (pick == BwdForm::kMerged) hipLaunchKernelGGL((nfd::mfma::attn_bwd_merged<4, 3, 4, 2>), grid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((nfd::mfma::attn_bwd_merged<2, 1, 3, 3>), grid, dim3(256), 0, st, p);
+    }
     return check_hip(h, hipGetLastError(), "backward launch");
 }
 
