@@ -1,11 +1,10 @@
 // bf16 matrix-core forward kernels for head width 64 (gfx950 / CDNA4): what all shapes share, and the shapes built
-// on the 32x32x16 matrix instruction - the 128-row latency shape, and both shapes over the 8-bit cache.  The 256-row
-// throughput shape over a bf16 cache is in kernels_mfma16.hpp (same structure, 16x16x32 instruction).
+// on the 32x32x16 matrix instruction - the 128-row latency shape, over a bf16 and over the 8-bit cache.  The 256-row
+// throughput shape is in kernels_mfma16.hpp (same structure, 16x16x32 instruction).
 //
-// Flash-style online softmax.  A workgroup of 4 wavefronts owns up to 256 consecutive query rows of
+// Flash-style online softmax.  A workgroup of 4 wavefronts owns up to 128 consecutive query rows of
 // one (batch, head) - the 32-row blocks of a head are dealt evenly to its query tiles -; each wavefront
-// owns 64 of them as two 32-wide column blocks (blocks w and w + 4 of the workgroup's eight; a single
-// block where the tile has fewer) of the TRANSPOSED score matrix:
+// owns one 32-wide column block of the TRANSPOSED score matrix (two in the 256-row shape):
 //
 //   S^T[key, query] = K_tile[key, :] . Q^T[:, query]       v_mfma_f32_32x32x16_bf16, A = K (LDS), B = Q^T (registers)
 //   O^T[d,   query] += V_tile^T[d, key] . P^T[key, query]  A = V^T (LDS, transposing read), B = P^T (registers)
@@ -84,6 +83,8 @@ constexpr int kPipeSlots = 4;
 struct __attribute__((aligned(16))) SmemRingPipe {
     __bf16 k[kPipeSlots][kTileElems];
     __bf16 v[kPipeSlots][kTileElems];
+    __device__ void* in_k() { return k; }  // where the tile loads land
+    __device__ void* in_v() { return v; }
 };
 
 // 8-bit cache (E4M3 codes): a K tile is 64 keys x 64 features, a V tile 64 features x 64 keys (V is stored
@@ -97,15 +98,16 @@ struct __attribute__((aligned(16))) SmemRing8 {
 };
 __device__ __forceinline__ int chunk_swizzle8(int r) { return (r >> 2) & 3; }
 
-// 64-row workgroup shape over the 8-bit cache: the four wavefronts widen each tile ONCE, together, from the
-// ring of code tiles into a double-buffered pair of bf16 tiles in the bf16 kernel's layout (V with the 8 keys of
-// one matrix operand contiguous), one tile ahead of its use; the products then read bf16 fragments.  16
-// conversions per wavefront and tile instead of 64.
-struct __attribute__((aligned(16))) SmemRing8Wide {
-    unsigned char k[kRingSlots][kTileElems];
-    unsigned char v[kRingSlots][kTileElems];
-    __bf16 kb[2][kTileElems];
-    __bf16 vb[2][kTileElems];
+// 256-row shape over the 8-bit cache: the four wavefronts widen each tile ONCE, together, from the ring of code tiles
+// into a ring of bf16 tiles in the bf16 kernel's layout (V with the 8 keys of one matrix operand contiguous), ahead of
+// its use; the products then read bf16 fragments.  16 conversions per wavefront and tile instead of 64.  72 KB.
+struct __attribute__((aligned(16))) SmemRingPipe8 {
+    unsigned char k8[kRingSlots][kTileElems];
+    unsigned char v8[kRingSlots][kTileElems];
+    __bf16 k[kRingSlots][kTileElems];
+    __bf16 v[kRingSlots][kTileElems];
+    __device__ void* in_k() { return k8; }
+    __device__ void* in_v() { return v8; }
 };
 
 // Eight E4M3 codes (two dwords, lowest byte first) widened to bf16; every E4M3 value is a bf16 value.
@@ -227,34 +229,31 @@ __device__ __forceinline__ void store_rows(const FwdParams& p, const WorkItem& w
     }
 }
 
-// QT = 2: 64 query rows per wavefront, 256 per workgroup, two wavefronts per SIMD: the throughput shape.
-// QT = 1: 32 rows per wavefront, 128 per workgroup, three wavefronts per SIMD: half the softmax and half the
-// matrix work per tile and wavefront, i.e. a shorter chain per key tile, for calls with few query rows whose
+// The 128-row shape: 32 rows per wavefront, three wavefronts per SIMD: half the softmax and half the matrix work per
+// tile and wavefront of the 256-row shape, i.e. a shorter chain per key tile, for calls with few query rows whose
 // time is the length of that chain (cached forms); it reads twice the LDS bytes per FLOP.
 //
-// KV8: K and V come from the 8-bit cache and are widened to bf16 (exact) before they reach the matrix operands;
-// the per-head scales are folded into the softmax scale (K) and the final write (V), so the arithmetic between
-// the operands is the same as for a bf16 cache.  QT = 1: every wavefront widens its own fragments on their way
-// out of LDS (SmemRing8); the feature order inside the first product's contraction is then permuted (a 16-byte
-// read serves two steps), the same way for K and Q.  QT = 2: the workgroup widens each tile once (SmemRing8Wide).
+// KV8: K and V come from the 8-bit cache and are widened to bf16 (exact) before they reach the matrix operands, by
+// every wavefront on the way of its own fragments out of LDS (SmemRing8); the feature order inside the first
+// product's contraction is then permuted (a 16-byte read serves two steps), the same way for K and Q.  The per-head
+// scales are folded into the softmax scale (K) and the final write (V), so the arithmetic between the operands is the
+// same as for a bf16 cache.
 //
 // EXACTQ: the forward of the training pair, which also writes the log-sum-exp the backward normalises with.  The
 // queries enter the first product as given, the scores are exact sums of products of the inputs, and the softmax
 // scale is applied to the fp32 scores (one multiply per score); the reference max is then kept in raw score units.
 // Without it the scale is folded into the query fragments (one more bf16 rounding of an input, no multiply).
-template <int QT, bool KV8>
+template <bool KV8>
 struct SmemOf {
-    static_assert(QT == 1 || KV8, "the 256-row shape over a bf16 cache is attn_fwd_item16");
-    static constexpr bool WIDE = KV8 && QT == 2;   // tiles widened once per workgroup (see SmemRing8Wide)
-    typedef typename std::conditional<WIDE, SmemRing8Wide, typename std::conditional<KV8, SmemRing8, SmemRing>::type>::type type;
+    typedef typename std::conditional<KV8, SmemRing8, SmemRing>::type type;
 };
 
 // One work item (head, query tile, key split) from the first load to the final write.  Every wavefront of the
 // workgroup passes the same barriers and returns; the LDS ring may be reused after a workgroup barrier.
-template <int QT, bool KV8, bool EXACTQ>
-__device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem& wi, typename SmemOf<QT, KV8>::type& sm) {
+template <bool KV8, bool EXACTQ>
+__device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem& wi, typename SmemOf<KV8>::type& sm) {
     constexpr int PRIO = kMfmaPriority;
-    constexpr bool WIDE = SmemOf<QT, KV8>::WIDE;
+    constexpr int QT = 1;  // 32-row blocks per wavefront
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -301,12 +300,6 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
     }
 
     // ---- this wavefront's queries -------------------------------------------------------
-    // QT = 2: the wavefront owns the 32-row blocks `wave` and `wave + 4` of the workgroup's (up to) eight, not two
-    // adjacent ones.  Where a frame boundary falls inside the workgroup, the later frame's extra key tiles are
-    // then shared by all four wavefronts (each running one block) instead of keeping the last wavefronts busy
-    // with two blocks while the first ones idle.  In a tile of fewer than eight blocks the wavefronts without a
-    // block `wave + 4` own block `wave` alone, as their LATER block: the earlier one is dead (no rows, key bound 0),
-    // so every tile runs in the second, one-block loop and nothing is computed for rows that do not exist.
     // The softmax scale (times log2 e, times the K scale of an 8-bit cache) is folded into the query fragments once,
     // rounded to bf16: the score accumulators then hold base-2 exponents directly and the softmax needs no multiply.
     float c = p.scale_log2e;
@@ -316,19 +309,17 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
     bf16x8 qf[QT][4];
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
-        const bool pair = QT == 2 && wave + kWaves < n_blk;   // this wavefront has two blocks
-        const bool dead = QT == 2 && qt == 0 && !pair;         // single block: it is block index 1
-        const int b0 = r0 + 32 * (QT == 2 && qt == 1 && pair ? wave + kWaves : wave);
-        row[qt] = dead ? 0x40000000 : b0 + n;                  // dead rows are never stored
+        const int b0 = r0 + 32 * wave;
+        row[qt] = b0 + n;
         const int rc = min(row[qt], p.Sq - 1);  // rows past the end: compute a duplicate, never store it
         kmax_lane[qt] = kmax_of_row(rc, p.T, p.P);
-        kmin_blk[qt] = dead ? 0 : kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
-        kmax_blk[qt] = dead ? 0 : kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);
+        kmin_blk[qt] = kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
+        kmax_blk[qt] = kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             // contraction step ks, lane half h: features 16*ks + 8*h ..+7; with the 8-bit cache the features of
             // the 16-byte chunk 2*(ks/2) + h, first or second half (ks % 2) - the order the K reads deliver
-            const int d0 = KV8 && !WIDE ? 16 * (2 * (ks >> 1) + h) + 8 * (ks & 1) : 16 * ks + 8 * h;
+            const int d0 = KV8 ? 16 * (2 * (ks >> 1) + h) + 8 * (ks & 1) : 16 * ks + 8 * h;
             const bf16x8 raw = *(const bf16x8*)(qg + (int64_t)rc * kD + d0);
             if constexpr (EXACTQ) {
                 qf[qt][ks] = raw;
@@ -433,42 +424,9 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
     for (int kp = 0; kp < 2; ++kp) k_off8[kp] = n * kD + 16 * ((2 * kp + h) ^ f8);
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) v_off8[ch] = n * kBN + 16 * (ch ^ f8) + 8 * (h ^ ((n >> 4) & 1));
-    // Widened tiles (WIDE): V^T rows of 64 bf16 whose 16-byte chunk 2*ch + h holds the 8 keys lane half h needs of
-    // the 16-key chunk ch; read like K, with K's offsets (k_off[ch]).  A lane widens the 16 codes of chunk cv_c of tile row cv_row of both
-    // tensors.  Eight consecutive lanes take the eight even (or odd) rows of the wavefront's 16: the 16-byte
-    // stores of such a group then fall on eight different chunk positions of the 128-byte rows (stores are
-    // served eight lanes at a time), and the 16-byte loads stay conflict-free (measured: 0 conflict cycles
-    // for both; 16 consecutive rows per 16 lanes cost a two-way conflict on either side).
-    const int cv_row = 16 * wave + 2 * (lane & 7) + ((lane >> 3) & 1), cv_c = lane >> 4;
-    const int cv_src = cv_row * 64 + 16 * (cv_c ^ chunk_swizzle8(cv_row));
-    const int cv_f = chunk_swizzle(cv_row), cv_s = (cv_row >> 4) & 1;
-    // destinations (elements): the two halves of a chunk go to chunk positions that differ in their lowest bit
-    const int cv_k0 = cv_row * kD + 8 * ((2 * cv_c) ^ cv_f);
-    const int cv_v0 = cv_row * kD + 8 * ((2 * cv_c + cv_s) ^ cv_f);
-    auto widen_tile = [&](int t, int fslot, int buf) {
-        if constexpr (WIDE) {
-            const u32x4 rk = *(const u32x4*)(sm.k[fslot] + cv_src);
-            u32x4 rv = *(const u32x4*)(sm.v[fslot] + cv_src);
-            const int j0 = t * kBN;
-            if (j0 + kBN > p.Sk) {  // last tile of the cache: V codes at or past the end count as zero
-#pragma unroll
-                for (int x = 0; x < 2; ++x) {  // bytes 8x..8x+7: keys 4hh..4hh+3 and 8+4hh.. of the chunk, hh = x ^ s
-                    const int left = p.Sk - (j0 + 16 * cv_c + 4 * (x ^ cv_s));
-                    rv[2 * x] = left >= 4 ? rv[2 * x] : left <= 0 ? 0u : rv[2 * x] & ((1u << (8 * left)) - 1u);
-                    rv[2 * x + 1] = left >= 12 ? rv[2 * x + 1] : left <= 8 ? 0u : rv[2 * x + 1] & ((1u << (8 * (left - 8))) - 1u);
-                }
-            }
-            *(bf16x8*)(sm.kb[buf] + cv_k0) = widen_e4m3x8(rk[0], rk[1]);
-            *(bf16x8*)(sm.kb[buf] + (cv_k0 ^ 8)) = widen_e4m3x8(rk[2], rk[3]);
-            *(bf16x8*)(sm.vb[buf] + cv_v0) = widen_e4m3x8(rv[0], rv[1]);
-            *(bf16x8*)(sm.vb[buf] + (cv_v0 ^ 8)) = widen_e4m3x8(rv[2], rv[3]);
-        }
-    };
 
     if (t_begin < t_end) load_tile(t_begin, 0);
     if (t_begin + 1 < t_end) load_tile(t_begin + 1, 1);
-    if constexpr (WIDE)
-        if (t_begin + 2 < t_end) load_tile(t_begin + 2, 2);
     // The Q fragments are complete from here on and the compiler knows it: no later guard on them
     // can drain the tile prefetch.  (This also lands tiles 0 and 1, once per workgroup.)
     wait_vmem_all();
@@ -488,17 +446,15 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
         if constexpr (EXACTQ) return __builtin_fmaf(s, c, -ref_exponent);
         else return s - ref_exponent;
     };
-    // QA = first block of the wavefront that still has visible keys in this tile (1: its earlier block is done)
-    auto tile_body = [&](int t, int slot, auto qa_tag) {
-        constexpr int QA = decltype(qa_tag)::value;
+    auto tile_body = [&](int t, int slot) {
         const int j0 = t * kBN;
         {
-            const auto* ks_ = [&]() { if constexpr (WIDE) return sm.kb[slot]; else return sm.k[slot]; }();
-            const auto* vs_ = [&]() { if constexpr (WIDE) return sm.vb[slot]; else return sm.v[slot]; }();
+            const auto* ks_ = sm.k[slot];
+            const auto* vs_ = sm.v[slot];
             // ---- S^T = K . Q^T: all eight K fragments are requested before the first product ------
             f32x16 s_acc[2][QT];  // [kb][qt]
             bf16x8 kf[2][4];
-            if constexpr (KV8 && !WIDE) {
+            if constexpr (KV8) {
                 u32x4 raw[2][2];
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
@@ -531,13 +487,13 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-                for (int qt = QA; qt < QT; ++qt)
+                for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) s_acc[kb][qt][r] = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                    for (int qt = QA; qt < QT; ++qt)
+                    for (int qt = 0; qt < QT; ++qt)
                         s_acc[kb][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][ks], qf[qt][ks], s_acc[kb][qt], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -551,10 +507,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                     for (int g = 0; g < 2; ++g)
 #pragma unroll
                         for (int dt = 0; dt < 2; ++dt) {
-                            if constexpr (WIDE) {
-                                vf[kb][g][dt] = lds_read_b128(vs_ + 32 * dt * kD + k_off[2 * kb + g]);
-                                continue;
-                            } else if constexpr (KV8) {
+                            if constexpr (KV8) {
                                 const u32x2 w01 = *(const u32x2*)(vs_ + 32 * dt * kBN + v_off8[2 * kb + g]);
                                 uint32_t w0 = w01[0], w1 = w01[1];
                                 if (j0 + kBN > p.Sk) {  // last tile of the cache: codes past the end count as zero
@@ -574,11 +527,11 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                         }
             };
             // ---- mask (only tiles that cross some row's bound) ---------------------------------
-            if (j0 + kBN > kmin_blk[QA]) {
+            if (j0 + kBN > kmin_blk[0]) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int qt = QA; qt < QT; ++qt)
+                    for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
                             const int key = j0 + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
@@ -591,7 +544,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
             auto form_p = [&]() {  // P = exp2(s - m_used) in bf16; row sums by plain fp32 adds (the
                                    // packed dot instruction shares the matrix pipe and would stall MFMAs)
 #pragma unroll
-                for (int qt = QA; qt < QT; ++qt) {
+                for (int qt = 0; qt < QT; ++qt) {
                     const float mc = EXACTQ ? m_used[qt] * c : m_used[qt];
                     float l = 0.f, l2 = 0.f;
 #pragma unroll
@@ -622,10 +575,10 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
                     for (int b = 0; b < 2; ++b)
 #pragma unroll
-                        for (int e = QA; e < QT; ++e) asm volatile("" : "+v"(pf[a][b][e]));
+                        for (int e = 0; e < QT; ++e) asm volatile("" : "+v"(pf[a][b][e]));
                 bad = false;
 #pragma unroll
-                for (int qt = QA; qt < QT; ++qt) bad |= !(l_tile[qt] < kOptimisticLimit);
+                for (int qt = 0; qt < QT; ++qt) bad |= !(l_tile[qt] < kOptimisticLimit);
             }
             // V^T fragments are requested once P is formed (earlier they would not fit the register
             // file next to the scores kept for the rare exact pass); the latency passes behind the
@@ -633,7 +586,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
             read_v_frags();
             if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // exact path: this tile's max, rescale, redo
 #pragma unroll
-                for (int qt = QA; qt < QT; ++qt) {
+                for (int qt = 0; qt < QT; ++qt) {
                     float a = fmaxf(s_acc[0][qt][0], s_acc[1][qt][0]);
 #pragma unroll
                     for (int r = 1; r < 16; ++r) a = fmaxf(fmaxf(a, s_acc[0][qt][r]), s_acc[1][qt][r]);
@@ -650,7 +603,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                 form_p();
             }
 #pragma unroll
-            for (int qt = QA; qt < QT; ++qt) l_sum[qt] += l_tile[qt];
+            for (int qt = 0; qt < QT; ++qt) l_sum[qt] += l_tile[qt];
             // ---- O^T += V^T . P^T -----------------------------------------------------------------
             __builtin_amdgcn_sched_barrier(0);
             if (early) __builtin_amdgcn_s_setprio(PRIO + 1);
@@ -662,76 +615,38 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
                     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                        for (int qt = QA; qt < QT; ++qt)
+                        for (int qt = 0; qt < QT; ++qt)
                             o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kb][g][dt], pf[kb][g][qt], o_acc[dt][qt], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // The tile loop runs twice in sequence for QT = 2: tiles in which both blocks of the wavefront have visible
-    // keys, then the tiles only its later block still sees (two loops rather than a branch inside one: each keeps
-    // its own, smaller, set of live registers).  Every wavefront passes the same number of barriers.
-    int slot = 0;         // ring slot of tile t (of tile t+1 with widened tiles)
-    int buf = 0;          // widened tiles: buffer of tile t
-    auto run_tiles = [&](int t_from, int t_to, auto qa_tag) {
-        constexpr int QA = decltype(qa_tag)::value;
-        for (int t = t_from; t < t_to; ++t) {
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (WIDE) {
-                // Code tiles t+1 and t+2 are in the ring (t+3 on its way into the slot tile t left), tile t sits
-                // widened in buffer `buf`.  Per tile: one barrier; then every wavefront requests tile t+3, widens
-                // its share of tile t+1 into the other buffer and runs the products of tile t.  The barrier at the
-                // top of the next round makes the widened tile visible and frees the buffer and the code slot read.
-                if (t + 2 < t_end) asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");  // tile t+1 landed, own LDS traffic done
-                else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_sched_barrier(0);
-                if (t + 3 < t_end) load_tile(t + 3, slot == 0 ? 2 : slot - 1);  // (slot + 2) % 3: the slot of tile t
-                if (t + 1 < t_end) widen_tile(t + 1, slot, buf ^ 1);
-                if (QA == 0 || (wave_active && t * kBN < kmax_wave)) tile_body(t, buf, qa_tag);
-                buf ^= 1;
-            } else {
-                // Tile t has landed for this wavefront once at most tile t+1's loads are in flight (four; two with
-                // the 8-bit cache); after the barrier it has landed for all, and every wavefront is done with tile
-                // t-1, whose slot the load of tile t+2 reuses.
-                if (t + 1 < t_end) {
-                    if constexpr (KV8) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-                    else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-                } else {
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                }
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_sched_barrier(0);
-                if (t + 2 < t_end) load_tile(t + 2, slot == 0 ? 2 : slot - 1);  // (slot + 2) % 3
-                if (QA == 0 || (wave_active && t * kBN < kmax_wave)) tile_body(t, slot, qa_tag);
-            }
-            slot = slot == 2 ? 0 : slot + 1;
+    // Every wavefront passes the same number of barriers, with or without visible keys in a tile.
+    // Tile t has landed for this wavefront once at most tile t+1's loads are in flight (four; two with the 8-bit
+    // cache); after the barrier it has landed for all, and every wavefront is done with tile t-1, whose slot the
+    // load of tile t+2 reuses.
+    int slot = 0;  // ring slot of tile t
+    const int t_mid = wave_active ? max(t_begin, min(t_end, (kmax_wave + kBN - 1) / kBN)) : t_begin;
+    auto turn_ring = [&](int t) {
+        if (t + 1 < t_end) {
+            if constexpr (KV8) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 2 < t_end) load_tile(t + 2, slot == 0 ? 2 : slot - 1);  // (slot + 2) % 3
     };
-    if constexpr (WIDE) {
-        __builtin_amdgcn_s_barrier();  // tile t_begin landed for all (the wait above covered this wavefront's loads)
-        if (t_begin < t_end) widen_tile(t_begin, 0, 0);
-        slot = 1;
+    for (int t = t_begin; t < t_mid; ++t) {
+        __builtin_amdgcn_sched_barrier(0);
+        turn_ring(t);
+        tile_body(t, slot);
+        slot = slot == 2 ? 0 : slot + 1;
     }
-    if constexpr (QT == 2) {
-        // tiles below the earlier block's bound (none for a wavefront past the end of a ragged last query tile)
-        const int t_mid = wave_active ? max(t_begin, min(t_end, (kmax_blk[0] + kBN - 1) / kBN)) : t_begin;
-        run_tiles(t_begin, t_mid, std::integral_constant<int, 0>{});
-        run_tiles(t_mid, t_end, std::integral_constant<int, 1>{});
-    } else {
-        const int t_mid = wave_active ? max(t_begin, min(t_end, (kmax_wave + kBN - 1) / kBN)) : t_begin;
-        run_tiles(t_begin, t_mid, std::integral_constant<int, 0>{});
-        for (int t = t_mid; t < t_end; ++t) {  // tiles this wavefront sees nothing of: keep the ring turning
-            if (t + 1 < t_end) {
-                if constexpr (KV8) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-            } else {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            }
-            __builtin_amdgcn_s_barrier();
-            if (t + 2 < t_end) load_tile(t + 2, slot == 0 ? 2 : slot - 1);
-            slot = slot == 2 ? 0 : slot + 1;
-        }
+    for (int t = t_mid; t < t_end; ++t) {  // tiles this wavefront sees nothing of: keep the ring turning
+        turn_ring(t);
+        slot = slot == 2 ? 0 : slot + 1;
     }
 
     if (!wave_active) return;
@@ -750,13 +665,13 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
     store_rows<QT>(p, wi, row, h, o_acc, l_sum, m_used);
 }
 
-template <int QT, bool KV8 = false, bool EXACTQ = false>
-__global__ void __launch_bounds__(kWaves * 64, QT == 2 ? 2 : 3)
+template <bool KV8 = false, bool EXACTQ = false>
+__global__ void __launch_bounds__(kWaves * 64, 3)
 attn_fwd_bf16_d64(FwdParams p) {
-    __shared__ typename SmemOf<QT, KV8>::type sm;
+    __shared__ typename SmemOf<KV8>::type sm;
     const WorkItem wi = decode_work(p);
     if (!wi.valid) return;  // whole workgroup leaves together
-    attn_fwd_item<QT, KV8, EXACTQ>(p, wi, sm);
+    attn_fwd_item<KV8, EXACTQ>(p, wi, sm);
 }
 
 // Merge the key-split partials of one query row: out = sum_s w_s O_s / sum_s w_s l_s with

@@ -1,5 +1,5 @@
-// The 256-row throughput shape of the forward kernel over a bf16 cache (64 query rows per wavefront), on the 16x16x32
-// shape of the bf16 matrix instruction.
+// The 256-row throughput shape of the forward kernel (64 query rows per wavefront), on the 16x16x32 shape of the bf16
+// matrix instruction.
 //
 // Same decomposition, tile ring, swizzle, mask handling and optimistic softmax as the shapes in kernels_mfma.hpp (read
 // its header first); what differs is the register layout, a software-pipelined tile loop, and row sums formed on
@@ -31,6 +31,11 @@
 namespace nfd {
 namespace mfma {
 
+template <bool KV8>
+struct SmemPipeOf {
+    typedef typename std::conditional<KV8, SmemRingPipe8, SmemRingPipe>::type type;
+};
+
 // Four-register slice fb of a sixteen-register accumulator.  The accumulators of one query column are kept as one
 // sixteen-register value: the rare rescale is then a partial update of a value too large to be worth copying, and the
 // allocator leaves it where it is (as four independent values it was moved at every join of the rare and common paths).
@@ -49,9 +54,20 @@ __device__ __forceinline__ void acc_mfma(f32x16& v, const bf16x8& a, const bf16x
     acc_set<FB>(v, __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc_slice<FB>(v), 0, 0, 0));
 }
 
-template <bool EXACTQ>
-__device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkItem& wi, SmemRingPipe& sm) {
+// KV8: K and V come from the 8-bit cache.  The four wavefronts widen each tile once, together, into the bf16 ring, one tile
+// ahead of the point from which the bf16 cache's tiles are visible, so the products and everything between them are the
+// same code; what differs is the way into the ring and the V operand.  The V cache is feature-major, so V^T needs no
+// transposing read: a widened V tile has feature rows of eight 16-byte chunks, chunk 4 kb + g holding the eight keys of
+// positions (g, 0..7) of step kb, and is read with K's offsets - operand row i of a 16-feature block is then feature
+// 4 sg(i / 4) + i % 4, which the final write undoes.  The per-head scales are folded into the softmax scale (K) and the
+// final write (V).  Four frames over 32 cached ones of 336 tokens, 16 heads: 87 us, against 97 of a 256-row shape on the
+// 32x32x16 instruction, whose stages did not overlap inside a wavefront.
+template <bool EXACTQ, bool KV8>
+__device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkItem& wi, typename SmemPipeOf<KV8>::type& sm) {
+    static_assert(!(EXACTQ && KV8), "training does not run over the 8-bit cache");
     constexpr int PRIO = kMfmaPriority;
+    constexpr int SLOTS = KV8 ? 3 : kPipeSlots;
+    auto ring = [](int i) { return KV8 ? __builtin_amdgcn_readfirstlane((int)((unsigned)i % 3u)) : i & 3; };  // slot of the i-th tile of the chain
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
@@ -69,7 +85,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     const __bf16* qg = (const __bf16*)p.q + (int64_t)wi.bh * p.Sq * kD;
     const __bf16* kg = (const __bf16*)p.k + (int64_t)wi.bh * p.Scap * kD;
     const __bf16* vg = (const __bf16*)p.v + (int64_t)wi.bh * p.Scap * kD;
-    const bool fused = p.k_new != nullptr;
+    const bool fused = !KV8 && p.k_new != nullptr;
     const __bf16* kn = fused ? (const __bf16*)p.k_new + ((int64_t)wi.bh * p.Sq - p.Snew0) * kD : kg;
     const __bf16* vn = fused ? (const __bf16*)p.v_new + ((int64_t)wi.bh * p.Sq - p.Snew0) * kD : vg;
     constexpr int kMaxCopy = 4;
@@ -93,7 +109,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     }
 
     // ---- this wavefront's queries: 32-row blocks `wave` and `wave + 4` (or one block, as the later one) -------
-    const float c = p.scale_log2e;
+    const float c = KV8 ? p.scale_log2e * p.k_scale[wi.bh] : p.scale_log2e;  // scores of the codes -> scores of the values
     int b0_blk[2];                 // [qt]: first row of the block, or a row no tensor has (dead block)
     int kmin_blk[2], kmax_blk[2];  // [qt]
     bf16x8 qf[4][2];               // [cq][ks]
@@ -161,9 +177,26 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     const int ld_chunk = (lane & 7) ^ chunk_swizzle(ld_row);
     const unsigned ld_voff[2] = {(unsigned)(ld_row * kD + ld_chunk * 8) * 2u, (unsigned)((ld_row + 32) * kD + ld_chunk * 8) * 2u};
     const int ld_plain_end = min(p.Sk, p.Snew0);
-    const unsigned lds_k0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.k[0][0]) + wave * 1024;
-    const unsigned lds_v0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.v[0][0]) + wave * 1024;
+    const unsigned lds_k0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(sm.in_k()) + wave * 1024;
+    const unsigned lds_v0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(sm.in_v()) + wave * 1024;
+    // 8-bit cache: one instruction fills 16 tile rows of 64 bytes; the tensors are padded to whole tiles
+    auto fresh_lane = [&]() {  // the lane index, formed where it is used
+        int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(ln));
+        return ln;
+    };
     auto load_tile = [&](int t, int slot) {
+        if constexpr (KV8) {
+            const int ln = fresh_lane();
+            const int row = ln >> 2, chunk = 16 * ((ln & 3) ^ chunk_swizzle8(row));  // rows + 16: the same swizzle
+            const unsigned char* kt = (const unsigned char*)p.k + ((int64_t)wi.bh * p.Spad + (int64_t)t * kBN + 16 * wave) * kD;
+            const unsigned char* vt = (const unsigned char*)p.v + ((int64_t)wi.bh * kD + 16 * wave) * p.Spad + (int64_t)t * kBN;
+            const unsigned kdst = lds_k0 + (unsigned)(slot * kTileElems);
+            const unsigned vdst = lds_v0 + (unsigned)(slot * kTileElems);
+            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"((unsigned)(row * kD + chunk)), "s"(kt), "s"(kdst) : "memory", "m0");
+            asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(vt + ((uint64_t)(unsigned)row * (unsigned)p.Spad + (unsigned)chunk)), "s"(vdst) : "memory", "m0");
+            return;
+        }
         if ((t + 1) * kBN <= ld_plain_end) {
             const __bf16* kt = kg + (int64_t)t * kTileElems;
             const __bf16* vt = vg + (int64_t)t * kTileElems;
@@ -205,7 +238,52 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     if (t_begin < t_end) load_tile(t_begin, 0);
     if (t_begin + 1 < t_end) load_tile(t_begin + 1, 1);
     if (t_begin + 2 < t_end) load_tile(t_begin + 2, 2);
+    // 8-bit cache: the lane widens the 16 codes of chunk cv_c of tile row cv_row of both tensors - of a row its own wavefront
+    // loaded, so its own wait suffices.  The lane order keeps the 16-byte loads and stores free of bank conflicts.  V: the
+    // cache holds, in the two 8-byte halves x of a 16-key chunk, keys 4hh .. + 3 and 8 + 4hh .. + 3, hh = x ^ (bit 4 of the
+    // feature): quads hh and 2 + hh, which are the first (second, for odd chunks) four positions of lane groups
+    // (0, 1) for hh = 0 and (3, 2) for hh = 1.  The lane's addresses are formed anew for every tile: kept through the loop
+    // they do not find registers, and a reload from scratch waits for the tile loads in flight before it (104 against
+    // 87 us at four speculative frames over 32).
+    auto widen_tile = [&](int t, int slot) {  // the code slot and the bf16 slot of a tile have the same number
+        if constexpr (KV8) {
+            const int ln = fresh_lane();
+            const int cv_row = 16 * wave + 2 * (ln & 7) + ((ln >> 3) & 1), cv_c = ln >> 4;
+            const int cv_src = cv_row * 64 + 16 * (cv_c ^ chunk_swizzle8(cv_row));
+            const int cv_f = chunk_swizzle(cv_row), cv_s = wave & 1;
+            const int cv_k0 = cv_row * kD + 8 * ((2 * cv_c) ^ cv_f);
+            const int cv_v0 = cv_row * kD + 8 * ((4 * (cv_c >> 1)) ^ cv_f) + 4 * (cv_c & 1);
+            const u32x4 rk = *(const u32x4*)(sm.k8[slot] + cv_src);
+            u32x4 rv = *(const u32x4*)(sm.v8[slot] + cv_src);
+            const int j0 = t * kBN;
+            if (j0 + kBN > p.Sk) {  // last tile of the cache: V codes at or past the end count as zero
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    const int left = p.Sk - (j0 + 16 * cv_c + 4 * (x ^ cv_s));
+                    rv[2 * x] = left >= 4 ? rv[2 * x] : left <= 0 ? 0u : rv[2 * x] & ((1u << (8 * left)) - 1u);
+                    rv[2 * x + 1] = left >= 12 ? rv[2 * x + 1] : left <= 8 ? 0u : rv[2 * x + 1] & ((1u << (8 * (left - 8))) - 1u);
+                }
+            }
+            *(bf16x8*)(sm.k[slot] + cv_k0) = widen_e4m3x8(rk[0], rk[1]);
+            *(bf16x8*)(sm.k[slot] + (cv_k0 ^ 8)) = widen_e4m3x8(rk[2], rk[3]);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const bf16x8 w = widen_e4m3x8(rv[2 * x], rv[2 * x + 1]);
+                const int odd = x ^ cv_s;  // hh: chunk positions 0 and 1, or 3 and 2, of the four of this step
+                *(bf16x4*)(sm.v[slot] + (cv_v0 ^ (odd * 24))) = __builtin_shufflevector(w, w, 0, 1, 2, 3);
+                *(bf16x4*)(sm.v[slot] + (cv_v0 ^ (odd * 24) ^ 8)) = __builtin_shufflevector(w, w, 4, 5, 6, 7);
+            }
+        }
+    };
+
     wait_vmem_all();
+    if constexpr (KV8) {
+        if (t_begin < t_end) widen_tile(t_begin, 0);
+        if (t_begin + 1 < t_end) widen_tile(t_begin + 1, 1);
+        if (t_begin + 3 < t_end) load_tile(t_begin + 3, 0);
+        if (t_begin + 4 < t_end) load_tile(t_begin + 4, 1);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // visible to all after the barrier in front of the tile loops
+    }
     if (fused) {
 #pragma unroll
         for (int i = 0; i < kMaxCopy; ++i)
@@ -220,6 +298,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         else return s - ref_exponent;
     };
     auto read_v_frag = [&](const __bf16* tile, int kb, int fb) {  // V^T fragment of the 32-key step kb, features 16 fb ..
+        if constexpr (KV8) return lds_read_b128(tile + 16 * fb * kD + k_off[kb]);
         const __bf16* vp = tile + 32 * kb * kD + v_off[fb];
         const s16x4 lo = lds_read_tr(vp);
         const s16x4 hi = lds_read_tr(vp + 16 * kD);
@@ -375,12 +454,32 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     const int t_mid = wave_active ? max(t_begin, min(t_end, (kmax_blk[0] + kBN - 1) / kBN)) : t_begin;
     int t_pipe = wave_active ? max(t_begin, min(t_mid, kmin_blk[0] / kBN)) : t_begin;
     if (t_pipe - t_begin < 2) t_pipe = t_begin;
-    auto bar = [&](int t, auto load_slot) {  // load_slot: the ring slot of tile t + 3 (an int or a compile-time constant)
-        if (t + 2 < t_end) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 3 < t_end) load_tile(t + 3, (int)load_slot);
+    // 8-bit cache: the bf16 ring has three slots, filled by widening.  After Bar(t) a wavefront widens its rows of tile t+2
+    // into the slot of tile t-1 (Bar(t+1) makes them visible) and requests the codes of tile t+5 into the slot it read.
+    auto bar = [&](int t, auto load_slot) {  // load_slot: the ring slot of tile t - 1 (an int or a compile-time constant)
+        if constexpr (KV8) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wavefront's share of tile t+1 is written
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            if (t + 2 < t_end) {
+                // codes of tile t+2 landed; those of t+3, t+4 (two loads each) may be in flight
+                if (t + 4 < t_end) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+                else if (t + 3 < t_end) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                widen_tile(t + 2, (int)load_slot);
+                // the codes read have left LDS before their slot is filled again
+                if (t + 5 < t_end) {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    load_tile(t + 5, (int)load_slot);
+                }
+            }
+        } else {
+            if (t + 2 < t_end) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            if (t + 3 < t_end) load_tile(t + 3, (int)load_slot);
+        }
         // Key-split launches: the wave priority falls with the quarter of the chain the workgroup is in, so that of
         // two workgroups sharing a CU the one that lags is served first and both finish together (the arbiter
         // otherwise prefers the older one throughout: 52 against 70 us at four speculative frames).  Training
@@ -524,9 +623,9 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             }
         };
 
-        // The four steps of one key tile in ring slot `slot`.  The main loop below runs four tiles per round with the
+        // The four steps of one key tile in ring slot `slot`.  The main loop below runs a ring of tiles per round with the
         // slots as compile-time constants: every LDS address is then a per-lane offset fixed before the loop plus an
-        // immediate, and the round spends no vector instruction on addresses.  Up to three tiles remain for the
+        // immediate, and the round spends no vector instruction on addresses.  The remaining tiles (fewer than a ring) go through the
         // second loop, which computes its slots.
         auto tile_steps = [&](int t, auto slot, auto slot_next, auto slot_load, bool first) __attribute__((always_inline)) {
             float lu[2];
@@ -571,15 +670,21 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         typedef std::integral_constant<int, 2> I2;
         typedef std::integral_constant<int, 3> I3;
         int t = t_begin;
-        for (; t + 4 <= t_pipe; t += 4) {
-            tile_steps(t, I0{}, I1{}, I3{}, t == t_begin);
-            tile_steps(t + 1, I1{}, I2{}, I0{}, false);
-            tile_steps(t + 2, I2{}, I3{}, I1{}, false);
-            tile_steps(t + 3, I3{}, I0{}, I2{}, false);
+        for (; t + SLOTS <= t_pipe; t += SLOTS) {
+            if constexpr (KV8) {
+                tile_steps(t, I0{}, I1{}, I2{}, t == t_begin);
+                tile_steps(t + 1, I1{}, I2{}, I0{}, false);
+                tile_steps(t + 2, I2{}, I0{}, I1{}, false);
+            } else {
+                tile_steps(t, I0{}, I1{}, I3{}, t == t_begin);
+                tile_steps(t + 1, I1{}, I2{}, I0{}, false);
+                tile_steps(t + 2, I2{}, I3{}, I1{}, false);
+                tile_steps(t + 3, I3{}, I0{}, I2{}, false);
+            }
         }
         for (; t < t_pipe; ++t) {
-            const int slot = (t - t_begin) & 3;
-            tile_steps(t, slot, (slot + 1) & 3, (slot + 3) & 3, t == t_begin);
+            const int slot = ring(t - t_begin);
+            tile_steps(t, slot, ring(slot + 1), ring(slot + SLOTS - 1), t == t_begin);
         }
         __builtin_amdgcn_sched_barrier(0);
         pv(1, 1);  // drain: PV of the last unit
@@ -592,16 +697,25 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         constexpr int QA = decltype(qa_tag)::value;
         for (int t = t_from; t < t_to; ++t) {
             __builtin_amdgcn_sched_barrier(0);
-            bar(t, (t + 3 - t_begin) & 3);
-            if (QA == 0) tile_body(t, (t - t_begin) & 3, std::integral_constant<int, 0>{});
-            if (QA == 0 || (wave_active && t * kBN < kmax_wave)) tile_body(t, (t - t_begin) & 3, std::integral_constant<int, 1>{});
+            const int slot = ring(t - t_begin);
+            bar(t, ring(slot + SLOTS - 1));
+            if (QA == 0) tile_body(t, slot, std::integral_constant<int, 0>{});
+            if (QA == 0 || (wave_active && t * kBN < kmax_wave)) tile_body(t, slot, std::integral_constant<int, 1>{});
         }
     };
     run_rest(t_pipe, t_mid, std::integral_constant<int, 0>{});
     run_rest(t_mid, t_end, std::integral_constant<int, 1>{});
 
-    // ---- final write: lane (j, g) holds, for query column cq, features 16 fb + 4 g + 0..3 -----------------------
+    // ---- final write: lane (j, g) holds, for query column cq, features 16 fb + 4 g + 0..3 (4 sg(g) with KV8) --------
     if (!wave_active) return;
+    if constexpr (KV8) {  // values of V = codes * scale: linear, so applied once to the accumulator
+        const float vs = p.v_scale[wi.bh];
+#pragma unroll
+        for (int cq = 0; cq < 4; ++cq)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o_acc[cq][r] *= vs;
+    }
+    const int f0 = 4 * (KV8 ? sg(g) : g);
 #pragma unroll
     for (int cq = 0; cq < 4; ++cq) {
         float l_row;
@@ -620,7 +734,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
 #pragma unroll
             for (int fb = 0; fb < 4; ++fb) {
                 const f32x4 x = {o_acc[cq][4 * fb] * inv, o_acc[cq][4 * fb + 1] * inv, o_acc[cq][4 * fb + 2] * inv, o_acc[cq][4 * fb + 3] * inv};
-                *(bf16x4*)(og + 16 * fb + 4 * g) = __builtin_convertvector(x, bf16x4);
+                *(bf16x4*)(og + 16 * fb + f0) = __builtin_convertvector(x, bf16x4);
             }
             if (p.lse && g == 0) p.lse[(int64_t)wi.bh * p.Sq + row] = (m_exp + __builtin_log2f(l_row)) * kLn2;
         } else {
@@ -629,7 +743,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
 #pragma unroll
             for (int fb = 0; fb < 4; ++fb) {
                 const f32x4 x = {o_acc[cq][4 * fb], o_acc[cq][4 * fb + 1], o_acc[cq][4 * fb + 2], o_acc[cq][4 * fb + 3]};
-                *(bf16x4*)(po + 16 * fb + 4 * g) = __builtin_convertvector(x, bf16x4);
+                *(bf16x4*)(po + 16 * fb + f0) = __builtin_convertvector(x, bf16x4);
             }
             if (g == 0) {
                 const f32x2 ml = {m_exp, l_row};
@@ -639,13 +753,13 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     }
 }
 
-template <bool EXACTQ>
+template <bool EXACTQ, bool KV8 = false>
 __global__ void __launch_bounds__(kWaves * 64, 2)
 attn_fwd_bf16_d64_m16(FwdParams p) {
-    __shared__ SmemRingPipe sm;
+    __shared__ typename SmemPipeOf<KV8>::type sm;
     const WorkItem wi = decode_work(p);
     if (!wi.valid) return;
-    attn_fwd_item16<EXACTQ>(p, wi, sm);
+    attn_fwd_item16<EXACTQ, KV8>(p, wi, sm);
 }
 
 }  // namespace mfma

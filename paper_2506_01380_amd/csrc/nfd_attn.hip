@@ -397,17 +397,17 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
     if (pl.kernel == 1) {
         const dim3 grid(pl.n_workgroups), block(nfd::mfma::kWaves * 64);
         if (kv8 && pl.block_m == nfd::mfma::kBM)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<2, true>), grid, block, 0, st, p);
+            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64_m16<false, true>), grid, block, 0, st, p);
         else if (kv8)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<1, true>), grid, block, 0, st, p);
+            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<true>), grid, block, 0, st, p);
         else if (lse && pl.block_m == nfd::mfma::kBM)  // training pair: scores from the queries as given
             hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64_m16<true>), grid, block, 0, st, p);
         else if (lse)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<1, false, true>), grid, block, 0, st, p);
+            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<false, true>), grid, block, 0, st, p);
         else if (pl.block_m == nfd::mfma::kBM)
             hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64_m16<false>), grid, block, 0, st, p);
         else
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<1, false>), grid, block, 0, st, p);
+            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<false>), grid, block, 0, st, p);
         if (pl.n_splits > 1) {
             const int64_t total = (int64_t)p.BH * p.Sq * (nfd::mfma::kD / 4);
             hipLaunchKernelGGL(nfd::mfma::attn_combine_d64, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);
