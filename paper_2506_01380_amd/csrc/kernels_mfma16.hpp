@@ -62,7 +62,11 @@ __device__ __forceinline__ void acc_mfma(f32x16& v, const bf16x8& a, const bf16x
 // 4 sg(i / 4) + i % 4, which the final write undoes.  The per-head scales are folded into the softmax scale (K) and the
 // final write (V).  Four frames over 32 cached ones of 336 tokens, 16 heads: 87 us, against 97 of a 256-row shape on the
 // 32x32x16 instruction, whose stages did not overlap inside a wavefront.
-template <bool EXACTQ, bool KV8>
+//
+// NCQ: 16-query column blocks per wavefront.  4: 64 rows, the 32-row blocks `wave` and `wave + 4` of the workgroup's eight.
+// 3: 48 rows, the 32-row block `wave` and the 16-row block `wave` behind the first 128 rows: a workgroup of 192, for tiles of
+// six 32-row blocks (the rule and its figures are at the launch).  222 VGPRs, no spills.
+template <bool EXACTQ, bool KV8, int NCQ>
 __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkItem& wi, typename SmemPipeOf<KV8>::type& sm) {
     static_assert(!(EXACTQ && KV8), "training does not run over the 8-bit cache");
     constexpr int PRIO = kMfmaPriority;
@@ -112,21 +116,34 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     const float c = KV8 ? p.scale_log2e * p.k_scale[wi.bh] : p.scale_log2e;  // scores of the codes -> scores of the values
     int b0_blk[2];                 // [qt]: first row of the block, or a row no tensor has (dead block)
     int kmin_blk[2], kmax_blk[2];  // [qt]
-    bf16x8 qf[4][2];               // [cq][ks]
+    bf16x8 qf[NCQ][2];             // [cq][ks]
     // row of this lane's query column cq and its key bound: recomputed where needed (masked tiles, the final write)
     // rather than kept in registers through the loops
+    // column blocks of the wavefront's row block qt
+    auto has = [](int qt, int cb) { return 2 * qt + cb < NCQ; };
     auto row_of = [&](int cq) { return b0_blk[cq >> 1] + 16 * (cq & 1) + j; };
     auto kmax_lane_of = [&](int cq) { return kmax_of_row(min(row_of(cq), p.Sq - 1), p.T, p.P); };
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-        const bool pair = wave + kWaves < n_blk;
-        const bool dead = qt == 0 && !pair;
-        const int b0 = r0 + 32 * (qt == 1 && pair ? wave + kWaves : wave);
-        b0_blk[qt] = dead ? 0x40000000 : b0;
-        kmin_blk[qt] = dead ? 0 : kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
-        kmax_blk[qt] = dead ? 0 : kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);
+        if constexpr (NCQ == 4) {
+            const bool pair = wave + kWaves < n_blk;
+            const bool dead = qt == 0 && !pair;
+            const int b0 = r0 + 32 * (qt == 1 && pair ? wave + kWaves : wave);
+            b0_blk[qt] = dead ? 0x40000000 : b0;
+            kmin_blk[qt] = dead ? 0 : kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
+            kmax_blk[qt] = dead ? 0 : kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);
+        } else {
+            // a workgroup without this wavefront's second block: a duplicate of the last row, never stored, that runs
+            // along with the first block (same bounds; the wavefront would wait at the barriers instead)
+            const bool none = qt == 1 && 4 * 32 + 16 * wave >= 32 * n_blk;
+            const int b0 = r0 + (qt == 0 ? 32 * wave : 4 * 32 + 16 * wave);
+            b0_blk[qt] = none ? 0x40000000 : b0;
+            kmin_blk[qt] = none ? kmin_blk[0] : kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
+            kmax_blk[qt] = none ? kmax_blk[0] : kmax_of_row(min(b0 + (qt == 0 ? 31 : 15), p.Sq - 1), p.T, p.P);
+        }
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
+            if (!has(qt, cb)) continue;
             const int cq = 2 * qt + cb;
             const int rc = min(row_of(cq), p.Sq - 1);
 #pragma unroll
@@ -144,9 +161,9 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     const int kmax_wave = kmax_blk[1];
     const bool wave_active = wave < n_blk;
 
-    f32x16 o_acc[4];  // [cq], element 4 fb + e: feature 16 fb + 4 g + e
+    f32x16 o_acc[NCQ];  // [cq], element 4 fb + e: feature 16 fb + 4 g + e
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NCQ; ++a)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o_acc[a][r] = 0.f;
     // Row sums.  MSUM (the plain forward): the second product also multiplies P^T by a block of ones, so the sum of a
@@ -159,13 +176,13 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     // values on the vector unit and the test on them.
     constexpr bool MSUM = !EXACTQ;
     constexpr float kRefBias = MSUM ? 8.f : 0.f;
-    float m_used[4], l_sum[4];  // [cq]; m_used in accumulator units (raw scores with EXACTQ)
+    float m_used[NCQ], l_sum[NCQ];  // [cq]; m_used in accumulator units (raw scores with EXACTQ)
     bf16x8 ones;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
     asm volatile("" : "+v"(ones));  // keep it in registers: rebuilt from constants it costs two moves per step
 #pragma unroll
-    for (int cq = 0; cq < 4; ++cq) { m_used[cq] = kNegBig; l_sum[cq] = 0.f; }
+    for (int cq = 0; cq < NCQ; ++cq) { m_used[cq] = kNegBig; l_sum[cq] = 0.f; }
     // some value of the two packed operands is >= 2 (or not a number): bit 14 of a bf16 is the top exponent bit
     auto any_big = [](const bf16x8& a, const bf16x8& b) {
         const u32x4 x = __builtin_bit_cast(u32x4, a), y = __builtin_bit_cast(u32x4, b);
@@ -320,7 +337,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     // of the wavefront per call: these tiles are few, and half the scores at a time keep the register peak of this
     // path below that of the pipelined loop (a value that finds no register here is reloaded at every use, there too)
     auto tile_body = [&](int t, int slot, auto qt_tag) {
-        constexpr int C0 = 2 * decltype(qt_tag)::value, C1 = C0 + 2;  // this block's query columns
+        constexpr int C0 = 2 * decltype(qt_tag)::value, C1 = C0 + 2 < NCQ ? C0 + 2 : NCQ;  // this block's query columns
         const int j0 = t * kBN;
         const __bf16* ks_ = sm.k[slot];
         const __bf16* vs_ = sm.v[slot];
@@ -497,12 +514,12 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
 
     if (t_pipe > t_begin) {
         f32x4 S[2][2][2];      // [qt][rb'][cb]: the unit in flight of each 32-row block
-        f32x4 minit[4];        // [cq]: minus the reference, the C operand of the first product
+        f32x4 minit[NCQ];      // [cq]: minus the reference, the C operand of the first product
         bf16x8 P[2][2];        // [qt][cb]
         bf16x8 kf[2][2][2];    // [kb][rb'][ks]
         bf16x8 vf[2][4];       // [kb][fb]
 #pragma unroll
-        for (int cq = 0; cq < 4; ++cq)
+        for (int cq = 0; cq < NCQ; ++cq)
 #pragma unroll
             for (int e = 0; e < 4; ++e) minit[cq][e] = 0.f;
 #pragma unroll
@@ -532,22 +549,23 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb)
-                    S[qt][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][rb][0], qf[2 * qt + cb][0], minit[2 * qt + cb], 0, 0, 0);
+                    if (has(qt, cb)) S[qt][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][rb][0], qf[2 * qt + cb][0], minit[2 * qt + cb], 0, 0, 0);
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb)
-                    S[qt][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][rb][1], qf[2 * qt + cb][1], S[qt][rb][cb], 0, 0, 0);
+                    if (has(qt, cb)) S[qt][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][rb][1], qf[2 * qt + cb][1], S[qt][rb][cb], 0, 0, 0);
         };
         auto pv = [&](int kb, int qt) {
             if constexpr (MSUM) {  // the unit's column sums first: their adds then find room later in the same step
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb)
-                    l_sum[2 * qt + cb] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[qt][cb], zero, 0, 0, 0)[0];
+                    if (has(qt, cb)) l_sum[2 * qt + cb] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[qt][cb], zero, 0, 0, 0)[0];
             }
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
+                if (!has(qt, cb)) continue;
                 acc_mfma<0>(o_acc[2 * qt + cb], vf[kb][0], P[qt][cb]);
                 acc_mfma<1>(o_acc[2 * qt + cb], vf[kb][1], P[qt][cb]);
                 acc_mfma<2>(o_acc[2 * qt + cb], vf[kb][2], P[qt][cb]);
@@ -558,6 +576,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         auto sm_unit = [&](int qt, const float (&sub)[2], float (&lu)[2], bool subtract) {
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
+                if (!has(qt, cb)) { lu[cb] = 0.f; continue; }
                 float l = 0.f, l2 = 0.f;
 #pragma unroll
                 for (int rb = 0; rb < 2; ++rb)
@@ -581,11 +600,12 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         // After SM(u): if the unit's test fails (or the unit is a block's first), take the unit's exact max, move the
         // reference, rescale the block's accumulators and form P again.  S[qt] is still intact.
         auto settle = [&](int qt, float (&lu)[2], bool fresh) {
-            const bool bad = fresh || (MSUM ? any_big(P[qt][0], P[qt][1]) : !(lu[0] < kOptimisticLimit) || !(lu[1] < kOptimisticLimit));
+            const bool bad = fresh || (MSUM ? any_big(P[qt][0], P[qt][has(qt, 1) ? 1 : 0]) : !(lu[0] < kOptimisticLimit) || !(lu[1] < kOptimisticLimit));
             if (__builtin_amdgcn_ballot_w64(bad) != 0) {
                 float up[2];
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
+                    if (!has(qt, cb)) continue;
                     const int cq = 2 * qt + cb;
                     float a = S[qt][0][cb][0];
 #pragma unroll
@@ -605,7 +625,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             }
             if constexpr (!MSUM) {
                 l_sum[2 * qt] += lu[0];
-                l_sum[2 * qt + 1] += lu[1];
+                if (has(qt, 1)) l_sum[2 * qt + 1] += lu[1];
             }
         };
         // PV of unit (kp, qp), then QK of unit (kq, qq): order, interleave ratio and wave priorities were swept on the
@@ -615,13 +635,16 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             qk(kq, qq);
         };
         // one MFMA : two vector instructions, for every MFMA of the step (ratios 1 to 4 measured: 2 is best by 1 %)
-        auto interleave = [&]() {
+        auto interleave = [&](auto mfma_qt) {  // mfma_qt: the row block whose products the step issues
+            constexpr int NB = NCQ == 3 && decltype(mfma_qt)::value == 1 ? 1 : 2;
 #pragma unroll
-            for (int i = 0; i < (MSUM ? 18 : 16); ++i) {
+            for (int i = 0; i < NB * (MSUM ? 9 : 8); ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x402, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x402, NCQ == 4 ? 2 : NB == 1 ? 4 : 1, 0);
             }
         };
+        const std::integral_constant<int, 0> blk0_tag{};
+        const std::integral_constant<int, 1> blk1_tag{};
 
         // The four steps of one key tile in ring slot `slot`.  The main loop below runs a ring of tiles per round with the
         // slots as compile-time constants: every LDS address is then a per-lane offset fixed before the loop plus an
@@ -633,7 +656,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             __builtin_amdgcn_sched_barrier(0);
             qk_pv(0, 1, 1, 1);
             sm_unit(0, no_sub, lu, false);
-            interleave();
+            interleave(blk1_tag);
             __builtin_amdgcn_sched_barrier(0);
             settle(0, lu, first);
             bar(t, slot_load);
@@ -643,14 +666,14 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             read_v((int)slot, 0);
             qk_pv(1, 0, 0, 0);
             sm_unit(1, no_sub, lu, false);
-            interleave();
+            interleave(blk0_tag);
             __builtin_amdgcn_sched_barrier(0);
             settle(1, lu, first);
             // step (1,0): QK(1,1), PV(0,1), SM(1,0)
             __builtin_amdgcn_sched_barrier(0);
             qk_pv(1, 1, 0, 1);
             sm_unit(0, no_sub, lu, false);
-            interleave();
+            interleave(blk1_tag);
             __builtin_amdgcn_sched_barrier(0);
             settle(0, lu, false);
             // step (1,1): PV(1,0), QK(0,0) of the next tile (a discarded product after the last tile), SM(1,1)
@@ -659,7 +682,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             read_v((int)slot, 1);
             qk_pv(0, 0, 1, 0);
             sm_unit(1, no_sub, lu, false);
-            interleave();
+            interleave(blk0_tag);
             __builtin_amdgcn_sched_barrier(0);
             settle(1, lu, false);
         };
@@ -690,7 +713,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         pv(1, 1);  // drain: PV of the last unit
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int cq = 0; cq < 4; ++cq) m_used[cq] = -minit[cq][0];
+        for (int cq = 0; cq < NCQ; ++cq) m_used[cq] = -minit[cq][0];
     }
     // tiles at the frame bounds (mask) and tiles only the later block sees: one tile at a time
     auto run_rest = [&](int t_from, int t_to, auto qa_tag) {
@@ -711,13 +734,13 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     if constexpr (KV8) {  // values of V = codes * scale: linear, so applied once to the accumulator
         const float vs = p.v_scale[wi.bh];
 #pragma unroll
-        for (int cq = 0; cq < 4; ++cq)
+        for (int cq = 0; cq < NCQ; ++cq)
 #pragma unroll
             for (int r = 0; r < 16; ++r) o_acc[cq][r] *= vs;
     }
     const int f0 = 4 * (KV8 ? sg(g) : g);
 #pragma unroll
-    for (int cq = 0; cq < 4; ++cq) {
+    for (int cq = 0; cq < NCQ; ++cq) {
         float l_row;
         if constexpr (MSUM) {
             l_row = l_sum[cq];  // every lane group holds the whole column's sum
@@ -753,13 +776,13 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     }
 }
 
-template <bool EXACTQ, bool KV8 = false>
+template <bool EXACTQ, bool KV8 = false, int NCQ = 4>
 __global__ void __launch_bounds__(kWaves * 64, 2)
 attn_fwd_bf16_d64_m16(FwdParams p) {
     __shared__ typename SmemPipeOf<KV8>::type sm;
     const WorkItem wi = decode_work(p);
     if (!wi.valid) return;
-    attn_fwd_item16<EXACTQ, KV8>(p, wi, sm);
+    attn_fwd_item16<EXACTQ, KV8, NCQ>(p, wi, sm);
 }
 
 }  // namespace mfma

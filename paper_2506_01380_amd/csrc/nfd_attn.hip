@@ -396,18 +396,32 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
 
     if (pl.kernel == 1) {
         const dim3 grid(pl.n_workgroups), block(nfd::mfma::kWaves * 64);
-        if (kv8 && pl.block_m == nfd::mfma::kBM)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64_m16<false, true>), grid, block, 0, st, p);
-        else if (kv8)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<true>), grid, block, 0, st, p);
-        else if (lse && pl.block_m == nfd::mfma::kBM)  // training pair: scores from the queries as given
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64_m16<true>), grid, block, 0, st, p);
-        else if (lse)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<false, true>), grid, block, 0, st, p);
-        else if (pl.block_m == nfd::mfma::kBM)
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64_m16<false>), grid, block, 0, st, p);
-        else
-            hipLaunchKernelGGL((nfd::mfma::attn_fwd_bf16_d64<false>), grid, block, 0, st, p);
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, p); };
+        using namespace nfd::mfma;
+        // Which kernel runs a 256-row tile depends on the 32-row blocks the largest one holds.  Measured: 8 sequences of 16
+        // heads, one frame over 40 cached ones (forward / with log-sum-exp / 8-bit cache, us).
+        //   six   48 rows per wavefront, all wavefronts with the same work: 59.9 / 62.3 / 59.3, against 65.4 / 69.0 / 70.5 with
+        //         two wavefronts of 64 rows and two of 32 (which lack the pipelined loop) at the same barriers; one frame of 576
+        //         tokens over 64: 750 -> 685.  At five blocks 48 rows take 49.6 against 48.5, and splitting 42 blocks into
+        //         seven tiles of six instead of six of seven 75.6 against 76.5 (90.1 against 85.9 over the 8-bit cache).
+        //   1..4  one block per wavefront: the 128-row kernel, three workgroups per CU: with log-sum-exp 13.0 against 14.8 us
+        //         (one block), 34.1 against 35.1 (four); over the 8-bit cache 34.8 against 40.9 (48 rows).  Not for
+        //         the plain forward, whose row sums are of the rounded weights that the output is formed from: the 128-row
+        //         kernel's are not, and its error is up to 0.2 % larger.
+        const int tile_blocks = p.blocks_lo + (p.n_hi > 0);
+        if (pl.block_m == kBM / 2 || (tile_blocks <= 4 && (kv8 || lse))) {
+            if (kv8) go(attn_fwd_bf16_d64<true>);
+            else if (lse) go(attn_fwd_bf16_d64<false, true>);  // training pair: scores from the queries as given
+            else go(attn_fwd_bf16_d64<false>);
+        } else if (tile_blocks != kBM48 / 32) {
+            if (kv8) go(attn_fwd_bf16_d64_m16<false, true>);
+            else if (lse) go(attn_fwd_bf16_d64_m16<true>);
+            else go(attn_fwd_bf16_d64_m16<false>);
+        } else {
+            if (kv8) go(attn_fwd_bf16_d64_m16<false, true, 3>);
+            else if (lse) go(attn_fwd_bf16_d64_m16<true, false, 3>);
+            else go(attn_fwd_bf16_d64_m16<false, false, 3>);
+        }
         if (pl.n_splits > 1) {
             const int64_t total = (int64_t)p.BH * p.Sq * (nfd::mfma::kD / 4);
             hipLaunchKernelGGL(nfd::mfma::attn_combine_d64, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);

@@ -356,7 +356,7 @@ def test_fused_rotary_and_quantising_append(attn, B, H, grid, F, pos, n):
 
 
 @pytest.mark.parametrize("B,H,T,kvf,qf,F", [
-    # 256-row workgroups (64 heads or more): chains of one key tile to more than two turns of the three-slot ring, ends of
+    # 64 heads or more: wavefronts of 48 and of 64 rows; chains of one key tile to more than two turns of the three-slot ring, ends of
     # the cache inside a tile, wavefronts with one block and with two, key splits and none
     (1, 64, 40, 1, 1, 1),       # one tile, 40 keys: nothing to widen ahead
     (1, 64, 64, 2, 1, 3),       # two whole tiles
@@ -364,10 +364,13 @@ def test_fused_rotary_and_quantising_append(attn, B, H, grid, F, pos, n):
     (1, 64, 250, 1, 1, 1),      # eight blocks: four tiles, wavefronts with two blocks each, 58 keys in the last
     (2, 256, 32, 15, 1, 16),    # no splits: eight tiles
     (1, 512, 160, 4, 4, 4),     # no splits, frame bounds inside workgroups: both tile loops after the pipelined one
-    (1, 64, 161, 7, 1, 7),      # odd frame, splits
+    (1, 64, 161, 7, 1, 7),      # six blocks, splits
+    (2, 256, 48, 5, 4, 5),      # six blocks, no splits, frame bounds inside both row blocks of a wavefront
+    (1, 64, 150, 12, 1, 12),    # five blocks
+    (1, 64, 224, 9, 1, 10),     # seven
     (1, 16, 336, 9, 4, 10),     # seven blocks a workgroup
 ])
-def test_attention_256_row_chains(attn, B, H, T, kvf, qf, F):
+def test_attention_chains(attn, B, H, T, kvf, qf, F):
     assert nb.nfd_attn_plan(nb.NFD_BF16, B, H, F, T, 64, kvf, qf)["block_m"] == 256
     got, ref = _run(attn, B, H, T, kvf, qf, F, seed=wl.BASE_SEED + 90 + T)
     _check(got, ref, (B, H, T, kvf, qf))
