@@ -31,21 +31,58 @@ constexpr int kMaxD = 256;
 
 template <typename T> __device__ __forceinline__ T from_f32(float x) { return (T)x; }  // RNE for bf16
 
+// N consecutive features of a row, as stored where they are loaded as one vector.
 template <typename T, bool VEC, int N>
-__device__ __forceinline__ void load_features(const T* row, int f, int D, float (&x)[N]) {
-    if constexpr (VEC) {
-        typedef __attribute__((ext_vector_type(N))) T vec_t;
-        const vec_t v = *(const vec_t*)(row + f);
+struct Group {
+    typedef __attribute__((ext_vector_type(N))) typename std::conditional<VEC, T, float>::type type;
+    static __device__ __forceinline__ type load(const T* row, int f, int D) {
+        if constexpr (VEC) {
+            return *(const type*)(row + f);
+        } else {
+            type x;
 #pragma unroll
-        for (int e = 0; e < N; ++e) x[e] = (float)v[e];
-    } else {
-#pragma unroll
-        for (int e = 0; e < N; ++e) x[e] = f + e < D ? (float)row[f + e] : 0.f;
+            for (int e = 0; e < N; ++e) x[e] = f + e < D ? (float)row[f + e] : 0.f;
+            return x;
+        }
     }
+};
+
+// Widened here and not where the value is used.
+__device__ __forceinline__ float widen(float x) { return x; }
+__device__ __forceinline__ float widen(__bf16 x) {
+    float y = (float)x;
+    asm volatile("" : "+v"(y));
+    return y;
 }
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, const f32x4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Where a product does not write the registers it adds to, the compiler takes those as free at once and keeps no distance to
+// a vector instruction that writes them (for the bf16 products it does).  Measured: the distance is needed - with the
+// softmax of one column block scheduled into the products of the next, whose accumulators had moved, rows of that block
+// came out wrong by percents, differently from run to run.  So no vector instruction is scheduled into a group of products
+// (loads are), and the last of them is left to read its operands.
+extern "C" __device__ void s_nop(short) __asm("llvm.amdgcn.s.nop");  // (inline assembly is not held by the fences)
+__device__ __forceinline__ void begin_products() { __builtin_amdgcn_sched_barrier(0x20); }
+__device__ __forceinline__ void pin(f32x4& x) { asm volatile("" : "+v"(x)); }
+template <typename X, int N>
+__device__ __forceinline__ void pin(X (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) pin(x[i]);
+}
+template <typename... X>
+__device__ __forceinline__ void end_products(X&... x) {  // x: all that the group adds to
+    (pin(x), ...);
+    __builtin_amdgcn_sched_barrier(0x20);
+    s_nop(7);
+    __builtin_amdgcn_sched_barrier(0x20);
+}
+template <int N>
+__device__ __forceinline__ void zero(f32x4 (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 template <int DP>
@@ -55,27 +92,43 @@ struct Shape {
     static constexpr int NC = DP / (16 * NF);
 };
 
-// 16 rows as an operand of the first pattern: lane (i, g) holds row i, features 16 m + 4 g + e.
+// 16 rows as an operand of the first pattern: lane (i, g) holds row i, features 16 m + 4 g + e, as loaded and widened.
+template <typename T, int DP, bool VEC>
+struct RowRaw {
+    typename Group<T, VEC, 4>::type x[Shape<DP>::M];
+    __device__ __forceinline__ void load(const T* row, int g, int D) {
+#pragma unroll
+        for (int m = 0; m < Shape<DP>::M; ++m) x[m] = Group<T, VEC, 4>::load(row, 16 * m + 4 * g, D);
+    }
+};
 template <typename T, int DP, bool VEC>
 struct RowFrag {
     float x[Shape<DP>::M][4];
-    __device__ __forceinline__ void load(const T* row, int g, int D) {
+    __device__ __forceinline__ void operator=(const RowRaw<T, DP, VEC>& r) {
 #pragma unroll
-        for (int m = 0; m < Shape<DP>::M; ++m) load_features<T, VEC, 4>(row, 16 * m + 4 * g, D, x[m]);
+        for (int m = 0; m < Shape<DP>::M; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[m][e] = widen(r.x[m][e]);
+    }
+    __device__ __forceinline__ void load(const T* row, int g, int D) {
+        RowRaw<T, DP, VEC> r;
+        r.load(row, g, D);
+        *this = r;
     }
 };
-// 16 rows as an operand of the second pattern: lane (i, g) holds rows 4 g + e, features 16 NF c + NF i + b.
+// 16 rows as an operand of the second pattern: lane (i, g) holds rows 4 g + e, features 16 NF c + NF i + b (as stored
+// where they were loaded as a vector).
 template <typename T, int DP, bool VEC>
 struct ColFrag {
-    float x[4][Shape<DP>::NC][Shape<DP>::NF];
+    typedef Group<T, VEC, Shape<DP>::NF> group;
+    typename group::type x[4][Shape<DP>::NC];
     template <typename RowPtr>
     __device__ __forceinline__ void load(RowPtr row_ptr, int i, int D) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const T* row = row_ptr(e);
 #pragma unroll
-            for (int c = 0; c < Shape<DP>::NC; ++c)
-                load_features<T, VEC, Shape<DP>::NF>(row, 16 * Shape<DP>::NF * c + Shape<DP>::NF * i, D, x[e][c]);
+            for (int c = 0; c < Shape<DP>::NC; ++c) x[e][c] = group::load(row, 16 * Shape<DP>::NF * c + Shape<DP>::NF * i, D);
         }
     }
 };
@@ -94,15 +147,6 @@ struct Acc {
 #pragma unroll
             for (int b = 0; b < Shape<DP>::NF; ++b) x[c][b] *= a;
     }
-    template <typename Frag>
-    __device__ __forceinline__ void mac(const Frag& a, const f32x4& p) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int c = 0; c < Shape<DP>::NC; ++c)
-#pragma unroll
-                for (int b = 0; b < Shape<DP>::NF; ++b) x[c][b] = mfma4(a.x[e][c][b], p[e], x[c][b]);
-    }
     // into column j of a [16][DP] block in LDS
     __device__ __forceinline__ void store(float* col, int g) const {
 #pragma unroll
@@ -114,13 +158,31 @@ struct Acc {
                     col[16 * Shape<DP>::NF * c + Shape<DP>::NF * (4 * g + e) + b] = x[c][b][e];
     }
 };
-template <int DP, typename FragA, typename FragB>
-__device__ __forceinline__ f32x4 dot_block(const FragA& a, const FragB& b, f32x4 acc) {
+// acc += A times P for every column block.  These accumulators live through the loops and stay where they are in all but one
+// kernel (it fences them itself): fences here cost 10 % (forward 45 -> 50 us at 12 heads, 4 frames of 336, fp32).
+template <int DP, typename Frag, int N>
+__device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, const f32x4 (&p)[N]) {
+    float x[4][Shape<DP>::NC][Shape<DP>::NF];
 #pragma unroll
-    for (int m = 0; m < Shape<DP>::M; ++m)
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc = mfma4(a.x[m][e], b.x[m][e], acc);
-    return acc;
+        for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+            for (int b = 0; b < Shape<DP>::NF; ++b) x[e][c][b] = widen(a.x[e][c][b]);
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+                for (int b = 0; b < Shape<DP>::NF; ++b) acc[n].x[c][b] = mfma4(x[e][c][b], p[n][e], acc[n].x[c][b]);
+}
+// The four rows 4 g + e of a block that starts at row r0 of `base`; past the last one (`n` rows) the last again.
+template <bool CLAMP, typename T>
+__device__ __forceinline__ auto block_rows(const T* base, int r0, int g, int n, int D) {
+    const T* first = base + (int64_t)(r0 + 4 * g) * D;
+    return [=](int e) { return CLAMP ? base + (int64_t)min(r0 + 4 * g + e, n - 1) * D : first + e * D; };
 }
 
 // Sum of the four wavefronts' [16 C][DP] blocks in LDS, times `factor(row)`, to rows row0 .. (below `limit`) of `dst`.
@@ -146,7 +208,7 @@ __host__ __forceinline__ int cols_per_workgroup(int64_t rows, int64_t BH, int D,
 }
 
 template <typename T, int DP, bool VEC, int CQ>
-__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
+__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : DP == 128 && sizeof(T) == 2 ? 3 : 2)
 attn_fwd_general(FwdParams p) {
     __shared__ float o_s[kWaves * 16 * CQ * DP];
     __shared__ float m_s[kWaves][16 * CQ], l_s[kWaves][16 * CQ], inv_s[16 * CQ];
@@ -171,25 +233,33 @@ attn_fwd_general(FwdParams p) {
         l[c] = 0.f;
         kmax_lane[c] = kmax_of_row(rc, p.T, p.P);
     }
-    const int kmin = kmax_of_row(min(r0, p.Sq - 1), p.T, p.P);
-    const int n_blk = (kmax_of_row(min(r0 + 16 * CQ, p.Sq) - 1, p.T, p.P) + 15) / 16;
+    const int kmin = kmax_of_row(min(r0, p.Sq - 1), p.T, p.P), kmax = kmax_of_row(min(r0 + 16 * CQ, p.Sq) - 1, p.T, p.P);
+    const int n_blk = (kmax + 15) / 16;
     // The next block's keys are requested before this block's products where that costs no resident wavefront (wide
     // heads: 726 against 778 us at 32 heads, 8 frames of 336, D = 128), behind them otherwise (D = 64: 314 against 318).
     constexpr bool PREFETCH = DP > 64;
-    RowFrag<T, DP, VEC> kf;
-    if (wave < n_blk) kf.load(kg + (int64_t)min(16 * wave + j, p.Sk - 1) * D, g, D);
-    for (int b = wave; b < n_blk; b += kWaves) {
+    RowRaw<T, DP, VEC> kr;  // the next block's keys, widened when their turn comes
+    if (wave < n_blk) kr.load(kg + (int64_t)min(16 * wave + j, p.Sk - 1) * D, g, D);
+    auto block = [&](int b, auto masked) {
         const int j0 = 16 * b;
         ColFrag<T, DP, VEC> vf;
-        vf.load([&](int e) { return vg + (int64_t)min(j0 + 4 * g + e, p.Sk - 1) * D; }, j, D);
-        RowFrag<T, DP, VEC> kn = kf;
-        if (PREFETCH && b + kWaves < n_blk) kn.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
+        vf.load(block_rows<masked>(vg, j0, g, p.Sk, D), j, D);
+        RowFrag<T, DP, VEC> kf;
+        kf = kr;
+        if (PREFETCH && b + kWaves < n_blk) kr.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
         f32x4 s[CQ];
+        zero(s);
+        begin_products();
 #pragma unroll
-        for (int c = 0; c < CQ; ++c) s[c] = dot_block<DP>(kf, qf[c], f32x4{0.f, 0.f, 0.f, 0.f});
+        for (int m = 0; m < Shape<DP>::M; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c = 0; c < CQ; ++c) s[c] = mfma4(kf.x[m][e], qf[c].x[m][e], s[c]);
+        end_products(s);
 #pragma unroll
         for (int c = 0; c < CQ; ++c) {
-            if (j0 + 16 > kmin) {
+            if (masked) {
                 const int left = kmax_lane[c] - (j0 + 4 * g);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -207,11 +277,12 @@ attn_fwd_general(FwdParams p) {
             l[c] = l[c] * alpha + ((s[c][0] + s[c][1]) + (s[c][2] + s[c][3]));
             if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) o[c].scale(alpha);
         }
-#pragma unroll
-        for (int c = 0; c < CQ; ++c) o[c].mac(vf, s[c]);
-        if constexpr (PREFETCH) kf = kn;
-        else if (b + kWaves < n_blk) kf.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
-    }
+        accumulate(o, vf, s);
+        if (!PREFETCH && b + kWaves < n_blk) kr.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
+    };
+    int b = wave;
+    for (; b < n_blk && 16 * b + 16 <= kmin; b += kWaves) block(b, std::false_type{});
+    for (; b < n_blk; b += kWaves) block(b, std::true_type{});
 #pragma unroll
     for (int c = 0; c < CQ; ++c) {
         l[c] += __shfl_xor(l[c], 16);
@@ -292,21 +363,20 @@ attn_bwd_dq_general(BwdParams p) {
         dq[c].zero();
         kmax_lane[c] = kmax_of_row(rc, p.T, p.P);
     }
-    const int kmin = kmax_of_row(min(r0, p.Sq - 1), p.T, p.P);
-    const int n_blk = (kmax_of_row(min(r0 + 16 * CQ, p.Sq) - 1, p.T, p.P) + 15) / 16;
-    for (int b = wave; b < n_blk; b += kWaves) {
+    const int kmin = kmax_of_row(min(r0, p.Sq - 1), p.T, p.P), kmax = kmax_of_row(min(r0 + 16 * CQ, p.Sq) - 1, p.T, p.P);
+    const int n_blk = (kmax + 15) / 16;
+    auto block = [&](int b, auto masked) {
         const int j0 = 16 * b;
         RowFrag<T, DP, VEC> kf, vf;
-        const int64_t at = (int64_t)min(j0 + j, p.Sk - 1) * D;
+        const int64_t at = (int64_t)(masked ? min(j0 + j, p.Sk - 1) : j0 + j) * D;
         kf.load(kg + at, g, D);
         vf.load(vg + at, g, D);
         ColFrag<T, DP, VEC> kt;
-        kt.load([&](int e) { return kg + (int64_t)min(j0 + 4 * g + e, p.Sk - 1) * D; }, j, D);
+        kt.load(block_rows<masked>(kg, j0, g, p.Sk, D), j, D);
         f32x4 s[CQ], dp[CQ];
-#pragma unroll
-        for (int c = 0; c < CQ; ++c) {
-            s[c] = dp[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        zero(s);
+        zero(dp);
+        begin_products();
 #pragma unroll
         for (int m = 0; m < Shape<DP>::M; ++m)
 #pragma unroll
@@ -316,18 +386,21 @@ attn_bwd_dq_general(BwdParams p) {
                     s[c] = mfma4(kf.x[m][e], qf[c].x[m][e], s[c]);
                     dp[c] = mfma4(vf.x[m][e], gf[c].x[m][e], dp[c]);
                 }
+        end_products(s, dp);
 #pragma unroll
         for (int c = 0; c < CQ; ++c) {
-            const int left = j0 + 16 > kmin ? kmax_lane[c] - (j0 + 4 * g) : 4;
+            const int left = masked ? kmax_lane[c] - (j0 + 4 * g) : 4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float pr = __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2[c]);
                 dp[c][e] = e < left ? pr * (dp[c][e] - delta[c]) : 0.f;
             }
         }
-#pragma unroll
-        for (int c = 0; c < CQ; ++c) dq[c].mac(kt, dp[c]);
-    }
+        accumulate(dq, kt, dp);
+    };
+    int b = wave;
+    for (; b < n_blk && 16 * b + 16 <= kmin; b += kWaves) block(b, std::false_type{});
+    for (; b < n_blk; b += kWaves) block(b, std::true_type{});
 #pragma unroll
     for (int c = 0; c < CQ; ++c) dq[c].store(o_s + (wave * 16 * CQ + 16 * c + j) * DP, g);
     __syncthreads();
@@ -335,7 +408,8 @@ attn_bwd_dq_general(BwdParams p) {
 }
 
 // dk, dv: a workgroup owns 16 CK keys, its wavefronts split the 16-row blocks of queries that see them.  A lane holds
-// key column j and rows 4 g + e of a block.  Key j is visible to row i iff i >= (floor(j/T) - P) T.
+// key column j and rows 4 g + e of a block.  Key j is visible to row i iff i >= (floor(j/T) - P) T: the blocks that cross a
+// bound are the first ones, and a ragged last one.
 template <typename T, int DP, bool VEC, int CK>
 __global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
 attn_bwd_dkdv_general(BwdParams p) {
@@ -352,6 +426,7 @@ attn_bwd_dkdv_general(BwdParams p) {
     RowFrag<T, DP, VEC> kf[CK], vf[CK];
     Acc<DP> dk[CK], dv[CK];
     int rmin_lane[CK];
+    auto first_row = [&](int key) { return max(0, (key / p.T - p.P) * p.T); };  // the first row that sees the key
 #pragma unroll
     for (int c = 0; c < CK; ++c) {
         const int kc = min(k0 + 16 * c + j, p.Sk - 1);
@@ -360,19 +435,35 @@ attn_bwd_dkdv_general(BwdParams p) {
         vf[c].load((const T*)p.v + at, g, D);
         dk[c].zero();
         dv[c].zero();
-        rmin_lane[c] = (kc / p.T - p.P) * p.T;
+        rmin_lane[c] = first_row(kc);
     }
-    const int b0 = max(0, (k0 / p.T - p.P) * p.T) / 16, b1 = (p.Sq + 15) / 16;
-    for (int b = b0 + wave; b < b1; b += kWaves) {
+    constexpr bool FENCED = DP == 32 && CK == 2;  // here the compiler moves dv and dk (see accumulate)
+    constexpr bool EARLY = DP <= 64;  // all four operands of a block are requested at once where the registers hold them
+    const int rmin = first_row(k0), rmax = first_row(min(k0 + 16 * CK, p.Sk) - 1);
+    const int b0 = rmin / 16, b1 = (p.Sq + 15) / 16;
+    auto block = [&](int b, auto masked) {
         const int i0 = 16 * b;
         f32x4 s[CK], dp[CK];
+        ColFrag<T, DP, VEC> tg, tq;
+        float lse2[4], dl[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int ic = masked ? min(i0 + 4 * g + e, p.Sq - 1) : i0 + 4 * g + e;
+            lse2[e] = lse[ic];
+            dl[e] = delta[ic];
+        }
         {
             RowFrag<T, DP, VEC> qa, ga;
-            const int64_t at = (int64_t)min(i0 + j, p.Sq - 1) * D;
+            const int64_t at = (int64_t)(masked ? min(i0 + j, p.Sq - 1) : i0 + j) * D;
             qa.load(qg + at, g, D);
             ga.load(gg + at, g, D);
-#pragma unroll
-            for (int c = 0; c < CK; ++c) s[c] = dp[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (EARLY) {
+                tg.load(block_rows<masked>(gg, i0, g, p.Sq, D), j, D);
+                tq.load(block_rows<masked>(qg, i0, g, p.Sq, D), j, D);
+            }
+            zero(s);
+            zero(dp);
+            begin_products();
 #pragma unroll
             for (int m = 0; m < Shape<DP>::M; ++m)
 #pragma unroll
@@ -382,28 +473,35 @@ attn_bwd_dkdv_general(BwdParams p) {
                         s[c] = mfma4(qa.x[m][e], kf[c].x[m][e], s[c]);
                         dp[c] = mfma4(ga.x[m][e], vf[c].x[m][e], dp[c]);
                     }
+            end_products(s, dp);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int i = i0 + 4 * g + e, ic = min(i, p.Sq - 1);
-            const float lse2 = lse[ic] * kLog2e, dl = delta[ic];
+            const int i = i0 + 4 * g + e;
 #pragma unroll
             for (int c = 0; c < CK; ++c) {
-                const bool seen = i >= rmin_lane[c] && i < p.Sq;
-                const float pr = seen ? __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2) : 0.f;
+                const bool seen = !masked || (i >= rmin_lane[c] && i < p.Sq);
+                const float pr = seen ? __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2[e] * kLog2e) : 0.f;
                 s[c][e] = pr;
-                dp[c][e] = pr * (dp[c][e] - dl);
+                dp[c][e] = pr * (dp[c][e] - dl[e]);
             }
         }
-        ColFrag<T, DP, VEC> t;
-        auto row_of = [&](const T* base) { return [=](int e) { return base + (int64_t)min(i0 + 4 * g + e, p.Sq - 1) * D; }; };
-        t.load(row_of(gg), j, D);
-#pragma unroll
-        for (int c = 0; c < CK; ++c) dv[c].mac(t, s[c]);
-        t.load(row_of(qg), j, D);
-#pragma unroll
-        for (int c = 0; c < CK; ++c) dk[c].mac(t, dp[c]);
-    }
+        auto add = [&](ColFrag<T, DP, VEC>& t, Acc<DP>(&acc)[CK], f32x4(&w)[CK]) {
+            if constexpr (FENCED) {  // weights complete, nothing of what comes before left over
+                pin(w);
+                begin_products();
+            }
+            accumulate(acc, t, w);
+        };
+        if (!EARLY) tg.load(block_rows<masked>(gg, i0, g, p.Sq, D), j, D);
+        add(tg, dv, s);
+        if (!EARLY) tq.load(block_rows<masked>(qg, i0, g, p.Sq, D), j, D);
+        add(tq, dk, dp);
+    };
+    int b = b0 + wave;
+    for (; b < b1 && 16 * b < rmax; b += kWaves) block(b, std::true_type{});
+    for (; b < b1 && 16 * b + 16 <= p.Sq; b += kWaves) block(b, std::false_type{});
+    for (; b < b1; b += kWaves) block(b, std::true_type{});
 #pragma unroll
     for (int c = 0; c < CK; ++c) dk[c].store(o_s + (wave * 16 * CK + 16 * c + j) * DP, g);
     __syncthreads();
