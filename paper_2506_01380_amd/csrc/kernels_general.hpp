@@ -18,7 +18,15 @@
 //   O^T[f, query] += V^T . P^T       step e contracts keys 4 k + e: B = the accumulators as they are; A row i of block
 //                                    (c, b) is feature 16 NF c + NF i + b: one load of NF features per lane and e
 //                                    D: query j, features 16 NF c + NF (4 g + e) + b
-// The gradients use the same two patterns.  DP: head width rounded up to 32, 64, 128 or 256; VEC: D == DP and rows
+// The gradients use the same two patterns.
+//
+// A pair that the mask excludes has weight zero, but the second pattern multiplies all 16 rows of a block into all 16
+// columns, and zero times an infinity or a NaN is a NaN: what a later frame holds must not reach an earlier one.  A block
+// that crosses a bound is therefore looked through first (one fma an element), and if it holds such a value it is
+// accumulated once per distinct bound of the workgroup's columns, the rows past that bound set to zero, each column
+// keeping the sums of its own pass.
+//
+// DP: head width rounded up to 32, 64, 128 or 256; VEC: D == DP and rows
 // 16-byte aligned, otherwise features are loaded one by one and those past D are zero.
 #pragma once
 #include "nfd_common.hpp"
@@ -131,6 +139,28 @@ struct ColFrag {
             for (int c = 0; c < Shape<DP>::NC; ++c) x[e][c] = group::load(row, 16 * Shape<DP>::NF * c + Shape<DP>::NF * i, D);
         }
     }
+    // does any lane of the wavefront hold an infinity or a NaN
+    __device__ __forceinline__ bool non_finite() const {
+        float t = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+                for (int b = 0; b < Shape<DP>::NF; ++b) t = __builtin_fmaf((float)x[e][c][b], 0.f, t);
+        return __builtin_amdgcn_ballot_w64(t != 0.f) != 0;
+    }
+    template <typename Seen>
+    __device__ __forceinline__ void zero_unless(Seen seen) {  // seen(e): whether the lane's row e counts
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool s = seen(e);
+#pragma unroll
+            for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+                for (int b = 0; b < Shape<DP>::NF; ++b) x[e][c][b] = s ? x[e][c][b] : 0;
+        }
+    }
 };
 template <int DP>
 struct Acc {
@@ -146,6 +176,25 @@ struct Acc {
         for (int c = 0; c < Shape<DP>::NC; ++c)
 #pragma unroll
             for (int b = 0; b < Shape<DP>::NF; ++b) x[c][b] *= a;
+    }
+    // plus A times P for the lanes that say so; the others keep their sums whatever the products are
+    template <typename Frag>
+    __device__ __forceinline__ void add_where(const Frag& a, const f32x4& p, bool mine) {
+#pragma unroll
+        for (int c = 0; c < Shape<DP>::NC; ++c)
+#pragma unroll
+            for (int b = 0; b < Shape<DP>::NF; ++b) {  // one after the other: four registers more, not all of them twice
+                f32x4 t = x[c][b];
+                float y[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = widen(a.x[e][c][b]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t = mfma4(y[e], p[e], t);
+                end_products(t);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[c][b][r] = mine ? t[r] : x[c][b][r];
+            }
     }
     // into column j of a [16][DP] block in LDS
     __device__ __forceinline__ void store(float* col, int g) const {
@@ -178,6 +227,12 @@ __device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, con
 #pragma unroll
                 for (int b = 0; b < Shape<DP>::NF; ++b) acc[n].x[c][b] = mfma4(x[e][c][b], p[n][e], acc[n].x[c][b]);
 }
+template <typename Frag, int N>
+__device__ __forceinline__ void done(Frag& a, f32x4 (&w)[N]) {  // a block already accumulated: nothing is left to add
+    a.zero_unless([](int) { return false; });
+    zero(w);
+}
+
 // The four rows 4 g + e of a block that starts at row r0 of `base`; past the last one (`n` rows) the last again.
 template <bool CLAMP, typename T>
 __device__ __forceinline__ auto block_rows(const T* base, int r0, int g, int n, int D) {
@@ -276,6 +331,14 @@ attn_fwd_general(FwdParams p) {
             for (int e = 0; e < 4; ++e) s[c][e] = __builtin_amdgcn_exp2f(s[c][e] - m_new);
             l[c] = l[c] * alpha + ((s[c][0] + s[c][1]) + (s[c][2] + s[c][3]));
             if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) o[c].scale(alpha);
+        }
+        if (masked && vf.non_finite()) {
+            for (int bound = kmax; bound >= kmin && bound > j0; bound -= p.T) {  // latest frame first: ever fewer rows count
+                vf.zero_unless([&](int e) { return j0 + 4 * g + e < bound; });
+#pragma unroll
+                for (int c = 0; c < CQ; ++c) o[c].add_where(vf, s[c], kmax_lane[c] == bound);
+            }
+            done(vf, s);
         }
         accumulate(o, vf, s);
         if (!PREFETCH && b + kWaves < n_blk) kr.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
@@ -396,6 +459,14 @@ attn_bwd_dq_general(BwdParams p) {
                 dp[c][e] = e < left ? pr * (dp[c][e] - delta[c]) : 0.f;
             }
         }
+        if (masked && kt.non_finite()) {
+            for (int bound = kmax; bound >= kmin && bound > j0; bound -= p.T) {  // latest frame first: ever fewer rows count
+                kt.zero_unless([&](int e) { return j0 + 4 * g + e < bound; });
+#pragma unroll
+                for (int c = 0; c < CQ; ++c) dq[c].add_where(kt, dp[c], kmax_lane[c] == bound);
+            }
+            done(kt, dp);
+        }
         accumulate(dq, kt, dp);
     };
     int b = wave;
@@ -409,7 +480,7 @@ attn_bwd_dq_general(BwdParams p) {
 
 // dk, dv: a workgroup owns 16 CK keys, its wavefronts split the 16-row blocks of queries that see them.  A lane holds
 // key column j and rows 4 g + e of a block.  Key j is visible to row i iff i >= (floor(j/T) - P) T: the blocks that cross a
-// bound are the first ones, and a ragged last one.
+// bound are the first ones (passes from the earliest frame on), and a ragged last one.
 template <typename T, int DP, bool VEC, int CK>
 __global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
 attn_bwd_dkdv_general(BwdParams p) {
@@ -483,10 +554,19 @@ attn_bwd_dkdv_general(BwdParams p) {
                 const bool seen = !masked || (i >= rmin_lane[c] && i < p.Sq);
                 const float pr = seen ? __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2[e] * kLog2e) : 0.f;
                 s[c][e] = pr;
-                dp[c][e] = pr * (dp[c][e] - dl[e]);
+                dp[c][e] = seen ? pr * (dp[c][e] - dl[e]) : 0.f;
             }
         }
         auto add = [&](ColFrag<T, DP, VEC>& t, Acc<DP>(&acc)[CK], f32x4(&w)[CK]) {
+            if (masked && t.non_finite()) {
+                t.zero_unless([&](int e) { return i0 + 4 * g + e < p.Sq; });
+                for (int bound = rmin; bound <= rmax && bound < i0 + 16; bound += p.T) {
+                    t.zero_unless([&](int e) { return i0 + 4 * g + e >= bound; });
+#pragma unroll
+                    for (int c = 0; c < CK; ++c) acc[c].add_where(t, w[c], rmin_lane[c] == bound);
+                }
+                done(t, w);
+            }
             if constexpr (FENCED) {  // weights complete, nothing of what comes before left over
                 pin(w);
                 begin_products();
