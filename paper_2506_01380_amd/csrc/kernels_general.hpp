@@ -208,9 +208,9 @@ struct Acc {
     }
 };
 // acc += A times P for every column block.  These accumulators live through the loops and stay where they are in all but one
-// kernel (it fences them itself): fences here cost 10 % (forward 45 -> 50 us at 12 heads, 4 frames of 336, fp32).
-template <int DP, typename Frag, int N>
-__device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, const f32x4 (&p)[N]) {
+// kernel: fences cost 10 % (forward 45 -> 50 us at 12 heads, 4 frames of 336, fp32), so only that one has them.
+template <bool FENCED = false, int DP, typename Frag, int N>
+__device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, f32x4 (&p)[N]) {
     float x[4][Shape<DP>::NC][Shape<DP>::NF];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -218,6 +218,10 @@ __device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, con
         for (int c = 0; c < Shape<DP>::NC; ++c)
 #pragma unroll
             for (int b = 0; b < Shape<DP>::NF; ++b) x[e][c][b] = widen(a.x[e][c][b]);
+    if constexpr (FENCED) {
+        pin(p);
+        begin_products();
+    }
 #pragma unroll
     for (int n = 0; n < N; ++n)
 #pragma unroll
@@ -226,6 +230,11 @@ __device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, con
             for (int c = 0; c < Shape<DP>::NC; ++c)
 #pragma unroll
                 for (int b = 0; b < Shape<DP>::NF; ++b) acc[n].x[c][b] = mfma4(x[e][c][b], p[n][e], acc[n].x[c][b]);
+    if constexpr (FENCED) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) pin(acc[n].x);
+        end_products();
+    }
 }
 template <typename Frag, int N>
 __device__ __forceinline__ void done(Frag& a, f32x4 (&w)[N]) {  // a block already accumulated: nothing is left to add
@@ -325,10 +334,10 @@ attn_fwd_general(FwdParams p) {
             a = fmaxf(a, __shfl_xor(a, 16));
             a = fmaxf(a, __shfl_xor(a, 32));
             const float m_new = fmaxf(m[c], a);
-            const float alpha = __builtin_amdgcn_exp2f(m[c] - m_new);
+            const float alpha = exp2f(m[c] - m_new);
             m[c] = m_new;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[c][e] = __builtin_amdgcn_exp2f(s[c][e] - m_new);
+            for (int e = 0; e < 4; ++e) s[c][e] = exp2f(s[c][e] - m_new);
             l[c] = l[c] * alpha + ((s[c][0] + s[c][1]) + (s[c][2] + s[c][3]));
             if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) o[c].scale(alpha);
         }
@@ -361,7 +370,7 @@ attn_fwd_general(FwdParams p) {
         float mm = m_s[0][16 * c + j];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) mm = fmaxf(mm, m_s[w][16 * c + j]);
-        o[c].scale(__builtin_amdgcn_exp2f(m[c] - mm));
+        o[c].scale(exp2f(m[c] - mm));
         o[c].store(o_s + (wave * 16 * CQ + 16 * c + j) * DP, g);
     }
     if ((int)threadIdx.x < 16 * CQ) {  // one thread per row: the merged row sum
@@ -370,7 +379,7 @@ attn_fwd_general(FwdParams p) {
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) mm = fmaxf(mm, m_s[w][r]);
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) ll += l_s[w][r] * __builtin_amdgcn_exp2f(m_s[w][r] - mm);
+        for (int w = 0; w < kWaves; ++w) ll += l_s[w][r] * exp2f(m_s[w][r] - mm);
         inv_s[r] = 1.0f / ll;
         if (p.lse && r0 + r < p.Sq) p.lse[(int64_t)bh * p.Sq + r0 + r] = (mm + log2f(ll)) * kLn2;
     }
@@ -455,7 +464,7 @@ attn_bwd_dq_general(BwdParams p) {
             const int left = masked ? kmax_lane[c] - (j0 + 4 * g) : 4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float pr = __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2[c]);
+                const float pr = exp2f(s[c][e] * p.scale_log2e - lse2[c]);
                 dp[c][e] = e < left ? pr * (dp[c][e] - delta[c]) : 0.f;
             }
         }
@@ -552,7 +561,7 @@ attn_bwd_dkdv_general(BwdParams p) {
 #pragma unroll
             for (int c = 0; c < CK; ++c) {
                 const bool seen = !masked || (i >= rmin_lane[c] && i < p.Sq);
-                const float pr = seen ? __builtin_amdgcn_exp2f(s[c][e] * p.scale_log2e - lse2[e] * kLog2e) : 0.f;
+                const float pr = seen ? exp2f(s[c][e] * p.scale_log2e - lse2[e] * kLog2e) : 0.f;
                 s[c][e] = pr;
                 dp[c][e] = seen ? pr * (dp[c][e] - dl[e]) : 0.f;
             }
@@ -567,11 +576,7 @@ attn_bwd_dkdv_general(BwdParams p) {
                 }
                 done(t, w);
             }
-            if constexpr (FENCED) {  // weights complete, nothing of what comes before left over
-                pin(w);
-                begin_products();
-            }
-            accumulate(acc, t, w);
+            accumulate<FENCED>(acc, t, w);
         };
         if (!EARLY) tg.load(block_rows<masked>(gg, i0, g, p.Sq, D), j, D);
         add(tg, dv, s);
