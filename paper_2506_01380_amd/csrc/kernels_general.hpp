@@ -26,8 +26,11 @@
 // accumulated once per distinct bound of the workgroup's columns, the rows past that bound set to zero, each column
 // keeping the sums of its own pass.
 //
-// DP: head width rounded up to 32, 64, 128 or 256; VEC: D == DP and rows
-// 16-byte aligned, otherwise features are loaded one by one and those past D are zero.
+// DP: head width rounded up to 32, 64, 128 or 256.  LOAD, how features are loaded (those past D are zero):
+//   kWhole   D == DP, tensors 16-byte aligned: vectors of four (two at DP = 32, second pattern)
+//   kGroups  D a multiple of four, tensors 16-byte aligned: the same vectors, each of them below D or past it.  One by one
+//            they took bf16, D = 96, 12 heads, 4 frames of 336: forward 280 us, backward 980, against 99 and 331
+//   kSingle  anything else: one by one
 #pragma once
 #include "nfd_common.hpp"
 
@@ -39,13 +42,19 @@ constexpr int kMaxD = 256;
 
 template <typename T> __device__ __forceinline__ T from_f32(float x) { return (T)x; }  // RNE for bf16
 
+enum { kSingle, kGroups, kWhole };
 // N consecutive features of a row, as stored where they are loaded as one vector.
-template <typename T, bool VEC, int N>
+template <typename T, int LOAD, int N>
 struct Group {
-    typedef __attribute__((ext_vector_type(N))) typename std::conditional<VEC, T, float>::type type;
+    typedef __attribute__((ext_vector_type(N))) typename std::conditional<LOAD != kSingle, T, float>::type type;
     static __device__ __forceinline__ type load(const T* row, int f, int D) {
-        if constexpr (VEC) {
+        if constexpr (LOAD == kWhole) {
             return *(const type*)(row + f);
+        } else if constexpr (LOAD == kGroups) {
+            type x = *(const type*)(row + (f < D ? f : 0));
+#pragma unroll
+            for (int e = 0; e < N; ++e) x[e] = f < D ? x[e] : 0;
+            return x;
         } else {
             type x;
 #pragma unroll
@@ -101,34 +110,34 @@ struct Shape {
 };
 
 // 16 rows as an operand of the first pattern: lane (i, g) holds row i, features 16 m + 4 g + e, as loaded and widened.
-template <typename T, int DP, bool VEC>
+template <typename T, int DP, int LOAD>
 struct RowRaw {
-    typename Group<T, VEC, 4>::type x[Shape<DP>::M];
+    typename Group<T, LOAD, 4>::type x[Shape<DP>::M];
     __device__ __forceinline__ void load(const T* row, int g, int D) {
 #pragma unroll
-        for (int m = 0; m < Shape<DP>::M; ++m) x[m] = Group<T, VEC, 4>::load(row, 16 * m + 4 * g, D);
+        for (int m = 0; m < Shape<DP>::M; ++m) x[m] = Group<T, LOAD, 4>::load(row, 16 * m + 4 * g, D);
     }
 };
-template <typename T, int DP, bool VEC>
+template <typename T, int DP, int LOAD>
 struct RowFrag {
     float x[Shape<DP>::M][4];
-    __device__ __forceinline__ void operator=(const RowRaw<T, DP, VEC>& r) {
+    __device__ __forceinline__ void operator=(const RowRaw<T, DP, LOAD>& r) {
 #pragma unroll
         for (int m = 0; m < Shape<DP>::M; ++m)
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[m][e] = widen(r.x[m][e]);
     }
     __device__ __forceinline__ void load(const T* row, int g, int D) {
-        RowRaw<T, DP, VEC> r;
+        RowRaw<T, DP, LOAD> r;
         r.load(row, g, D);
         *this = r;
     }
 };
 // 16 rows as an operand of the second pattern: lane (i, g) holds rows 4 g + e, features 16 NF c + NF i + b (as stored
 // where they were loaded as a vector).
-template <typename T, int DP, bool VEC>
+template <typename T, int DP, int LOAD>
 struct ColFrag {
-    typedef Group<T, VEC, Shape<DP>::NF> group;
+    typedef Group<T, LOAD, Shape<DP>::NF> group;
     typename group::type x[4][Shape<DP>::NC];
     template <typename RowPtr>
     __device__ __forceinline__ void load(RowPtr row_ptr, int i, int D) {
@@ -207,8 +216,8 @@ struct Acc {
                     col[16 * Shape<DP>::NF * c + Shape<DP>::NF * (4 * g + e) + b] = x[c][b][e];
     }
 };
-// acc += A times P for every column block.  These accumulators live through the loops and stay where they are in all but one
-// kernel: fences cost 10 % (forward 45 -> 50 us at 12 heads, 4 frames of 336, fp32), so only that one has them.
+// acc += A times P for every column block.  These accumulators live through the loops and stay where they are in all but the
+// kernels that say so: fences cost 10 % (forward 45 -> 50 us at 12 heads, 4 frames of 336, fp32), so only those have them.
 template <bool FENCED = false, int DP, typename Frag, int N>
 __device__ __forceinline__ void accumulate(Acc<DP> (&acc)[N], const Frag& a, f32x4 (&p)[N]) {
     float x[4][Shape<DP>::NC][Shape<DP>::NF];
@@ -271,8 +280,8 @@ __host__ __forceinline__ int cols_per_workgroup(int64_t rows, int64_t BH, int D,
     return padded_width(D) <= 64 && BH * ((rows + 31) / 32) >= 4 * num_cus ? 2 : 1;
 }
 
-template <typename T, int DP, bool VEC, int CQ>
-__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : DP == 128 && sizeof(T) == 2 ? 3 : 2)
+template <typename T, int DP, int LOAD, int CQ>
+__global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : DP == 128 && sizeof(T) == 2 && LOAD == kWhole ? 3 : 2)
 attn_fwd_general(FwdParams p) {
     __shared__ float o_s[kWaves * 16 * CQ * DP];
     __shared__ float m_s[kWaves][16 * CQ], l_s[kWaves][16 * CQ], inv_s[16 * CQ];
@@ -284,7 +293,7 @@ attn_fwd_general(FwdParams p) {
     const T* qg = (const T*)p.q + (int64_t)bh * p.Sq * D;
     const T* kg = (const T*)p.k + (int64_t)bh * p.Scap * D;
     const T* vg = (const T*)p.v + (int64_t)bh * p.Scap * D;
-    RowFrag<T, DP, VEC> qf[CQ];
+    RowFrag<T, DP, LOAD> qf[CQ];
     Acc<DP> o[CQ];
     float m[CQ], l[CQ];
     int kmax_lane[CQ];
@@ -302,13 +311,13 @@ attn_fwd_general(FwdParams p) {
     // The next block's keys are requested before this block's products where that costs no resident wavefront (wide
     // heads: 726 against 778 us at 32 heads, 8 frames of 336, D = 128), behind them otherwise (D = 64: 314 against 318).
     constexpr bool PREFETCH = DP > 64;
-    RowRaw<T, DP, VEC> kr;  // the next block's keys, widened when their turn comes
+    RowRaw<T, DP, LOAD> kr;  // the next block's keys, widened when their turn comes
     if (wave < n_blk) kr.load(kg + (int64_t)min(16 * wave + j, p.Sk - 1) * D, g, D);
     auto block = [&](int b, auto masked) {
         const int j0 = 16 * b;
-        ColFrag<T, DP, VEC> vf;
+        ColFrag<T, DP, LOAD> vf;
         vf.load(block_rows<masked>(vg, j0, g, p.Sk, D), j, D);
-        RowFrag<T, DP, VEC> kf;
+        RowFrag<T, DP, LOAD> kf;
         kf = kr;
         if (PREFETCH && b + kWaves < n_blk) kr.load(kg + (int64_t)min(j0 + 16 * kWaves + j, p.Sk - 1) * D, g, D);
         f32x4 s[CQ];
@@ -400,7 +409,7 @@ struct BwdParams {
     float scale, scale_log2e;
 };
 
-template <typename T, int DP, bool VEC, int CQ>
+template <typename T, int DP, int LOAD, int CQ>
 __global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
 attn_bwd_dq_general(BwdParams p) {
     __shared__ float o_s[kWaves * 16 * CQ * DP];
@@ -411,7 +420,7 @@ attn_bwd_dq_general(BwdParams p) {
     const int D = p.D;
     const T* kg = (const T*)p.k + (int64_t)bh * p.Scap * D;
     const T* vg = (const T*)p.v + (int64_t)bh * p.Scap * D;
-    RowFrag<T, DP, VEC> qf[CQ], gf[CQ];
+    RowFrag<T, DP, LOAD> qf[CQ], gf[CQ];
     Acc<DP> dq[CQ];
     float lse2[CQ], delta[CQ];
     int kmax_lane[CQ];
@@ -421,7 +430,7 @@ attn_bwd_dq_general(BwdParams p) {
         const int64_t at = ((int64_t)bh * p.Sq + rc) * D;
         qf[c].load((const T*)p.q + at, g, D);
         gf[c].load((const T*)p.dout + at, g, D);
-        RowFrag<T, DP, VEC> of;
+        RowFrag<T, DP, LOAD> of;
         of.load((const T*)p.out + at, g, D);
         float a = 0.f;
 #pragma unroll
@@ -439,11 +448,11 @@ attn_bwd_dq_general(BwdParams p) {
     const int n_blk = (kmax + 15) / 16;
     auto block = [&](int b, auto masked) {
         const int j0 = 16 * b;
-        RowFrag<T, DP, VEC> kf, vf;
+        RowFrag<T, DP, LOAD> kf, vf;
         const int64_t at = (int64_t)(masked ? min(j0 + j, p.Sk - 1) : j0 + j) * D;
         kf.load(kg + at, g, D);
         vf.load(vg + at, g, D);
-        ColFrag<T, DP, VEC> kt;
+        ColFrag<T, DP, LOAD> kt;
         kt.load(block_rows<masked>(kg, j0, g, p.Sk, D), j, D);
         f32x4 s[CQ], dp[CQ];
         zero(s);
@@ -490,7 +499,7 @@ attn_bwd_dq_general(BwdParams p) {
 // dk, dv: a workgroup owns 16 CK keys, its wavefronts split the 16-row blocks of queries that see them.  A lane holds
 // key column j and rows 4 g + e of a block.  Key j is visible to row i iff i >= (floor(j/T) - P) T: the blocks that cross a
 // bound are the first ones (passes from the earliest frame on), and a ragged last one.
-template <typename T, int DP, bool VEC, int CK>
+template <typename T, int DP, int LOAD, int CK>
 __global__ void __launch_bounds__(kWaves * 64, DP == 256 ? 1 : 2)
 attn_bwd_dkdv_general(BwdParams p) {
     __shared__ float o_s[kWaves * 16 * CK * DP];
@@ -503,7 +512,7 @@ attn_bwd_dkdv_general(BwdParams p) {
     const T* gg = (const T*)p.dout + (int64_t)bh * p.Sq * D;
     const float* lse = p.lse + (int64_t)bh * p.Sq;
     const float* delta = p.delta + (int64_t)bh * p.Sq;
-    RowFrag<T, DP, VEC> kf[CK], vf[CK];
+    RowFrag<T, DP, LOAD> kf[CK], vf[CK];
     Acc<DP> dk[CK], dv[CK];
     int rmin_lane[CK];
     auto first_row = [&](int key) { return max(0, (key / p.T - p.P) * p.T); };  // the first row that sees the key
@@ -517,14 +526,14 @@ attn_bwd_dkdv_general(BwdParams p) {
         dv[c].zero();
         rmin_lane[c] = first_row(kc);
     }
-    constexpr bool FENCED = DP == 32 && CK == 2;  // here the compiler moves dv and dk (see accumulate)
+    constexpr bool FENCED = CK == 2 && (DP == 32 || sizeof(T) == 2);  // here the compiler moves dv and dk (see accumulate)
     constexpr bool EARLY = DP <= 64;  // all four operands of a block are requested at once where the registers hold them
     const int rmin = first_row(k0), rmax = first_row(min(k0 + 16 * CK, p.Sk) - 1);
     const int b0 = rmin / 16, b1 = (p.Sq + 15) / 16;
     auto block = [&](int b, auto masked) {
         const int i0 = 16 * b;
         f32x4 s[CK], dp[CK];
-        ColFrag<T, DP, VEC> tg, tq;
+        ColFrag<T, DP, LOAD> tg, tq;
         float lse2[4], dl[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -533,7 +542,7 @@ attn_bwd_dkdv_general(BwdParams p) {
             dl[e] = delta[ic];
         }
         {
-            RowFrag<T, DP, VEC> qa, ga;
+            RowFrag<T, DP, LOAD> qa, ga;
             const int64_t at = (int64_t)(masked ? min(i0 + j, p.Sq - 1) : i0 + j) * D;
             qa.load(qg + at, g, D);
             ga.load(gg + at, g, D);
@@ -566,7 +575,7 @@ attn_bwd_dkdv_general(BwdParams p) {
                 dp[c][e] = seen ? pr * (dp[c][e] - dl[e]) : 0.f;
             }
         }
-        auto add = [&](ColFrag<T, DP, VEC>& t, Acc<DP>(&acc)[CK], f32x4(&w)[CK]) {
+        auto add = [&](ColFrag<T, DP, LOAD>& t, Acc<DP>(&acc)[CK], f32x4(&w)[CK]) {
             if (masked && t.non_finite()) {
                 t.zero_unless([&](int e) { return i0 + 4 * g + e < p.Sq; });
                 for (int bound = rmin; bound <= rmax && bound < i0 + 16; bound += p.T) {

@@ -105,23 +105,25 @@ BwdForm bwd_form(int64_t BH, int64_t Sq, int64_t Sk, int T, int P, int num_cus) 
     return std::max(1.93 * ws + 0.5 * 0.97 * longest, 0.97 * longest) < merged ? BwdForm::kMergedSmall : BwdForm::kMerged;
 }
 
-// Call f with the instance of the general kernels for these arguments: (element type, padded width, 16-byte loads, 16-column
-// blocks per workgroup).
+// Call f with the instance of the general kernels for these arguments: (element type, padded width, how features are loaded,
+// 16-column blocks per workgroup).  `aligned`: all tensors 16-byte aligned.
 template <typename Launch>
-void general_dispatch(nfd_dtype_t dtype, int D, bool vec, int cols, Launch f) {
+void general_dispatch(nfd_dtype_t dtype, int D, bool aligned, int cols, Launch f) {
+    using namespace nfd::general;
     auto width = [&](auto e, auto dp) {
-        typedef std::integral_constant<int, 1> C1;
-        typedef std::integral_constant<int, decltype(dp)::value <= 64 ? 2 : 1> C2;
-        constexpr bool never_vec = sizeof(e) == 2 && decltype(dp)::value == 64;  // bf16 with D = 64 takes the other path
-        if constexpr (!never_vec) {
-            if (vec && cols == 1) return f(e, dp, std::true_type{}, C1{});
-            if (vec) return f(e, dp, std::true_type{}, C2{});
-        }
-        if (cols == 1) f(e, dp, std::false_type{}, C1{});
-        else f(e, dp, std::false_type{}, C2{});
+        constexpr int DP = decltype(dp)::value;
+        auto load = [&](auto l) {
+            if constexpr (DP <= 64)
+                if (cols == 2) return f(e, dp, l, std::integral_constant<int, 2>{});
+            f(e, dp, l, std::integral_constant<int, 1>{});
+        };
+        if constexpr (sizeof(e) == 4 || DP != 64)  // bf16 with D = 64 takes the other path
+            if (aligned && D == DP) return load(std::integral_constant<int, kWhole>{});
+        if (aligned && D % 4 == 0) return load(std::integral_constant<int, kGroups>{});
+        load(std::integral_constant<int, kSingle>{});
     };
     auto type = [&](auto e) {
-        switch (nfd::general::padded_width(D)) {
+        switch (padded_width(D)) {
             case 32: return width(e, std::integral_constant<int, 32>{});
             case 64: return width(e, std::integral_constant<int, 64>{});
             case 128: return width(e, std::integral_constant<int, 128>{});
@@ -427,9 +429,9 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
             hipLaunchKernelGGL(nfd::mfma::attn_combine_d64, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);
         }
     } else {
-        const bool vec = D == nfd::general::padded_width(D) && ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) % 16 == 0;
-        general_dispatch(h->dtype, D, vec, pl.block_m / 16, [&](auto e, auto dp, auto v16, auto cols) {
-            hipLaunchKernelGGL((nfd::general::attn_fwd_general<decltype(e), decltype(dp)::value, decltype(v16)::value, decltype(cols)::value>),
+        const bool aligned = ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) % 16 == 0;
+        general_dispatch(h->dtype, D, aligned, pl.block_m / 16, [&](auto e, auto dp, auto load, auto cols) {
+            hipLaunchKernelGGL((nfd::general::attn_fwd_general<decltype(e), decltype(dp)::value, decltype(load)::value, decltype(cols)::value>),
                                dim3(pl.n_workgroups), dim3(nfd::general::kWaves * 64), 0, st, p);
         });
     }
@@ -597,14 +599,13 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
         g.scale_log2e = scale * nfd::kLog2e;
         hipStream_t gs = (hipStream_t)stream;
         const dim3 blk(nfd::general::kWaves * 64);
-        const bool vec = D == nfd::general::padded_width(D) &&
-                         ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)dout) % 16 == 0;
-        general_dispatch(h->dtype, D, vec, cq, [&](auto e, auto dp, auto v16, auto cols) {
-            hipLaunchKernelGGL((nfd::general::attn_bwd_dq_general<decltype(e), decltype(dp)::value, decltype(v16)::value, decltype(cols)::value>),
+        const bool aligned = ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)dout) % 16 == 0;
+        general_dispatch(h->dtype, D, aligned, cq, [&](auto e, auto dp, auto load, auto cols) {
+            hipLaunchKernelGGL((nfd::general::attn_bwd_dq_general<decltype(e), decltype(dp)::value, decltype(load)::value, decltype(cols)::value>),
                                dim3((unsigned)(BH * g.n_q_tiles)), blk, 0, gs, g);
         });
-        general_dispatch(h->dtype, D, vec, ck, [&](auto e, auto dp, auto v16, auto cols) {
-            hipLaunchKernelGGL((nfd::general::attn_bwd_dkdv_general<decltype(e), decltype(dp)::value, decltype(v16)::value, decltype(cols)::value>),
+        general_dispatch(h->dtype, D, aligned, ck, [&](auto e, auto dp, auto load, auto cols) {
+            hipLaunchKernelGGL((nfd::general::attn_bwd_dkdv_general<decltype(e), decltype(dp)::value, decltype(load)::value, decltype(cols)::value>),
                                dim3((unsigned)(BH * g.n_k_tiles)), blk, 0, gs, g);
         });
         return check_hip(h, hipGetLastError(), "general backward launch");
