@@ -19,6 +19,7 @@
 #include "kernels_mfma.hpp"
 #include "kernels_mfma16.hpp"
 #include "kernels_mfma_bwd.hpp"
+#include "kernels_rows.hpp"
 #include "kernels_stream.hpp"
 
 struct nfd_attn {
@@ -103,6 +104,37 @@ BwdForm bwd_form(int64_t BH, int64_t Sq, int64_t Sk, int T, int P, int num_cus) 
     const double w = steps(256, 192, 3) / (2.0 * num_cus), ws = steps(128, 64, 3) / (3.0 * num_cus);
     const double merged = std::max(2.7 * w + 0.5 * 1.57 * longest, 1.57 * longest);
     return std::max(1.93 * ws + 0.5 * 0.97 * longest, 0.97 * longest) < merged ? BwdForm::kMergedSmall : BwdForm::kMerged;
+}
+
+// Whether the kernels that give every row a wavefront of its own beat the tile kernels on the general path.  Both are priced as
+// the time of one wavefront (one workgroup of four) times how often the chip is filled; the constants are fitted (least
+// regret) to both sides measured at 1705 sizes a direction: 1 to 4096 keys and 1 to 85 rows a head, 2 to 4096 heads, ten
+// widths, both types.  Taking the cheaper, forward / backward are more than a tenth slower than the row kernels at 46 / 93 of
+// them (1.9 times at most), where the tile kernels alone were at over 400 / 600 (38 / 53 times).  4096 heads, fp32, D = 64, rows x
+// keys (rows / tiles, us): forward 1 x 1 7.4 / 31, 4 x 16 22 / 31, 16 x 16 71 / 34; backward 1 x 1 14 / 83, 8 x 8 103 / 105,
+// 16 x 16 250 / 122.
+struct GeneralPrice {
+    double row, row_dot, row_sum;                        // a row: fixed, per 64 keys and feature, per key and 64 features
+    double tile, tile_block, tile_load, one_by_one, one_by_one_16;  // a tile: fixed, per 64 keys, and per padded feature of it
+    double rows_per_cu, tiles_per_cu;                    // resident (tiles: times the workgroups per CU that the width leaves)
+};
+constexpr GeneralPrice kFwdPrice{2.9, 0.031, 0.058, 2.4, 0.9, 0.0012, 0.041, 0.021, 42.5, 0.82};
+constexpr GeneralPrice kBwdPrice{0.14, 0.0013, 0.096, 0.81, 0.23, 0.0016, 0.045, 0.026, 61.0, 2.97};
+double rows_minus_tiles(const GeneralPrice& c, nfd_dtype_t dtype, int64_t BH, int64_t rows, int64_t keys, int D, int num_cus) {
+    const int DP = nfd::general::padded_width(D);
+    const double k64 = (double)((keys + 63) / 64);
+    const double load = c.tile_load + (D % 4 == 0 ? 0.0 : c.one_by_one + (dtype == NFD_BF16 ? c.one_by_one_16 : 0.0));
+    const double row = (c.row + k64 * c.row_dot * D + (double)keys * c.row_sum * ((D + 63) / 64)) *
+                       std::max(1.0, (double)(BH * rows) / (c.rows_per_cu * num_cus));
+    const double tile = (c.tile + k64 * (c.tile_block + load * DP)) *
+                        std::max(1.0, (double)(BH * ((rows + 15) / 16)) / (c.tiles_per_cu * std::min(8, 256 / DP) * num_cus));
+    return row - tile;
+}
+bool rows_pay_fwd(nfd_dtype_t dtype, int64_t BH, int64_t Sq, int64_t Sk, int D, int num_cus) {
+    return rows_minus_tiles(kFwdPrice, dtype, BH, Sq, Sk, D, num_cus) < 0;
+}
+bool rows_pay_bwd(nfd_dtype_t dtype, int64_t BH, int64_t Sq, int64_t Sk, int D, int num_cus) {
+    return rows_minus_tiles(kBwdPrice, dtype, BH, Sq, Sk, D, num_cus) + rows_minus_tiles(kBwdPrice, dtype, BH, Sk, Sq, D, num_cus) < 0;
 }
 
 // Call f with the instance of the general kernels for these arguments: (element type, padded width, how features are loaded,
@@ -237,17 +269,20 @@ int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_f
         pl.workspace_bytes = splits > 1 ? (size_t)(BH * Sq) * splits * kPartialRowBytes : 0;
     } else {
         pl.kernel = 0;
-        pl.block_m = 16 * nfd::general::cols_per_workgroup(Sq, BH, D, num_cus);
-        pl.block_n = 16;
+        const bool rows = rows_pay_fwd(dtype, BH, Sq, (int64_t)kv_frames * T, D, num_cus);
+        pl.block_m = rows ? nfd::rows::kRowsPerWorkgroup : 16 * nfd::general::cols_per_workgroup(Sq, BH, D, num_cus);
+        pl.block_n = rows ? 64 : 16;
         pl.n_q_tiles = (int)((Sq + pl.block_m - 1) / pl.block_m);
         pl.n_splits = 1;
-        if (BH * pl.n_q_tiles > (int64_t)0x7fffffff) return NFD_ERR_UNSUPPORTED;
-        pl.n_workgroups = (int)(BH * pl.n_q_tiles);
+        const int64_t workgroups = rows ? (BH * Sq + pl.block_m - 1) / pl.block_m : BH * pl.n_q_tiles;
+        if (workgroups > (int64_t)0x7fffffff) return NFD_ERR_UNSUPPORTED;
+        pl.n_workgroups = (int)workgroups;
+        const int64_t step = rows ? 1 : pl.block_m;  // rows that walk the same keys
         int64_t visited = 0;
-        for (int64_t qt = 0; qt < pl.n_q_tiles; ++qt)
-            visited += (kmax_rows(std::min<int64_t>((qt + 1) * pl.block_m, Sq) - 1, T, P) + 15) / 16;
+        for (int64_t r = 0; r < Sq; r += step)
+            visited += (kmax_rows(std::min<int64_t>(r + step, Sq) - 1, T, P) + pl.block_n - 1) / pl.block_n;
         pl.key_tiles_visited = visited * BH;
-        pl.key_tiles_dense = (int64_t)pl.n_q_tiles * (((int64_t)kv_frames * T + 15) / 16) * BH;
+        pl.key_tiles_dense = (Sq + step - 1) / step * (((int64_t)kv_frames * T + pl.block_n - 1) / pl.block_n) * BH;
         pl.workspace_bytes = 0;
     }
     *plan = pl;
@@ -428,6 +463,10 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
             const int64_t total = (int64_t)p.BH * p.Sq * (nfd::mfma::kD / 4);
             hipLaunchKernelGGL(nfd::mfma::attn_combine_d64, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);
         }
+    } else if (pl.block_m == nfd::rows::kRowsPerWorkgroup) {
+        const dim3 grid(pl.n_workgroups), block(nfd::rows::kRowsPerWorkgroup * 64);
+        if (h->dtype == NFD_FP32) hipLaunchKernelGGL(nfd::rows::attn_fwd_rows<float>, grid, block, 0, st, p);
+        else hipLaunchKernelGGL(nfd::rows::attn_fwd_rows<__bf16>, grid, block, 0, st, p);
     } else {
         const bool aligned = ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) % 16 == 0;
         general_dispatch(h->dtype, D, aligned, pl.block_m / 16, [&](auto e, auto dp, auto load, auto cols) {
@@ -581,7 +620,7 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
     const int64_t BH = (int64_t)B * H, Sq = (int64_t)q_frames * T, Sk = (int64_t)kv_frames * T;
     if (h->dtype != NFD_BF16 || D != nfd::mfma::kD) {
         if (const int dc = check_device(h)) return dc;
-        // general path: fp32 arithmetic, one wavefront per row
+        // general path: fp32 arithmetic
         if ((size_t)(BH * Sq) * sizeof(float) > h->workspace_bytes)
             return fail(h, NFD_ERR_ALLOC, "the per-row workspace of the backward exceeds the handle's workspace");
         nfd::general::BwdParams g{};
@@ -599,6 +638,21 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
         g.scale_log2e = scale * nfd::kLog2e;
         hipStream_t gs = (hipStream_t)stream;
         const dim3 blk(nfd::general::kWaves * 64);
+        if (rows_pay_bwd(h->dtype, BH, Sq, Sk, D, h->num_cus)) {
+            constexpr int kR = nfd::rows::kRowsPerWorkgroup;
+            const int64_t nq = (BH * Sq + kR - 1) / kR, nk = (BH * Sk + kR - 1) / kR;
+            if (nq > (int64_t)0x7fffffff || nk > (int64_t)0x7fffffff)
+                return fail(h, NFD_ERR_UNSUPPORTED, "too many rows for one launch of the general backward");
+            const dim3 gq((unsigned)nq), gk((unsigned)nk), b4(kR * 64);
+            if (h->dtype == NFD_BF16) {
+                hipLaunchKernelGGL(nfd::rows::attn_bwd_dq_rows<__bf16>, gq, b4, 0, gs, g);
+                hipLaunchKernelGGL(nfd::rows::attn_bwd_dkdv_rows<__bf16>, gk, b4, 0, gs, g);
+            } else {
+                hipLaunchKernelGGL(nfd::rows::attn_bwd_dq_rows<float>, gq, b4, 0, gs, g);
+                hipLaunchKernelGGL(nfd::rows::attn_bwd_dkdv_rows<float>, gk, b4, 0, gs, g);
+            }
+            return check_hip(h, hipGetLastError(), "general backward launch");
+        }
         const bool aligned = ((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)dout) % 16 == 0;
         general_dispatch(h->dtype, D, aligned, cq, [&](auto e, auto dp, auto load, auto cols) {
             hipLaunchKernelGGL((nfd::general::attn_bwd_dq_general<decltype(e), decltype(dp)::value, decltype(load)::value, decltype(cols)::value>),
