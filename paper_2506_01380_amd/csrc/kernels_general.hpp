@@ -273,11 +273,15 @@ __device__ __forceinline__ void write_sum(const float* s, T* dst, int row0, int 
 }
 
 // C = columns (query rows, or keys in the dk/dv kernel) per workgroup in units of 16.  Two where the registers of two
-// wavefronts per SIMD hold them (DP <= 64): an operand register then feeds two matrix instructions.  One otherwise, and
-// where two would give the chip less than a workgroup per CU.
+// wavefronts per SIMD hold them (DP <= 64) and four workgroups per CU remain: an operand register then feeds two matrix
+// instructions, but there is half as much to keep the pipe busy between them.  Measured, one block / two (us, fp32, D = 64; the
+// workgroups per CU that two leave): backward 148 / 150 (2.0), 345 / 329 (4.4), 314 / 286 (6), 1254 / 1066 (10.5); forward 40 / 47
+// (2.0), 91 / 106 (4.4), 83 / 86 (6), 323 / 322 (10.5), 1389 / 1356 (27) - the forward's line is at eight there; at D = 32 it
+// is the same as the backward's: 55 / 51 (4.4), 48 / 49 (6), 183 / 172 (10.5).
 __host__ __device__ constexpr int padded_width(int D) { return D <= 32 ? 32 : D <= 64 ? 64 : D <= 128 ? 128 : 256; }
-__host__ __forceinline__ int cols_per_workgroup(int64_t rows, int64_t BH, int D, int num_cus) {
-    return padded_width(D) <= 64 && BH * ((rows + 31) / 32) >= 4 * num_cus ? 2 : 1;
+__host__ __forceinline__ int cols_per_workgroup(int64_t rows, int64_t BH, int D, int num_cus, bool forward) {
+    const int per_cu = forward && padded_width(D) == 64 && D % 4 == 0 ? 8 : 4;
+    return padded_width(D) <= 64 && BH * ((rows + 31) / 32) >= per_cu * num_cus ? 2 : 1;
 }
 
 template <typename T, int DP, int LOAD, int CQ>

@@ -270,7 +270,7 @@ int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_f
     } else {
         pl.kernel = 0;
         const bool rows = rows_pay_fwd(dtype, BH, Sq, (int64_t)kv_frames * T, D, num_cus);
-        pl.block_m = rows ? nfd::rows::kRowsPerWorkgroup : 16 * nfd::general::cols_per_workgroup(Sq, BH, D, num_cus);
+        pl.block_m = rows ? nfd::rows::kRowsPerWorkgroup : 16 * nfd::general::cols_per_workgroup(Sq, BH, D, num_cus, true);
         pl.block_n = rows ? 64 : 16;
         pl.n_q_tiles = (int)((Sq + pl.block_m - 1) / pl.block_m);
         pl.n_splits = 1;
@@ -624,7 +624,7 @@ int nfd_block_causal_attn_bwd(nfd_attn_t* h, const void* q, const void* k, const
         if ((size_t)(BH * Sq) * sizeof(float) > h->workspace_bytes)
             return fail(h, NFD_ERR_ALLOC, "the per-row workspace of the backward exceeds the handle's workspace");
         nfd::general::BwdParams g{};
-        const int cq = nfd::general::cols_per_workgroup(Sq, BH, D, h->num_cus), ck = nfd::general::cols_per_workgroup(Sk, BH, D, h->num_cus);
+        const int cq = nfd::general::cols_per_workgroup(Sq, BH, D, h->num_cus, false), ck = nfd::general::cols_per_workgroup(Sk, BH, D, h->num_cus, false);
         g.n_q_tiles = (int)((Sq + 16 * cq - 1) / (16 * cq));
         g.n_k_tiles = (int)((Sk + 16 * ck - 1) / (16 * ck));
         if (BH * g.n_q_tiles > (int64_t)0x7fffffff || BH * g.n_k_tiles > (int64_t)0x7fffffff)

@@ -23,9 +23,9 @@ def _on_gpu(x, dtype, offset):
 @pytest.mark.parametrize("dtype,D,offset", [
     ("fp32", 4, 0), ("fp32", 28, 0), ("fp32", 36, 0), ("fp32", 100, 0), ("fp32", 132, 0), ("fp32", 252, 0),
     ("bf16", 4, 0), ("bf16", 20, 0), ("bf16", 60, 0), ("bf16", 68, 0), ("bf16", 196, 0),
-    ("fp32", 64, 1), ("fp32", 36, 2), ("bf16", 32, 4), ("bf16", 96, 1),
+    ("fp32", 64, 0), ("fp32", 64, 1), ("fp32", 36, 2), ("bf16", 32, 4), ("bf16", 96, 1),
 ])
-@pytest.mark.parametrize("B,H,T,kvf,qf", [(1, 2, 21, 4, 3), (2, 24, 93, 8, 8)])  # one column block, two (D <= 64)
+@pytest.mark.parametrize("B,H,T,kvf,qf", [(1, 2, 21, 4, 3), (4, 24, 93, 8, 8)])  # one column block, two (D <= 64)
 def test_loads(dtype, D, offset, B, H, T, kvf, qf):
     q, k, v = wl.make_qkv(B, H, D, T, kvf, qf, kvf, dtype, seed=wl.BASE_SEED + 5000 + D)
     g = wl.randn(q.shape, wl.BASE_SEED + 5001, dtype)

@@ -12,7 +12,7 @@ SHAPES = [
     ("fp32", 1, 2, 20, 64, 3, 3),
     ("fp32", 1, 2, 5, 64, 9, 7),      # four frames in a block
     ("fp32", 1, 3, 1, 32, 40, 40),    # a frame a row
-    ("fp32", 2, 24, 95, 64, 8, 8),    # two column blocks per workgroup
+    ("fp32", 4, 24, 95, 64, 8, 8),    # two column blocks per workgroup
     ("fp32", 1, 2, 21, 129, 6, 6),
     ("fp32", 1, 1, 40, 256, 3, 2),
     ("bf16", 1, 2, 33, 62, 3, 3),
