@@ -343,6 +343,17 @@ int nfd_block_causal_attn_fwd_fp8kv(nfd_attn_t* h, const void* q, const void* k8
 int nfd_attn_work_item(int BH, int n_q_tiles, int n_splits, int group_q_tiles, unsigned block, int* bh, int* q_tile,
                        int* split);
 
+/* How nfd_block_causal_attn_bwd launches its work for these arguments (host only, like nfd_attn_plan; num_cus <= 0: 256), so that
+ * the choice can be checked without a GPU.  Errors: NFD_ERR_NULL, then those of nfd_attn_check_args. */
+enum {
+    NFD_BWD_SEPARATE = 0,     /* matrix cores, dq and dk/dv in a launch each */
+    NFD_BWD_MERGED = 1,       /* both in one launch, work items as in the separate ones */
+    NFD_BWD_MERGED_SMALL = 2, /* both in one launch, smaller work items */
+    NFD_BWD_TILES = 3,        /* general path, 16-row tiles */
+    NFD_BWD_ROWS = 4          /* general path, a wavefront a row */
+};
+int nfd_attn_bwd_form(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames, int num_cus, int* form);
+
 /* Query rows [first_row, first_row + n_rows) of query tile q_tile when a head's `rows` query rows are cut into
  * n_q_tiles tiles (the plan's count) for the matrix-core forward: the same function the kernel evaluates.  The 32-row
  * blocks are dealt evenly (tile sizes differ by at most 32 rows); the tiles are disjoint and cover all rows.

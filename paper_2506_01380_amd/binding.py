@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libnfd_attn.so")
 
 NFD_BF16, NFD_FP32 = 0, 1
+NFD_BWD_SEPARATE, NFD_BWD_MERGED, NFD_BWD_MERGED_SMALL, NFD_BWD_TILES, NFD_BWD_ROWS = range(5)
 NFD_OK, NFD_ERR_NULL, NFD_ERR_SHAPE, NFD_ERR_UNSUPPORTED = 0, -1, -2, -3
 NFD_ERR_CAPACITY, NFD_ERR_HIP, NFD_ERR_ALLOC = -4, -5, -6
 _ERR_NAMES = {
@@ -28,7 +29,7 @@ EXPORTS = (
     "nfd_block_causal_attn_fwd_lse", "nfd_block_causal_attn_bwd",
     "nfd_kvcache_shift", "nfd_spec_init", "nfd_spec_next", "nfd_spec_accept", "nfd_attn_work_item",
     "nfd_block_causal_attn_fwd_noalloc", "nfd_kvcache_append_attn_fwd",
-    "nfd_attn_q_tile_rows",
+    "nfd_attn_q_tile_rows", "nfd_attn_bwd_form",
     "nfd_fp8_cache_bytes", "nfd_kvcache_append_fp8", "nfd_block_causal_attn_fwd_fp8kv", "nfd_kvcache_shift_fp8", "nfd_rope_kvcache_append_fp8",
 )
 
@@ -115,6 +116,8 @@ def lib():
         L.nfd_attn_work_item.restype = ci
         L.nfd_attn_q_tile_rows.argtypes = [ci] * 3 + [ctypes.POINTER(ci)] * 2
         L.nfd_attn_q_tile_rows.restype = ci
+        L.nfd_attn_bwd_form.argtypes = [ci] * 9 + [ctypes.POINTER(ci)]
+        L.nfd_attn_bwd_form.restype = ci
         L.nfd_fp8_cache_bytes.argtypes = [ci] * 5 + [ctypes.POINTER(ctypes.c_size_t)]
         L.nfd_fp8_cache_bytes.restype = ci
         L.nfd_kvcache_append_fp8.argtypes = [vp] * 7 + [ci] * 7 + [vp]
@@ -300,6 +303,13 @@ def nfd_attn_work_item(BH, n_q_tiles, n_splits, group_q_tiles, block):
     rc = lib().nfd_attn_work_item(BH, n_q_tiles, n_splits, int(group_q_tiles), block, ctypes.byref(bh), ctypes.byref(qt),
                                   ctypes.byref(sp))
     return (bh.value, qt.value, sp.value) if rc == NFD_OK else None
+
+
+def nfd_attn_bwd_form(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus=0):
+    """How the backward of these arguments is launched: one of NFD_BWD_*."""
+    form = ctypes.c_int()
+    _check(lib().nfd_attn_bwd_form(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus, ctypes.byref(form)), "nfd_attn_bwd_form")
+    return form.value
 
 
 def nfd_attn_q_tile_rows(rows, n_q_tiles, q_tile):

@@ -82,7 +82,7 @@ int64_t kmax_rows(int64_t r_last, int T, int P) { return ((int64_t)P + r_last / 
 // Measured, backward of 16 frames of 336 tokens (us; separate / merged / merged small): 12 heads 280 / 175 / 188, 24 heads
 // 340 / 302 / 341, 48 heads 590 / 574 / 705, 64 heads 763 / 777 / 943; 12 heads, 11 frames of 247: 156 / 85 / 66;
 // 192 heads, 20 frames of 40: 116 / 100 / 94; 32 heads, 64 frames of 576: 16 180 / 17 040 / 22 900.
-enum class BwdForm { kSeparate, kMerged, kMergedSmall };
+enum class BwdForm { kSeparate = NFD_BWD_SEPARATE, kMerged = NFD_BWD_MERGED, kMergedSmall = NFD_BWD_MERGED_SMALL };
 BwdForm bwd_form(int64_t BH, int64_t Sq, int64_t Sk, int T, int P, int num_cus) {
     int64_t longest = 0;
     auto steps = [&](int rows, int keys, int fixed) {  // of all heads, `fixed` more per workgroup
@@ -99,9 +99,11 @@ BwdForm bwd_form(int64_t BH, int64_t Sq, int64_t Sk, int T, int P, int num_cus) 
         }
         return (double)(n * BH);
     };
-    if (steps(256, 192, 0) / (2.0 * num_cus) > 3.0 * longest) return BwdForm::kSeparate;
+    const double all = steps(256, 192, 0);  // sets `longest`
+    if (all / (2.0 * num_cus) > 3.0 * longest) return BwdForm::kSeparate;
     // a workgroup's first loads and final write cost about three steps
-    const double w = steps(256, 192, 3) / (2.0 * num_cus), ws = steps(128, 64, 3) / (3.0 * num_cus);
+    const double w = steps(256, 192, 3) / (2.0 * num_cus);
+    const double ws = steps(128, 64, 3) / (3.0 * num_cus);
     const double merged = std::max(2.7 * w + 0.5 * 1.57 * longest, 1.57 * longest);
     return std::max(1.93 * ws + 0.5 * 0.97 * longest, 0.97 * longest) < merged ? BwdForm::kMergedSmall : BwdForm::kMerged;
 }
@@ -286,6 +288,17 @@ int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_f
         pl.workspace_bytes = 0;
     }
     *plan = pl;
+    return NFD_OK;
+}
+
+int nfd_attn_bwd_form(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames, int num_cus, int* form) {
+    if (!form) return NFD_ERR_NULL;
+    const int rc = nfd_attn_check_args(dtype, B, H, F, T, D, kv_frames, q_frames);
+    if (rc != NFD_OK) return rc;
+    if (num_cus <= 0) num_cus = 256;
+    const int64_t BH = (int64_t)B * H, Sq = (int64_t)q_frames * T, Sk = (int64_t)kv_frames * T;
+    if (dtype == NFD_BF16 && D == nfd::mfma::kD) *form = (int)bwd_form(BH, Sq, Sk, T, kv_frames - q_frames, num_cus);
+    else *form = rows_pay_bwd(dtype, BH, Sq, Sk, D, num_cus) ? NFD_BWD_ROWS : NFD_BWD_TILES;
     return NFD_OK;
 }
 

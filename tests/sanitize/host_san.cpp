@@ -51,6 +51,12 @@ static void plans() {
                                     }
                                 }
                                 std::free(pl);
+                                if (rc != NFD_OK || (long)kv * T < 2000000) {
+                                    int* form = (int*)std::malloc(sizeof(int));
+                                    CHECK(nfd_attn_bwd_form((nfd_dtype_t)dt, 1, H, F, T, D, kv, qf, 256, form) == rc);
+                                    CHECK(rc != NFD_OK || (*form >= NFD_BWD_SEPARATE && *form <= NFD_BWD_ROWS));
+                                    std::free(form);
+                                }
                             }
     CHECK(n_ok > 100);
     int r0, nr;

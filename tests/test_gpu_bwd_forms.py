@@ -12,17 +12,18 @@ from paper_2506_01380_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,H,T,kvf,qf,F", [
-    (24, 32, 40, 6, 6, 6),      # separate: 768 heads of 240 rows
-    (24, 33, 23, 9, 9, 9),      # separate, 207 rows: a second key block of 15 keys
-    (28, 32, 40, 8, 3, 9),      # separate, cached form, capacity to spare
-    (4, 24, 150, 7, 7, 7),      # merged: 96 heads of 1050 rows
-    (3, 25, 151, 7, 6, 8),      # merged, cached form, head count off the XCD count
-    (1, 2, 65, 1, 1, 1),        # merged small: one frame, one row past a 64-row step
-    (1, 3, 129, 1, 1, 2),       # ... one row past a 128-row tile
-    (2, 5, 43, 6, 2, 7),        # ... cached form
+@pytest.mark.parametrize("B,H,T,kvf,qf,F,form", [
+    (24, 32, 40, 6, 6, 6, nb.NFD_BWD_SEPARATE),     # 768 heads of 240 rows
+    (24, 33, 23, 9, 9, 9, nb.NFD_BWD_SEPARATE),     # 207 rows: a second key block of 15 keys
+    (28, 32, 40, 8, 3, 9, nb.NFD_BWD_SEPARATE),     # cached form, capacity to spare
+    (4, 24, 150, 7, 7, 7, nb.NFD_BWD_MERGED),       # 96 heads of 1050 rows
+    (3, 25, 151, 7, 6, 8, nb.NFD_BWD_MERGED),       # cached form, head count off the XCD count
+    (1, 2, 65, 1, 1, 1, nb.NFD_BWD_MERGED_SMALL),   # one frame, one row past a 64-row step
+    (1, 3, 129, 1, 1, 2, nb.NFD_BWD_MERGED_SMALL),  # one row past a 128-row tile
+    (2, 5, 43, 6, 2, 7, nb.NFD_BWD_MERGED_SMALL),   # cached form
 ])
-def test_backward_launch_forms(B, H, T, kvf, qf, F):
+def test_backward_launch_forms(B, H, T, kvf, qf, F, form):
+    assert nb.nfd_attn_bwd_form(nb.NFD_BF16, B, H, F, T, 64, kvf, qf) == form
     q, k, v = wl.make_qkv(B, H, 64, T, kvf, qf, F, "bf16", seed=wl.BASE_SEED + 4000 + T)
     g = wl.randn(q.shape, wl.BASE_SEED + 4001)
     k[:, :, kvf * T:] = np.nan
