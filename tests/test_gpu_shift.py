@@ -58,3 +58,35 @@ def test_shift_fp8_bit_exact(B, H, T, F, kv, drop, offset):
     assert np.array_equal(gk[:, :, :keep], hk[:, :, drop * T: kv * T]) and np.array_equal(gk[:, :, kv * T:], hk[:, :, kv * T:])
     assert np.array_equal(gv[..., :keep], hv[..., drop * T: kv * T]) and np.array_equal(gv[..., kv * T:], hv[..., kv * T:])
     a.close()
+
+
+def test_shift_fp8_more_threads_than_a_launch():
+    """2^18 heads have 2^24 feature rows: at one workgroup a row, 2^32 threads and more."""
+    B, H, T, F = 512, 512, 16, 2
+    n = nb.nfd_fp8_cache_bytes(B, H, F, T, 64)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k8, v8 = (torch.randint(0, 2 ** 62, (n // 8,), device="cuda", generator=gen, dtype=torch.int64).view(torch.uint8) for _ in range(2))
+    want_k, want_v = k8.view(B * H, 64, 64)[:, T:2 * T].clone(), v8.view(B * H * 64, 64)[:, T:2 * T].clone()
+    a = nb.Attention("bf16")
+    nb.nfd_kvcache_shift_fp8(a.h, k8, v8, B, H, F, T, 64, 2, 1)
+    assert torch.equal(k8.view(B * H, 64, 64)[:, :T], want_k) and torch.equal(v8.view(B * H * 64, 64)[:, :T], want_v)
+    a.close()
+
+
+@pytest.mark.parametrize("dtype,T,D,F,kv,drop", [
+    ("bf16", 97, 65, 9, 9, 4),   # two-byte units, 12.1 million chains a tensor: several rounds of every block
+    ("bf16", 96, 64, 40, 37, 12),
+    ("fp32", 33, 63, 12, 11, 9),  # fewer kept than dropped
+])
+def test_shift_many_chains(dtype, T, D, F, kv, drop):
+    B, H = 8, 60
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(kv)
+    k, v = (torch.randn((B, H, F * T, D), device="cuda", generator=gen).to(td) for _ in range(2))
+    k0, v0 = k.clone(), v.clone()
+    a = nb.Attention(dtype)
+    nb.nfd_kvcache_shift(a.h, k, v, B, H, F, T, D, kv, drop)
+    keep = (kv - drop) * T
+    for x, x0 in ((k, k0), (v, v0)):
+        assert torch.equal(x[:, :, :keep], x0[:, :, drop * T:kv * T]) and torch.equal(x[:, :, kv * T:], x0[:, :, kv * T:])
+    a.close()
