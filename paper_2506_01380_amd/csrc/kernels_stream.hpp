@@ -43,27 +43,27 @@ struct ShiftRun {
     int64_t rows, d, len;
 };
 template <typename E>
-__device__ __forceinline__ void shift_chains(const ShiftRun& a, int64_t block, int64_t n_blocks) {
+__device__ __forceinline__ void shift_chains(const ShiftRun& a, int64_t block) {
     constexpr int U = 8;
-    for (int64_t idx = block * 256 + threadIdx.x; idx < a.rows * a.d; idx += n_blocks * 256) {
-        const int64_t row = idx <= 0xffffffffll && a.d <= 0xffffffffll ? (int64_t)((uint32_t)idx / (uint32_t)a.d) : idx / a.d;
-        E* base = (E*)a.base + row * a.stride;
-        int64_t x = idx - row * a.d;
-        for (; x + (U - 1) * a.d < a.len; x += U * a.d) {
-            E r[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) r[u] = base[x + (u + 1) * a.d];
-#pragma unroll
-            for (int u = 0; u < U; ++u) base[x + u * a.d] = r[u];
-        }
+    const int64_t idx = block * 256 + threadIdx.x;
+    if (idx >= a.rows * a.d) return;
+    const int64_t row = idx <= 0xffffffffll && a.d <= 0xffffffffll ? (int64_t)((uint32_t)idx / (uint32_t)a.d) : idx / a.d;
+    E* base = (E*)a.base + row * a.stride;
+    int64_t x = idx - row * a.d;
+    for (; x + (U - 1) * a.d < a.len; x += U * a.d) {
         E r[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (x + u * a.d < a.len) r[u] = base[x + (u + 1) * a.d];
+        for (int u = 0; u < U; ++u) r[u] = base[x + (u + 1) * a.d];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (x + u * a.d < a.len) base[x + u * a.d] = r[u];
+        for (int u = 0; u < U; ++u) base[x + u * a.d] = r[u];
     }
+    E r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (x + u * a.d < a.len) r[u] = base[x + (u + 1) * a.d];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (x + u * a.d < a.len) base[x + u * a.d] = r[u];
 }
 template <typename E, bool PERM>
 __device__ __forceinline__ void shift_row(const ShiftRun& a, int64_t row) {
@@ -87,22 +87,22 @@ __device__ __forceinline__ void shift_row(const ShiftRun& a, int64_t row) {
         __syncthreads();
     }
 }
-// Heads of two tensors of one geometry, as chains (blockIdx.y: which).  The grids are bounded and the blocks walk what there is
-// (a launch holds fewer than 2^32 threads, a tensor more units).
+// Heads of two tensors of one geometry, as chains (blocks below nblk0: the first tensor).  `first`: the launch's first block, as
+// very large windows take several.
 template <typename E>
 __global__ void __launch_bounds__(256)
-kvcache_shift_inplace(ShiftRun a, ShiftRun b) {
-    shift_chains<E>(blockIdx.y == 0 ? a : b, blockIdx.x, gridDim.x);
+kvcache_shift_inplace(ShiftRun a, ShiftRun b, int64_t nblk0, int64_t first) {
+    const int64_t block = first + blockIdx.x;
+    if (block < nblk0) shift_chains<E>(a, block);
+    else shift_chains<E>(b, block - nblk0);
 }
-// The 8-bit caches: heads of K codes as chains (blocks below nblk0), feature rows of V codes whole.
+// The 8-bit caches: heads of K codes as chains, feature rows of V codes whole.
 template <typename EK, typename EV, bool PERM>
 __global__ void __launch_bounds__(256)
-kvcache_shift_fp8_inplace(ShiftRun k, ShiftRun v, unsigned nblk0) {
-    if (blockIdx.x < nblk0) {
-        shift_chains<EK>(k, blockIdx.x, nblk0);
-        return;
-    }
-    for (int64_t row = blockIdx.x - nblk0; row < v.rows; row += gridDim.x - nblk0) shift_row<EV, PERM>(v, row);
+kvcache_shift_fp8_inplace(ShiftRun k, ShiftRun v, int64_t nblk0, int64_t first) {
+    const int64_t block = first + blockIdx.x;
+    if (block < nblk0) shift_chains<EK>(k, block);
+    else shift_row<EV, PERM>(v, block - nblk0);
 }
 
 // ---------------------------------------------------------------------------------------------

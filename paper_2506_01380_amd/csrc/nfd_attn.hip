@@ -168,9 +168,14 @@ void general_dispatch(nfd_dtype_t dtype, int D, bool aligned, int cols, Launch f
     else type((__bf16)0.f);
 }
 
-// Blocks for `items` (of 256 chains, or whole rows): all, or enough to fill the chip several times over.
-unsigned shift_grid(const nfd_attn_t* h, int64_t items) { return (unsigned)std::min<int64_t>(items, (int64_t)h->num_cus * 32); }
-unsigned shift_blocks(const nfd_attn_t* h, const nfd::ShiftRun& r) { return shift_grid(h, (r.rows * r.d + 255) / 256); }
+int64_t shift_blocks(const nfd::ShiftRun& r) { return (r.rows * r.d + 255) / 256; }
+// Launch `blocks` blocks in pieces: a launch holds fewer than 2^32 threads.  (Blocks that walked several runs each did away with
+// the pieces, but took 114 registers for 80 and a tenth to a third longer.)
+template <typename Launch>
+void in_pieces(int64_t blocks, Launch go) {
+    constexpr int64_t kPiece = 1 << 23;
+    for (int64_t first = 0; first < blocks; first += kPiece) go(first, dim3((unsigned)std::min(blocks - first, kPiece)));
+}
 
 // A chain of the one-pass move is walked by one thread.  Past this many links (very many frames kept for each one dropped)
 // the walk takes longer than copying the kept frames out to the workspace and back: 16 heads, 16 tokens a frame, one
@@ -784,10 +789,13 @@ int nfd_kvcache_shift(nfd_attn_t* h, void* k_cache, void* v_cache, int B, int H,
         launch_frame_copy(h, es, k_cache, v_cache, ks, vs, BH, stride * f, len * f, 0, 0, len * f, st);
         return check_hip(h, hipGetLastError(), "kvcache shift launch");
     }
-    const dim3 grid(shift_blocks(h, rk), 2), block(256);
-    if (vec) hipLaunchKernelGGL(nfd::kvcache_shift_inplace<nfd::u32x4>, grid, block, 0, st, rk, rv);
-    else if (es == 2) hipLaunchKernelGGL(nfd::kvcache_shift_inplace<uint16_t>, grid, block, 0, st, rk, rv);
-    else hipLaunchKernelGGL(nfd::kvcache_shift_inplace<uint32_t>, grid, block, 0, st, rk, rv);
+    const int64_t nb = shift_blocks(rk);
+    in_pieces(2 * nb, [&](int64_t first, dim3 grid) {
+        const dim3 block(256);
+        if (vec) hipLaunchKernelGGL(nfd::kvcache_shift_inplace<nfd::u32x4>, grid, block, 0, st, rk, rv, nb, first);
+        else if (es == 2) hipLaunchKernelGGL(nfd::kvcache_shift_inplace<uint16_t>, grid, block, 0, st, rk, rv, nb, first);
+        else hipLaunchKernelGGL(nfd::kvcache_shift_inplace<uint32_t>, grid, block, 0, st, rk, rv, nb, first);
+    });
     return check_hip(h, hipGetLastError(), "kvcache shift launch");
 }
 
@@ -818,15 +826,19 @@ int nfd_kvcache_shift_fp8(nfd_attn_t* h, void* k8, void* v8t, int B, int H, int 
         launch_frame_copy(h, 16, h->workspace, nullptr, k8, nullptr, BH, rk.len, rk.stride, 0, rk.d, rk.len, st);
         launch_frame_copy(h, 16, k8, nullptr, h->workspace, nullptr, BH, rk.stride, rk.len, 0, 0, rk.len, st);
     }
-    const unsigned nb = staged ? 0 : shift_blocks(h, rk);
-    const dim3 grid(nb + shift_grid(h, BH * D)), block(256);
+    const int64_t nb = staged ? 0 : shift_blocks(rk);
+    const dim3 block(256);
     if (vec && T % 16 == 0) {
         const nfd::ShiftRun rv{v8t, Spad / 16, BH * D, (int64_t)n_drop * T / 16, keep_keys / 16};
-        hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<nfd::u32x4, nfd::u32x4, false>), grid, block, 0, st, rk, rv, nb);
+        in_pieces(nb + rv.rows, [&](int64_t first, dim3 grid) {
+            hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<nfd::u32x4, nfd::u32x4, false>), grid, block, 0, st, rk, rv, nb, first);
+        });
     } else {
         const nfd::ShiftRun rv{v8t, Spad, BH * D, (int64_t)n_drop * T, keep_keys};
-        if (vec) hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<nfd::u32x4, unsigned char, true>), grid, block, 0, st, rk, rv, nb);
-        else hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<unsigned char, unsigned char, true>), grid, block, 0, st, rk, rv, nb);
+        in_pieces(nb + rv.rows, [&](int64_t first, dim3 grid) {
+            if (vec) hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<nfd::u32x4, unsigned char, true>), grid, block, 0, st, rk, rv, nb, first);
+            else hipLaunchKernelGGL((nfd::kvcache_shift_fp8_inplace<unsigned char, unsigned char, true>), grid, block, 0, st, rk, rv, nb, first);
+        });
     }
     return check_hip(h, hipGetLastError(), "8-bit kvcache shift launch");
 }

@@ -74,7 +74,7 @@ def test_shift_fp8_more_threads_than_a_launch():
 
 
 @pytest.mark.parametrize("dtype,T,D,F,kv,drop", [
-    ("bf16", 97, 65, 9, 9, 4),   # two-byte units, 12.1 million chains a tensor: several rounds of every block
+    ("bf16", 97, 65, 9, 9, 4),   # two-byte units, 12.1 million chains a tensor
     ("bf16", 96, 64, 40, 37, 12),
     ("fp32", 33, 63, 12, 11, 9),  # fewer kept than dropped
 ])
