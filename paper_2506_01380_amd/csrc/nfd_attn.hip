@@ -177,6 +177,12 @@ void in_pieces(int64_t blocks, Launch go) {
     for (int64_t first = 0; first < blocks; first += kPiece) go(first, dim3((unsigned)std::min(blocks - first, kPiece)));
 }
 
+// Kept units that land where only dropped ones were can be copied.  That is the better way where few are kept: the chains' grid
+// covers the dropped ones (8 sequences of 16 heads, 64 frames of 576, 60 dropped: 23 us copied, 151 as chains; 33 of 64
+// frames of 336: 133 and 120), and without vectors also where about as many are (8-bit, 33 of 64 frames, caches off a 16-byte
+// boundary: 200 and 336).
+bool shift_copied(const nfd::ShiftRun& r, bool vec) { return r.len <= (vec ? r.d / 2 : r.d); }
+
 // A chain of the one-pass move is walked by one thread.  Past this many links (very many frames kept for each one dropped)
 // the walk takes longer than copying the kept frames out to the workspace and back: 16 heads, 16 tokens a frame, one
 // frame dropped: 7.1 against 9.6 us at 63 links, 11.5 against 9.5 at 127, 37 against 22 at 511.
@@ -746,6 +752,7 @@ static void launch_frame_copy(nfd_attn_t* h, size_t es, void* kd, void* vd, cons
                                len / f, BH);
     };
     if (vec) go(nfd::u32x4{}, (int64_t)(16 / es));
+    else if (es == 1) go((unsigned char)0, 1);
     else if (es == 2) go((uint16_t)0, 1);
     else go((uint32_t)0, 1);
 }
@@ -782,6 +789,10 @@ int nfd_kvcache_shift(nfd_attn_t* h, void* k_cache, void* v_cache, int B, int H,
     const int64_t stride = (int64_t)F * frame / f, d = n_drop * frame / f, len = (kv_frames - n_drop) * frame / f;
     const nfd::ShiftRun rk{k_cache, stride, BH, d, len}, rv{v_cache, stride, BH, d, len};
     hipStream_t st = (hipStream_t)stream;
+    if (shift_copied(rk, vec)) {
+        launch_frame_copy(h, es, k_cache, v_cache, k_cache, v_cache, BH, stride * f, stride * f, 0, d * f, len * f, st);
+        return check_hip(h, hipGetLastError(), "kvcache shift launch");
+    }
     if (shift_staged(h, rk, f * es, 2)) {
         void* ks = h->workspace;
         void* vs = (char*)h->workspace + (size_t)(BH * len * f) * es;
@@ -821,12 +832,18 @@ int nfd_kvcache_shift_fp8(nfd_attn_t* h, void* k8, void* v8t, int B, int H, int 
     const bool vec = ((uintptr_t)k8 | (uintptr_t)v8t) % 16 == 0;
     const int64_t f = vec ? 16 : 1;  // bytes per unit
     const nfd::ShiftRun rk{k8, Spad * D / f, BH, (int64_t)n_drop * T * D / f, keep_keys * D / f};
-    const bool staged = vec && shift_staged(h, rk, 16, 1);
-    if (staged) {
+    const bool copied = shift_copied(rk, vec), staged = !copied && vec && shift_staged(h, rk, 16, 1);
+    if (copied) {
+        launch_frame_copy(h, 1, k8, nullptr, k8, nullptr, BH, Spad * D, Spad * D, 0, (int64_t)n_drop * T * D, keep_keys * D, st);
+        if (T % 16 == 0) {
+            launch_frame_copy(h, 1, v8t, nullptr, v8t, nullptr, BH * D, Spad, Spad, 0, (int64_t)n_drop * T, keep_keys, st);
+            return check_hip(h, hipGetLastError(), "8-bit kvcache shift launch");
+        }
+    } else if (staged) {
         launch_frame_copy(h, 16, h->workspace, nullptr, k8, nullptr, BH, rk.len, rk.stride, 0, rk.d, rk.len, st);
         launch_frame_copy(h, 16, k8, nullptr, h->workspace, nullptr, BH, rk.stride, rk.len, 0, 0, rk.len, st);
     }
-    const int64_t nb = staged ? 0 : shift_blocks(rk);
+    const int64_t nb = copied || staged ? 0 : shift_blocks(rk);
     const dim3 block(256);
     if (vec && T % 16 == 0) {
         const nfd::ShiftRun rv{v8t, Spad / 16, BH * D, (int64_t)n_drop * T / 16, keep_keys / 16};

@@ -20,6 +20,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 1, 2, 4, 64, 99, 98, 1, 1024),  # the same, no workspace for it
     ("bf16", 1, 2, 3, 33, 12, 11, 2, 0),     # two-byte units
     ("fp32", 1, 2, 5, 31, 20, 19, 3, 0),     # four-byte units
+    ("bf16", 1, 2, 8, 64, 9, 9, 6, 0),       # three kept, six dropped: copied
+    ("bf16", 1, 2, 8, 64, 9, 9, 5, 0),       # four kept, five dropped: chains of one link
+    ("bf16", 1, 2, 3, 33, 12, 12, 6, 0),     # two-byte units, as many kept as dropped: copied
+    ("fp32", 1, 2, 5, 31, 20, 19, 9, 0),     # one more kept: chains
 ])
 def test_shift_bit_exact(dtype, B, H, T, D, F, kv, drop, ws):
     a = nb.Attention(dtype, workspace_bytes=ws)
@@ -40,6 +44,9 @@ def test_shift_bit_exact(dtype, B, H, T, D, F, kv, drop, ws):
     (1, 1, 336, 100, 100, 1),  # a feature row of more than one piece of 2048 vectors; 99 links of K: staged
     (1, 2, 100, 24, 23, 3),    # T no multiple of 16: V key by key, 2000 keys, one piece
     (1, 1, 100, 24, 24, 1),    # ... 2300 keys, two pieces
+    (2, 3, 48, 9, 9, 6),       # K and V copied
+    (2, 3, 48, 9, 9, 5),       # chains, or copied off the boundary
+    (2, 3, 37, 9, 8, 6),       # K copied, V key by key
 ])
 @pytest.mark.parametrize("offset", [0, 4])  # 4: caches not 16-byte aligned
 def test_shift_fp8_bit_exact(B, H, T, F, kv, drop, offset):
