@@ -467,6 +467,8 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
         //         two wavefronts of 64 rows and two of 32 (which lack the pipelined loop) at the same barriers; one frame of 576
         //         tokens over 64: 750 -> 685.  At five blocks 48 rows take 49.6 against 48.5, and splitting 42 blocks into
         //         seven tiles of six instead of six of seven 75.6 against 76.5 (90.1 against 85.9 over the 8-bit cache).
+        //   five  over the 8-bit cache also 48 rows: 8 sequences of 16 heads, one frame of 150 over 63: 71.8, with 64 rows 76.0 (76.3 of the
+        //         kernel before); 12 such sizes take 0.93 to 1.02 of what 64 rows take.
         //   1..4  one block per wavefront: the 128-row kernel, three workgroups per CU: with log-sum-exp 13.0 against 14.8 us
         //         (one block), 34.1 against 35.1 (four); over the 8-bit cache 34.8 against 40.9 (48 rows).  Not for
         //         the plain forward, whose row sums are of the rounded weights that the output is formed from: the 128-row
@@ -476,7 +478,7 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
             if (kv8) go(attn_fwd_bf16_d64<true>);
             else if (lse) go(attn_fwd_bf16_d64<false, true>);  // training pair: scores from the queries as given
             else go(attn_fwd_bf16_d64<false>);
-        } else if (tile_blocks != kBM48 / 32) {
+        } else if (!(tile_blocks == kBM48 / 32 || (kv8 && tile_blocks == 5))) {
             if (kv8) go(attn_fwd_bf16_d64_m16<false, true>);
             else if (lse) go(attn_fwd_bf16_d64_m16<true>);
             else go(attn_fwd_bf16_d64_m16<false>);
