@@ -189,43 +189,38 @@ __device__ __forceinline__ WorkItem decode_work(const FwdParams& p) {
 
 // Final write of one wavefront's 64 query rows: normalised bf16 output when the keys were not
 // split, otherwise the unnormalised accumulator (bf16) plus (reference max in log2 units, row sum; fp32).
-// Lane (n, h) holds, for query column n of block qt, output features 32*dt + 8*rb + 4*h + 0..3.
-template <int QT>
-__device__ __forceinline__ void store_rows(const FwdParams& p, const WorkItem& wi, const int (&row)[QT], int h,
-                                           const f32x16 (&o_acc)[2][QT], const float (&l_sum)[QT],
-                                           const float (&m_used)[QT]) {
+// Lane (n, h) holds, for query column n, output features 32*dt + 8*rb + 4*h + 0..3.
+__device__ __forceinline__ void store_rows(const FwdParams& p, const WorkItem& wi, int row, int h,
+                                           const f32x16 (&o_acc)[2], float l_sum, float m_used) {
+    const float l_row = l_sum + __shfl_xor(l_sum, 32);
+    if (row >= p.Sq) return;
+    if (p.n_splits == 1) {
+        const float inv = 1.0f / l_row;
+        __bf16* og = (__bf16*)p.out + ((int64_t)wi.bh * p.Sq + row) * kD;
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const float l_row = l_sum[qt] + __shfl_xor(l_sum[qt], 32);
-        if (row[qt] >= p.Sq) continue;
-        if (p.n_splits == 1) {
-            const float inv = 1.0f / l_row;
-            __bf16* og = (__bf16*)p.out + ((int64_t)wi.bh * p.Sq + row[qt]) * kD;
+        for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const f32x4 x = {o_acc[dt][qt][4 * rb] * inv, o_acc[dt][qt][4 * rb + 1] * inv,
-                                     o_acc[dt][qt][4 * rb + 2] * inv, o_acc[dt][qt][4 * rb + 3] * inv};
-                    const bf16x4 y = __builtin_convertvector(x, bf16x4);
-                    *(bf16x4*)(og + 32 * dt + 8 * rb + 4 * h) = y;
-                }
-            if (p.lse && h == 0) p.lse[(int64_t)wi.bh * p.Sq + row[qt]] = (m_used[qt] + __builtin_log2f(l_row)) * kLn2;
-        } else {
-            const int64_t prow = ((int64_t)wi.bh * p.n_splits + wi.split) * p.Sq + row[qt];
-            __bf16* po = p.part_o + prow * kD;
-#pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const f32x4 x = {o_acc[dt][qt][4 * rb], o_acc[dt][qt][4 * rb + 1], o_acc[dt][qt][4 * rb + 2],
-                                     o_acc[dt][qt][4 * rb + 3]};
-                    *(bf16x4*)(po + 32 * dt + 8 * rb + 4 * h) = __builtin_convertvector(x, bf16x4);
-                }
-            if (h == 0) {
-                const f32x2 ml = {m_used[qt], l_row};
-                *(f32x2*)(p.part_ml + prow * 2) = ml;
+            for (int rb = 0; rb < 4; ++rb) {
+                const f32x4 x = {o_acc[dt][4 * rb] * inv, o_acc[dt][4 * rb + 1] * inv,
+                                 o_acc[dt][4 * rb + 2] * inv, o_acc[dt][4 * rb + 3] * inv};
+                const bf16x4 y = __builtin_convertvector(x, bf16x4);
+                *(bf16x4*)(og + 32 * dt + 8 * rb + 4 * h) = y;
             }
+        if (p.lse && h == 0) p.lse[(int64_t)wi.bh * p.Sq + row] = (m_used + __builtin_log2f(l_row)) * kLn2;
+    } else {
+        const int64_t prow = ((int64_t)wi.bh * p.n_splits + wi.split) * p.Sq + row;
+        __bf16* po = p.part_o + prow * kD;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb) {
+                const f32x4 x = {o_acc[dt][4 * rb], o_acc[dt][4 * rb + 1], o_acc[dt][4 * rb + 2],
+                                 o_acc[dt][4 * rb + 3]};
+                *(bf16x4*)(po + 32 * dt + 8 * rb + 4 * h) = __builtin_convertvector(x, bf16x4);
+            }
+        if (h == 0) {
+            const f32x2 ml = {m_used, l_row};
+            *(f32x2*)(p.part_ml + prow * 2) = ml;
         }
     }
 }
@@ -254,7 +249,6 @@ struct SmemOf {
 template <bool KV8, bool EXACTQ>
 __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem& wi, typename SmemOf<KV8>::type& sm) {
     constexpr int PRIO = kMfmaPriority;
-    constexpr int QT = 1;  // 32-row blocks per wavefront
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -305,46 +299,35 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
     // rounded to bf16: the score accumulators then hold base-2 exponents directly and the softmax needs no multiply.
     float c = p.scale_log2e;
     if constexpr (KV8) c *= p.k_scale[wi.bh];  // scores of the codes -> scores of the values
-    int row[QT], kmax_lane[QT];
-    int kmin_blk[QT], kmax_blk[QT];  // key bound of a block's first / last row: mask needed above, nothing beyond
-    bf16x8 qf[QT][4];
+    const int b0 = r0 + 32 * wave, row = b0 + n;
+    const int rc = min(row, p.Sq - 1);  // rows past the end: compute a duplicate, never store it
+    const int kmax_lane = kmax_of_row(rc, p.T, p.P);
+    const int kmin_wave = kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);       // key bound of the wavefront's first row: mask needed above
+    const int kmax_wave = kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);  // and last: tiles starting at or above are skipped
+    bf16x8 qf[4];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const int b0 = r0 + 32 * wave;
-        row[qt] = b0 + n;
-        const int rc = min(row[qt], p.Sq - 1);  // rows past the end: compute a duplicate, never store it
-        kmax_lane[qt] = kmax_of_row(rc, p.T, p.P);
-        kmin_blk[qt] = kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
-        kmax_blk[qt] = kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);
+    for (int ks = 0; ks < 4; ++ks) {
+        // contraction step ks, lane half h: features 16*ks + 8*h ..+7; with the 8-bit cache the features of
+        // the 16-byte chunk 2*(ks/2) + h, first or second half (ks % 2) - the order the K reads deliver
+        const int d0 = KV8 ? 16 * (2 * (ks >> 1) + h) + 8 * (ks & 1) : 16 * ks + 8 * h;
+        const bf16x8 raw = *(const bf16x8*)(qg + (int64_t)rc * kD + d0);
+        if constexpr (EXACTQ) {
+            qf[ks] = raw;
+        } else {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            // contraction step ks, lane half h: features 16*ks + 8*h ..+7; with the 8-bit cache the features of
-            // the 16-byte chunk 2*(ks/2) + h, first or second half (ks % 2) - the order the K reads deliver
-            const int d0 = KV8 ? 16 * (2 * (ks >> 1) + h) + 8 * (ks & 1) : 16 * ks + 8 * h;
-            const bf16x8 raw = *(const bf16x8*)(qg + (int64_t)rc * kD + d0);
-            if constexpr (EXACTQ) {
-                qf[qt][ks] = raw;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) qf[qt][ks][e] = (__bf16)((float)raw[e] * c);
-            }
+            for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)raw[e] * c);
         }
     }
-    const int kmax_wave = kmax_blk[QT - 1];  // tiles starting at or above are skipped (blocks ascend)
     const bool wave_active = wave < n_blk;
 
-    f32x16 o_acc[2][QT];  // [dt][qt]: O^T rows 32*dt.., query block qt
+    f32x16 o_acc[2];  // [dt]: O^T rows 32*dt..
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < QT; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o_acc[a][b][r] = 0.f;
-    float m_used[QT];  // reference max (stale by design), in the units of the score accumulators: base-2 exponents,
-                       // or raw scores (exponent = c * score) with EXACTQ
-    float l_sum[QT];   // this lane's share of the row sum
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) { m_used[qt] = kNegBig; l_sum[qt] = 0.f; }
+        for (int r = 0; r < 16; ++r) o_acc[a][r] = 0.f;
+    float m_used = kNegBig;  // reference max (stale by design), in the units of the score accumulators: base-2 exponents,
+                             // or raw scores (exponent = c * score) with EXACTQ
+    float l_sum = 0.f;       // this lane's share of the row sum
 
     // ---- tile loads: one wave instruction fills 8 consecutive tile rows (1 KB); a wavefront owns
     // rows 8*wave + 32*pass + lane/8, and each lane fetches the chunk that belongs at its position ----
@@ -453,7 +436,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
             const auto* ks_ = sm.k[slot];
             const auto* vs_ = sm.v[slot];
             // ---- S^T = K . Q^T: all eight K fragments are requested before the first product ------
-            f32x16 s_acc[2][QT];  // [kb][qt]
+            f32x16 s_acc[2];  // [kb]
             bf16x8 kf[2][4];
             if constexpr (KV8) {
                 u32x4 raw[2][2];
@@ -488,14 +471,10 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) s_acc[kb][qt][r] = 0.f;
+                for (int r = 0; r < 16; ++r) s_acc[kb][r] = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt)
-                        s_acc[kb][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][ks], qf[qt][ks], s_acc[kb][qt], 0, 0, 0);
+                    s_acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][ks], qf[ks], s_acc[kb], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
             if (early) __builtin_amdgcn_s_setprio(1);
@@ -528,43 +507,38 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                         }
             };
             // ---- mask (only tiles that cross some row's bound) ---------------------------------
-            if (j0 + kBN > kmin_blk[0]) {
+            if (j0 + kBN > kmin_wave) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int key = j0 + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
-                            if (key >= kmax_lane[qt]) s_acc[kb][qt][r] = -INFINITY;
-                        }
+                    for (int r = 0; r < 16; ++r) {
+                        const int key = j0 + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
+                        if (key >= kmax_lane) s_acc[kb][r] = -INFINITY;
+                    }
             }
             // ---- optimistic softmax, lane-local per query column -------------------------------
-            bf16x8 pf[2][2][QT];  // [kb][g][qt]
-            float l_tile[QT];
+            bf16x8 pf[2][2];  // [kb][g]
+            float l_tile;
             auto form_p = [&]() {  // P = exp2(s - m_used) in bf16; row sums by plain fp32 adds (the
                                    // packed dot instruction shares the matrix pipe and would stall MFMAs)
+                const float mc = EXACTQ ? m_used * c : m_used;
+                float l = 0.f, l2 = 0.f;
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt) {
-                    const float mc = EXACTQ ? m_used[qt] * c : m_used[qt];
-                    float l = 0.f, l2 = 0.f;
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
+                    for (int g = 0; g < 2; ++g)
 #pragma unroll
-                        for (int g = 0; g < 2; ++g)
-#pragma unroll
-                            for (int jj = 0; jj < 4; ++jj) {
-                                const float p0 = __builtin_amdgcn_exp2f(to_exponent(s_acc[kb][qt][8 * g + 2 * jj], mc));
-                                const float p1 = __builtin_amdgcn_exp2f(to_exponent(s_acc[kb][qt][8 * g + 2 * jj + 1], mc));
-                                const f32x2 pp = {p0, p1};
-                                const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
-                                l += p0;
-                                l2 += p1;
-                                pf[kb][g][qt][2 * jj] = pb[0];
-                                pf[kb][g][qt][2 * jj + 1] = pb[1];
-                            }
-                    l_tile[qt] = l + l2;
-                }
+                        for (int jj = 0; jj < 4; ++jj) {
+                            const float p0 = __builtin_amdgcn_exp2f(to_exponent(s_acc[kb][8 * g + 2 * jj], mc));
+                            const float p1 = __builtin_amdgcn_exp2f(to_exponent(s_acc[kb][8 * g + 2 * jj + 1], mc));
+                            const f32x2 pp = {p0, p1};
+                            const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
+                            l += p0;
+                            l2 += p1;
+                            pf[kb][g][2 * jj] = pb[0];
+                            pf[kb][g][2 * jj + 1] = pb[1];
+                        }
+                l_tile = l + l2;
             };
             bool bad = true;  // a workgroup's first tile has no reference yet: straight to the exact pass
             if (t != t_begin) {
@@ -574,37 +548,29 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b)
-#pragma unroll
-                        for (int e = 0; e < QT; ++e) asm volatile("" : "+v"(pf[a][b][e]));
-                bad = false;
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt) bad |= !(l_tile[qt] < kOptimisticLimit);
+                    for (int b = 0; b < 2; ++b) asm volatile("" : "+v"(pf[a][b]));
+                bad = !(l_tile < kOptimisticLimit);
             }
             // V^T fragments are requested once P is formed (earlier they would not fit the register
             // file next to the scores kept for the rare exact pass); the latency passes behind the
             // overflow test and the other wavefront of the SIMD.
             read_v_frags();
             if (__builtin_amdgcn_ballot_w64(bad) != 0) {  // exact path: this tile's max, rescale, redo
+                float a = fmaxf(s_acc[0][0], s_acc[1][0]);
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt) {
-                    float a = fmaxf(s_acc[0][qt][0], s_acc[1][qt][0]);
+                for (int r = 1; r < 16; ++r) a = fmaxf(fmaxf(a, s_acc[0][r]), s_acc[1][r]);
+                a = fmaxf(a, __shfl_xor(a, 32));
+                const float m_new = fmaxf(a, m_used);
+                const float alpha = __builtin_amdgcn_exp2f(EXACTQ ? (m_used - m_new) * c : m_used - m_new);
+                m_used = m_new;
+                l_sum *= alpha;
 #pragma unroll
-                    for (int r = 1; r < 16; ++r) a = fmaxf(fmaxf(a, s_acc[0][qt][r]), s_acc[1][qt][r]);
-                    a = fmaxf(a, __shfl_xor(a, 32));
-                    const float m_new = fmaxf(a, m_used[qt]);
-                    const float alpha = __builtin_amdgcn_exp2f(EXACTQ ? (m_used[qt] - m_new) * c : m_used[qt] - m_new);
-                    m_used[qt] = m_new;
-                    l_sum[qt] *= alpha;
+                for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o_acc[dt][qt][r] *= alpha;
-                }
+                    for (int r = 0; r < 16; ++r) o_acc[dt][r] *= alpha;
                 form_p();
             }
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) l_sum[qt] += l_tile[qt];
+            l_sum += l_tile;
             // ---- O^T += V^T . P^T -----------------------------------------------------------------
             __builtin_amdgcn_sched_barrier(0);
             if (early) __builtin_amdgcn_s_setprio(PRIO + 1);
@@ -615,9 +581,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                 for (int g = 0; g < 2; ++g)
 #pragma unroll
                     for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                        for (int qt = 0; qt < QT; ++qt)
-                            o_acc[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kb][g][dt], pf[kb][g][qt], o_acc[dt][qt], 0, 0, 0);
+                        o_acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kb][g][dt], pf[kb][g], o_acc[dt], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -656,14 +620,10 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-            for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o_acc[dt][qt][r] *= vs;
+            for (int r = 0; r < 16; ++r) o_acc[dt][r] *= vs;
     }
-    if constexpr (EXACTQ)
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) m_used[qt] *= c;
-    store_rows<QT>(p, wi, row, h, o_acc, l_sum, m_used);
+    if constexpr (EXACTQ) m_used *= c;
+    store_rows(p, wi, row, h, o_acc, l_sum, m_used);
 }
 
 template <bool KV8 = false, bool EXACTQ = false>
