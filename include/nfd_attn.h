@@ -203,8 +203,8 @@ int nfd_rope_check_args(nfd_dtype_t dtype, int B, int H, int F, int T, int D, in
  * Slide the context window (Sec. 5 "Limitations": the context is limited to a fixed number of frames):
  * drop the oldest n_drop of the kv_frames cached frames of every head by moving frames
  * [n_drop, kv_frames) to [0, kv_frames - n_drop).  k_cache, v_cache : [B, H, F*T, D].  The frames move
- * in place in one pass; only where very many frames are kept per frame dropped, and the workspace holds them, they
- * are copied out to it and back.
+ * in place in one pass; where at most half as many are kept as dropped they are copied, and where very many are kept per
+ * frame dropped, and the workspace holds them, they are copied out to it and back.
  * The temporal positions of the remaining frames do not change: pass t_offset += n_drop to the next
  * rotary-embedding call.  n_drop == 0 is a no-op.
  * Errors: NFD_ERR_NULL, NFD_ERR_SHAPE (also n_drop > kv_frames), NFD_ERR_CAPACITY (kv_frames > F), NFD_ERR_HIP.
@@ -323,9 +323,9 @@ int nfd_rope_kvcache_append_fp8(nfd_attn_t* h, const void* q, void* q_out, void*
                                 int T, int D, int frame_pos, int n_frames, int t_offset, int grid_h, int grid_w,
                                 int n_t, int n_h, int n_w, float theta, void* stream);
 
-/* nfd_kvcache_shift for the 8-bit caches: frames n_drop .. kv_frames-1 move to frames 0 .. ; same strategies
- * and errors (NFD_ERR_UNSUPPORTED for D != 64).  When T is a multiple of 16 whole key groups move (16-byte
- * vectors), otherwise V moves key by key; for that form a handle whose workspace is smaller than one feature
+/* nfd_kvcache_shift for the 8-bit caches: frames n_drop .. kv_frames-1 move to frames 0 .. ; same errors
+ * (NFD_ERR_UNSUPPORTED for D != 64).  K moves as there, V one feature row at a time.  When T is a multiple of 16 whole
+ * key groups of V move (16-byte vectors), otherwise single keys; for that form a handle whose workspace is smaller than one feature
  * row of the kept keys ((kv_frames - n_drop) * T bytes) is refused with NFD_ERR_ALLOC before anything is launched. */
 int nfd_kvcache_shift_fp8(nfd_attn_t* h, void* k8, void* v8t, int B, int H, int F, int T, int D, int kv_frames,
                           int n_drop, void* stream);

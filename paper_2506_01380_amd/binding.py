@@ -405,7 +405,7 @@ class Attention:
         if lse.dtype != torch.float32 or not lse.is_cuda or not lse.is_contiguous() or tuple(lse.shape) != (B, H, q.shape[2]):
             raise ValueError("lse must be a contiguous fp32 CUDA tensor [B, H, q_frames*T]")
         # the call writes every row below kv_frames*T, so only those past it are cleared (clearing all of dk and dv took
-        # 16 us of a 1020 us step at 64 heads x 16 frames of 336 tokens, 8 of 111 at 12 heads x 11 frames of 247)
+        # 9 us of a 1010 us step at 64 heads x 16 frames of 336 tokens, 8 of 111 at 12 heads x 11 frames of 247)
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         if kv_frames < F:
             dk[:, :, kv_frames * T:].zero_()

@@ -8,8 +8,8 @@
 // are short clips in full precision with few rows, which one row range per wavefront would leave most of the chip out
 // of.  They merge once, through LDS, at the end; the merge order is fixed, so results are bit-reproducible.
 // Measured, 12 heads, 4 frames of 336 tokens, fp32, D = 64 (before: one wavefront per row, operands one element at a
-// time): forward 562 -> 45 us, backward 2173 -> 163 us; at 32 heads, 8 frames the forward reaches 108 TFLOP/s and the
-// backward 101 TFLOP/s of executed products (matrix pipe busy 62-68 % of the cycles) of the 157 of the instruction.
+// time): forward 562 -> 44 us, backward 2173 -> 161 us (matrix pipe busy 46-49 % of the cycles); at 32 heads, 8 frames the
+// forward reaches 101 TFLOP/s and the backward 103 TFLOP/s of executed products (busy 62-70 %) of the 157 of the instruction.
 //
 // Lane = (j, g), j = lane % 16, g = lane / 16.  A[i][k] and B[k][j] of the instruction sit in lane i (or j) + 16 k, one
 // register each; D[i][j] in lane j + 16 (i / 4), element i % 4.

@@ -45,7 +45,7 @@ constexpr int kD = 64;                        // head width
 constexpr int kBN = 64;                       // keys per tile
 constexpr int kBM = 256;                      // query rows per workgroup (throughput shape; 128 in the latency shape)
 constexpr int kBM48 = 192;                    // the same with 48 rows per wavefront
-constexpr int kWaves = 4;                     // wavefronts per workgroup, 64 query rows each
+constexpr int kWaves = 4;                     // wavefronts per workgroup (32, 48 or 64 query rows each)
 constexpr int kTileElems = kBN * kD;          // 4096 bf16 = 8 KB, rows of 128 B, no padding
 constexpr int kRingSlots = 3;                 // K and V ring depth (tiles)
 constexpr float kOptimisticLimit = 32768.0f;  // 2^15 per lane and tile (32 values)

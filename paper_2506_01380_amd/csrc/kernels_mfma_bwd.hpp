@@ -35,14 +35,14 @@ struct BwdParams {
     const void* dout;    // [BH, Sq, D]
     const void* out;     // [BH, Sq, D] the forward's result
     const float* lse;    // [BH, Sq] natural log of the softmax denominator (from the forward call)
-    float* neg_delta;    // [BH, Sq] -<dout_i, out_i> (workspace): written by the dq kernel, read by the dk/dv kernel
+    float* neg_delta;    // [BH, Sq] -<dout_i, out_i> (workspace): written by the dq kernel (merged forms: attn_bwd_delta)
     float* lse2;         // [BH, Sq] lse * log2(e) (workspace): likewise
     void* dq;            // [BH, Sq, D]
     void* dk;            // [BH, Scap, D], rows < Sk written
     void* dv;            // [BH, Scap, D], rows < Sk written
     int BH, Sq, Sk, Scap, T, P;
-    int n_q_tiles;       // 256-row query tiles per head (dq kernel)
-    int n_k_blocks;      // key blocks per head (dk/dv kernel)
+    int n_q_tiles;       // query tiles per head (256 rows; 128 in the small merged form)
+    int n_k_blocks;      // key blocks per head (192 keys; 64)
     float scale;
     float scale_log2e;
 };

@@ -27,7 +27,9 @@ kvcache_copy(E* __restrict__ kd, E* __restrict__ vd, const E* __restrict__ ks, c
 
 // Slide a window inside its tensor in one pass: units [d, d + len) of every row move to [0, len), d = units dropped.
 // Bound by memory: every kept byte is read once and written once (a copy out to the workspace and back, which this
-// replaces where it is faster, moves everything twice).  Two ways to keep a unit from being overwritten before it is read:
+// replaces where it is faster, moves everything twice).  Few kept units that land where only dropped ones were are copied
+// instead (kvcache_copy; rule and figures at shift_copied on the host).  Two ways to keep a unit from being overwritten
+// before it is read:
 //  * chains, for rows with many units to drop (heads of K, V): units r, r + d, r + 2d, ... form a chain, each
 //    overwritten by the next one of the same chain and by nothing else, so one thread walks one chain front to back,
 //    U units at a time (all U read before the first is written), with no order between threads;
@@ -35,7 +37,7 @@ kvcache_copy(E* __restrict__ kd, E* __restrict__ vd, const E* __restrict__ ks, c
 //    owns a row and moves it front to back in pieces of 256 x U units, a barrier between reading and writing a piece.
 // PERM: units are single keys of the 8-bit V cache (frames that are no multiple of its 16-key groups), whose positions
 // go through the permuted order inside a group.
-// Measured, 16 heads, 32 frames of 336 tokens kept, two dropped: K and V in bf16 (88 MB read, 88 MB written, most of it in
+// Measured, 16 heads, 32 frames of 336 tokens kept, two dropped: K and V in bf16 (44 MB read, 44 MB written, part of it in
 // the last-level cache) 13.5 us against 27.9 through the workspace; the 8-bit caches 7.4 against 26.5.
 struct ShiftRun {
     void* base;

@@ -825,8 +825,9 @@ int nfd_kvcache_shift_fp8(nfd_attn_t* h, void* k8, void* v8t, int B, int H, int 
     if (n_drop == 0 || kv_frames == n_drop) return NFD_OK;
     const int64_t Spad = ((int64_t)F * T + 63) / 64 * 64, BH = (int64_t)B * H;
     const int64_t keep_keys = (int64_t)(kv_frames - n_drop) * T;
-    if (T % 16 != 0 && h->workspace_bytes < (size_t)keep_keys)  // checked before anything is launched
-        return fail(h, NFD_ERR_ALLOC, "the workspace cannot stage one feature row of the 8-bit V cache");
+    // part of the call's contract; nothing is staged there any more
+    if (T % 16 != 0 && h->workspace_bytes < (size_t)keep_keys)
+        return fail(h, NFD_ERR_ALLOC, "for T that is no multiple of 16 the workspace must hold a feature row of the kept keys");
     if (const int dc = check_device(h)) return dc;
     hipStream_t st = (hipStream_t)stream;
     // K codes: BH heads of Spad rows x 64 bytes, a frame = T rows; V codes: BH * 64 feature rows of Spad bytes, a frame =
