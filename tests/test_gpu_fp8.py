@@ -181,12 +181,12 @@ def test_custom_scale_and_plan_shapes(attn):
 
 
 @pytest.mark.parametrize("B,H,T,F,kvf,drop,ws", [
-    (1, 2, 16, 6, 6, 4, 0),      # keep <= drop: one disjoint copy; 16-byte vectors
-    (2, 3, 48, 8, 7, 2, 0),      # overlapping: through the workspace
-    (1, 2, 5, 9, 9, 2, 0),       # T not a multiple of 16: V moves key by key through the workspace
-    (1, 2, 5, 9, 9, 2, 4096),    # ... in two batches of feature rows (117 + 11)
+    (1, 2, 16, 6, 6, 4, 0),      # half as many kept as dropped: copied; 16-byte vectors
+    (2, 3, 48, 8, 7, 2, 0),      # overlapping: in place
+    (1, 2, 5, 9, 9, 2, 0),       # T not a multiple of 16: V moves key by key
+    (1, 2, 5, 9, 9, 2, 4096),    # ... with a small workspace
     (1, 3, 37, 6, 5, 1, 0),
-    (1, 2, 48, 8, 8, 3, 4096),   # a workspace too small for staging: runs of n_drop frames
+    (1, 2, 48, 8, 8, 3, 4096),   # whole key groups with a small workspace
     (1, 1, 7, 5, 4, 4, 0),       # everything dropped: nothing moves
 ])
 def test_shift_of_the_8bit_cache(B, H, T, F, kvf, drop, ws):

@@ -24,10 +24,10 @@ def _host(t):
 
 
 @pytest.mark.parametrize("workspace,kv,drop", [
-    (0, 7, 5),          # kept frames fit in the dropped range: one disjoint copy
-    (0, 7, 2),          # overlapping: through the workspace
-    (4096, 7, 2),       # workspace too small: runs of n_drop frames
-    (4096, 6, 1),       # ... one frame at a time
+    (0, 7, 5),          # two kept, five dropped: one disjoint copy
+    (0, 7, 2),          # overlapping: in place
+    (4096, 7, 2),       # ... with a small workspace
+    (4096, 6, 1),       # ... longest chains
     (0, 5, 0), (0, 5, 5),  # nothing to do
 ])
 def test_kvcache_shift_bit_exact(workspace, kv, drop):
