@@ -338,8 +338,10 @@ int nfd_block_causal_attn_fwd_fp8kv(nfd_attn_t* h, const void* q, const void* k8
 
 /* Which (head, query tile, key split) workgroup `block` of the matrix-core forward launch works on: the
  * same function the kernel evaluates, exposed so that the schedule can be checked without a GPU (every item
- * exactly once over blocks 0 .. n_workgroups-1).  group_q_tiles: the ordering used when K/V exceed the
- * last-level cache.  Errors: NFD_ERR_NULL, NFD_ERR_SHAPE (also a block past the launch). */
+ * exactly once over blocks 0 .. n_workgroups-1).  group_q_tiles: the order.  0: heaviest query tiles first, heads in
+ * groups of eight (key-split launches); 1: the query tiles of a head and split together (key-split launches whose K/V exceed
+ * the last-level cache); n > 1: heads in groups of n, a remainder of less than three quarters of n joins the last (launches
+ * without key splits: 8 when B.H is a multiple of 8, otherwise 64).  Errors: NFD_ERR_NULL, NFD_ERR_SHAPE (also a block past the launch). */
 int nfd_attn_work_item(int BH, int n_q_tiles, int n_splits, int group_q_tiles, unsigned block, int* bh, int* q_tile,
                        int* split);
 

@@ -127,15 +127,23 @@ __device__ __forceinline__ bf16x8 widen_e4m3x8(uint32_t w0, uint32_t w1) {
 // tiles and key splits of a head share one L2; otherwise pinning would leave XCDs unevenly loaded
 // (or idle), and the items are dealt out plainly, consecutive ids going to consecutive heads.
 // Order of the items of an XCD (or of the launch):
-//  * by default the heaviest query tiles (latest frames) come first, heads fastest, so the tail
-//    of the launch is made of the lightest tiles; with more than kHeadGroup heads in the stream they go in
-//    groups of that many, one group after the other: the workgroups resident together then belong to few
-//    heads and share their K/V tiles in L2 (256 heads x 21 tiles: 917 -> 1017 TFLOP/s), while a group
-//    is still large enough to end on light tiles;
-//  * group_q_tiles (key-split launches whose K/V exceed the last-level cache): the query tiles of
+//  * the heaviest query tiles (latest frames) come first, heads fastest, so the tail of the launch is made of the
+//    lightest tiles; the heads go in groups, one group after the other: the workgroups resident together then belong
+//    to few heads and share their K/V tiles in L2 (256 heads x 21 tiles: 917 -> 1017 TFLOP/s against one group), while
+//    a group is still large enough to end on light tiles.  Launches without key splits: head_group() heads a group,
+//    group_q_tiles = that number; a remainder of less than three quarters of a group joins the last one, whose heavy
+//    tiles would otherwise start when the others end (forward of 16 frames of 336 tokens, one heads' remainder as a
+//    group of its own / joined: 72 heads 302 / 259 us, 136 heads 527 / 500).  Eight heads per XCD are a group; a
+//    stream that is not pinned runs over all XCDs, so 64 are (groups of 8 / of 64: 36 heads 174 / 142 us, 60 heads
+//    261 / 225, 108 heads of 28 frames of 72 tokens 96 / 77; groups of 32 are within 10 % of 64 either way).  Heads
+//    dealt in contiguous ranges to the XCDs there instead: 171 us at 36 heads, the heavy tiles no longer come first;
+//  * group_q_tiles = 0 (key-split launches, whose workgroups are mostly resident at once): groups of kHeadGroup heads
+//    per stream, a remainder is a group;
+//  * group_q_tiles = 1 (key-split launches whose K/V exceed the last-level cache): the query tiles of
 //    one (head, split) are consecutive instead, so they are resident together and their common
 //    K/V range is fetched from HBM once and found in L2 by the others.
 constexpr int kHeadGroup = 8;
+__host__ __forceinline__ int head_group(int BH) { return (BH & 7) == 0 ? kHeadGroup : 8 * kHeadGroup; }
 
 // The 32-row blocks of a head are dealt to its query tiles as evenly as they go: tile i owns blocks_lo blocks, the
 // first n_hi tiles one more, so no tile is mostly padding.  (blocks_lo = n_blocks / n_q_tiles, n_hi = n_blocks mod
@@ -159,11 +167,13 @@ __host__ __device__ __forceinline__ WorkItem work_item_of(unsigned block, int BH
     const int hh = pinned ? BH >> 3 : BH;  // heads this id stream runs over
     w.valid = j < hh * per_head;
     int head_local;
-    if (!group_q_tiles) {
-        // heads in groups of kHeadGroup: all items of a group before the next group's
-        const int per_group = kHeadGroup * per_head;
-        const int g0 = j / per_group * kHeadGroup, jj = j % per_group;
-        const int gh = max(1, min(kHeadGroup, hh - g0));  // heads of this group (the last one may be smaller; an id past the launch: 1)
+    if (group_q_tiles == 0 || group_q_tiles > 1) {
+        // all items of a group before the next group's
+        const int G = min(group_q_tiles ? group_q_tiles : kHeadGroup, hh);
+        const int n_groups = group_q_tiles ? max(1, (hh + G / 4) / G) : (hh + G - 1) / G;
+        const int group = min(j / (G * per_head), n_groups - 1);
+        const int g0 = group * G, jj = j - g0 * per_head;
+        const int gh = group == n_groups - 1 ? hh - g0 : G;  // heads of this group
         const int item = jj / gh;
         head_local = g0 + jj % gh;
         w.q_tile = n_q_tiles - 1 - item / n_splits;

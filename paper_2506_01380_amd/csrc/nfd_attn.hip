@@ -434,7 +434,8 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
     }
     p.n_splits = pl.n_splits;
     // K and V of all heads against the 256 MB last-level cache (with room for Q, O and partials)
-    p.group_q_tiles = pl.n_splits > 1 && (double)p.BH * p.Sk * nfd::mfma::kD * 2.0 * (kv8 ? 1.0 : 2.0) > 192e6;
+    p.group_q_tiles = pl.n_splits > 1 ? (double)p.BH * p.Sk * nfd::mfma::kD * 2.0 * (kv8 ? 1.0 : 2.0) > 192e6
+                                      : nfd::mfma::head_group(p.BH);
     p.scale_log2e = scale * nfd::kLog2e;
     p.Snew0 = 0x7fffffff;
     if (append) {

@@ -43,7 +43,7 @@ struct FwdParams {
     int blocks_lo;      // 32-row blocks per query tile; the first n_hi tiles own one more
     int n_hi;
     int n_splits;       // key splits per query tile
-    int group_q_tiles;  // split launches: 1 = query tiles of one (head, split) get adjacent workgroup ids
+    int group_q_tiles;  // order of the work items, see work_item_of: 0, 1 or the heads of a group
     float scale_log2e;  // softmax scale * log2(e)
     // 8-bit cache only (k: [BH, Spad, D] E4M3 codes, v: [BH, D, Spad] codes, value = code * scale[bh]):
     const float* k_scale;  // [BH]

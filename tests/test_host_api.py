@@ -140,6 +140,29 @@ def test_every_work_item_is_dealt_exactly_once(BH, nq, ns, group):
             assert groups == sorted(groups)
 
 
+@pytest.mark.parametrize("BH", [1, 7, 8, 12, 63, 65, 79, 111, 113, 130, 72, 104, 112, 120, 136, 256])
+@pytest.mark.parametrize("nq", [1, 6, 21])
+def test_work_items_without_key_splits_in_large_head_groups(BH, nq):
+    """The order of launches without key splits: a bijection, heads pinned where they can be, and in every id stream groups of
+    heads whose query tiles come heaviest first; a remainder of less than three quarters of a group belongs to the last."""
+    pinned = BH % 8 == 0
+    G = 8 if pinned else 64
+    items = [nb.nfd_attn_work_item(BH, nq, 1, G, b) for b in range(BH * nq)]
+    assert len(set(items)) == BH * nq and all(0 <= h < BH and 0 <= q < nq and s == 0 for h, q, s in items)
+    assert nb.nfd_attn_work_item(BH, nq, 1, G, BH * nq) is None
+    if pinned:
+        assert all(b % 8 == h % 8 for b, (h, _, _) in enumerate(items))
+    hh = BH // 8 if pinned else BH
+    n_groups = max(1, (hh + G // 4) // G)
+    for x in range(8 if pinned else 1):
+        stream = [(h // 8 if pinned else h, q) for h, q, _ in (items[x::8] if pinned else items)]
+        group = [min(h // G, n_groups - 1) for h, _ in stream]
+        assert group == sorted(group)
+        for n in range(n_groups):
+            tiles = [q for (_, q), k in zip(stream, group) if k == n]
+            assert tiles == sorted(tiles, reverse=True)
+
+
 def test_fp8_cache_bytes_rounds_the_key_count_to_whole_tiles():
     assert nb.nfd_fp8_cache_bytes(1, 16, 40, 336, 64) == 16 * 13440 * 64          # 40 * 336 = 210 tiles exactly
     assert nb.nfd_fp8_cache_bytes(2, 3, 5, 7, 64) == 2 * 3 * 64 * 64              # 35 keys -> one tile
