@@ -271,13 +271,13 @@ int nfd_attn_check_args(nfd_dtype_t dtype, int B, int H, int F, int T, int D, in
  * future frames IS the ~50 % saving the paper states). */
 typedef struct nfd_attn_plan {
     int kernel;          /* 0 = general (fp32 / any D), 1 = bf16 matrix-core D=64 */
-    int block_m;         /* query rows per workgroup, at most: the 32-row blocks of a head are dealt evenly to its
+    int block_m;         /* query rows per tile, at most: the 32-row blocks of a head are dealt evenly to its
                             n_q_tiles tiles (tile i owns floor(blocks / n_q_tiles) blocks, the first blocks mod n_q_tiles
                             tiles one more) */
     int block_n;         /* keys per inner tile */
     int n_q_tiles;       /* query tiles per (b, h) */
     int n_splits;        /* key splits per query tile (1 = no combine pass) */
-    int n_workgroups;    /* total workgroups of the main launch */
+    int n_workgroups;    /* total workgroups of the main launch, one per tile and split (nfd_attn_fwd_ranges: more and smaller ones) */
     int64_t key_tiles_visited; /* sum over workgroups of key tiles actually visited */
     int64_t key_tiles_dense;   /* the same count if no future tile were skipped */
     size_t workspace_bytes;    /* scratch the split launch needs (0 if n_splits == 1) */
@@ -286,6 +286,13 @@ typedef struct nfd_attn_plan {
 /* num_cus <= 0 selects 256; workspace_limit == 0 selects the default workspace. */
 int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames,
                   int q_frames, int num_cus, size_t workspace_limit, nfd_attn_plan_t* plan);
+
+/* How many workgroups a matrix-core forward launch puts on a head's rows (times n_splits), with the default workspace; fp8kv != 0: over
+ * the 8-bit cache.  The 32-row blocks of the rows are dealt to `ranges` workgroups as the plan's are to its tiles.  It is the
+ * plan's n_q_tiles, or more where 256-row tiles would leave the chip idle: then ranges of at most four blocks.  0 for
+ * the general kernels.  Host only.  Errors: NFD_ERR_NULL, then those of nfd_attn_check_args. */
+int nfd_attn_fwd_ranges(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames, int num_cus, int fp8kv,
+                        int* ranges, int* n_splits);
 
 /*
  * 8-bit KV cache.  Appendix B's cache held as OCP E4M3 codes (1 sign, 4 exponent, 3 mantissa bits, bias 7,
@@ -337,8 +344,8 @@ int nfd_block_causal_attn_fwd_fp8kv(nfd_attn_t* h, const void* q, const void* k8
                                     int T, int D, int kv_frames, int q_frames, float scale, void* stream);
 
 /* Which (head, query tile, key split) workgroup `block` of the matrix-core forward launch works on: the
- * same function the kernel evaluates, exposed so that the schedule can be checked without a GPU (every item
- * exactly once over blocks 0 .. n_workgroups-1).  group_q_tiles: the order.  0: heaviest query tiles first, heads in
+ * same function the kernel evaluates (n_q_tiles there: nfd_attn_fwd_ranges), exposed so that the schedule can be checked
+ * without a GPU (every item exactly once over blocks 0 .. n_workgroups-1).  group_q_tiles: the order.  0: heaviest query tiles first, heads in
  * groups of eight (key-split launches); 1: the query tiles of a head and split together (key-split launches whose K/V exceed
  * the last-level cache); n > 1: heads in groups of n, a remainder of less than three quarters of n joins the last (launches
  * without key splits: 8 when B.H is a multiple of 8, otherwise 64).  Errors: NFD_ERR_NULL, NFD_ERR_SHAPE (also a block past the launch). */

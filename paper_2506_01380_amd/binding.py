@@ -29,7 +29,7 @@ EXPORTS = (
     "nfd_block_causal_attn_fwd_lse", "nfd_block_causal_attn_bwd",
     "nfd_kvcache_shift", "nfd_spec_init", "nfd_spec_next", "nfd_spec_accept", "nfd_attn_work_item",
     "nfd_block_causal_attn_fwd_noalloc", "nfd_kvcache_append_attn_fwd",
-    "nfd_attn_q_tile_rows", "nfd_attn_bwd_form",
+    "nfd_attn_q_tile_rows", "nfd_attn_bwd_form", "nfd_attn_fwd_ranges",
     "nfd_fp8_cache_bytes", "nfd_kvcache_append_fp8", "nfd_block_causal_attn_fwd_fp8kv", "nfd_kvcache_shift_fp8", "nfd_rope_kvcache_append_fp8",
 )
 
@@ -118,6 +118,8 @@ def lib():
         L.nfd_attn_q_tile_rows.restype = ci
         L.nfd_attn_bwd_form.argtypes = [ci] * 9 + [ctypes.POINTER(ci)]
         L.nfd_attn_bwd_form.restype = ci
+        L.nfd_attn_fwd_ranges.argtypes = [ci] * 10 + [ctypes.POINTER(ci)] * 2
+        L.nfd_attn_fwd_ranges.restype = ci
         L.nfd_fp8_cache_bytes.argtypes = [ci] * 5 + [ctypes.POINTER(ctypes.c_size_t)]
         L.nfd_fp8_cache_bytes.restype = ci
         L.nfd_kvcache_append_fp8.argtypes = [vp] * 7 + [ci] * 7 + [vp]
@@ -310,6 +312,14 @@ def nfd_attn_bwd_form(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus=0):
     form = ctypes.c_int()
     _check(lib().nfd_attn_bwd_form(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus, ctypes.byref(form)), "nfd_attn_bwd_form")
     return form.value
+
+
+def nfd_attn_fwd_ranges(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus=0, fp8kv=False):
+    """(row ranges per head, key splits) of the matrix-core forward launch: a workgroup each."""
+    r, s = ctypes.c_int(), ctypes.c_int()
+    _check(lib().nfd_attn_fwd_ranges(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus, int(fp8kv), ctypes.byref(r), ctypes.byref(s)),
+           "nfd_attn_fwd_ranges")
+    return r.value, s.value
 
 
 def nfd_attn_q_tile_rows(rows, n_q_tiles, q_tile):

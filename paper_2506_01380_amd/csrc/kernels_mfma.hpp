@@ -1,13 +1,13 @@
-// bf16 matrix-core forward kernels for head width 64 (gfx950 / CDNA4): what all shapes share, and the shapes built
-// on the 32x32x16 matrix instruction - the 128-row latency shape, over a bf16 and over the 8-bit cache.  The 256-row
-// throughput shape is in kernels_mfma16.hpp (same structure, 16x16x32 instruction).
+// Matrix-core forward kernels for head width 64 (gfx950 / CDNA4): what all shapes share, and the one shape on the
+// 32x32x16 matrix instruction, 32 rows per wavefront over the 8-bit cache.  All others are in kernels_mfma16.hpp (same
+// structure, 16x16x32 instruction).
 //
-// Flash-style online softmax.  A workgroup of 4 wavefronts owns up to 128 consecutive query rows of
-// one (batch, head) - the 32-row blocks of a head are dealt evenly to its query tiles -; each wavefront
-// owns one 32-wide column block of the TRANSPOSED score matrix (two in the 256-row shape):
+// Flash-style online softmax.  A workgroup of 4 wavefronts owns up to 128, 192 or 256 consecutive query rows of
+// one (batch, head) - the 32-row blocks of a head are dealt evenly to its workgroups -; each wavefront of the shape here
+// owns one 32-wide column block of the TRANSPOSED score matrix:
 //
 //   S^T[key, query] = K_tile[key, :] . Q^T[:, query]       v_mfma_f32_32x32x16_bf16, A = K (LDS), B = Q^T (registers)
-//   O^T[d,   query] += V_tile^T[d, key] . P^T[key, query]  A = V^T (LDS, transposing read), B = P^T (registers)
+//   O^T[d,   query] += V_tile^T[d, key] . P^T[key, query]  A = V^T (LDS), B = P^T (registers)
 //
 // In the 32x32 accumulator layout a lane holds ONE query column (lane % 32) and 16 of the
 // 32 key rows, so row max / row sum are register-local plus a single exchange with
@@ -17,7 +17,7 @@
 // K and V tiles (64 keys) never pass through registers either: every wavefront issues 16-byte
 // global loads that land straight in LDS (one wave instruction = 1 KB = eight 128-byte tile
 // rows), two tiles ahead of their use, into a ring of three tile slots (three ahead, four slots in the
-// pipelined 256-row shape), with one bare barrier per tile.  A wave's 1 KB is contiguous in LDS, so rows
+// pipelined shapes), with one bare barrier per tile.  A wave's 1 KB is contiguous in LDS, so rows
 // cannot be padded; bank conflicts are avoided with an XOR swizzle instead: the 16-byte chunk c of tile row r is stored at chunk
 // position c ^ f(r).  The swizzle costs nothing on the way in (each lane simply fetches the
 // chunk that belongs at its position) and one precomputed per-lane offset on the way out.
@@ -26,7 +26,7 @@
 // looking at this tile's max; only if a lane's tile sum reaches kOptimisticLimit (which also
 // catches inf, i.e. the first tile of a row) the tile is redone with its exact max and the
 // accumulators are rescaled.  The softmax scale lives in the query fragments (rounded to bf16), so the
-// score accumulators hold base-2 exponents.  The forward of the training pair (EXACTQ) keeps the
+// score accumulators hold base-2 exponents.  The forward of the training pair (EXACTQ in kernels_mfma16.hpp) keeps the
 // queries as given and scales the fp32 scores instead.
 //
 // Mask (Sec. 3.1): row i sees keys j < kmax(i) = (P + i/T + 1) * T.  Key tiles entirely
@@ -43,7 +43,7 @@ namespace mfma {
 
 constexpr int kD = 64;                        // head width
 constexpr int kBN = 64;                       // keys per tile
-constexpr int kBM = 256;                      // query rows per workgroup (throughput shape; 128 in the latency shape)
+constexpr int kBM = 256;                      // query rows per workgroup (half of it in the shapes with short chains)
 constexpr int kBM48 = 192;                    // the same with 48 rows per wavefront
 constexpr int kWaves = 4;                     // wavefronts per workgroup (32, 48 or 64 query rows each)
 constexpr int kTileElems = kBN * kD;          // 4096 bf16 = 8 KB, rows of 128 B, no padding
@@ -77,8 +77,8 @@ struct __attribute__((aligned(16))) SmemRing {
     __bf16 k[kRingSlots][kTileElems];
     __bf16 v[kRingSlots][kTileElems];
 };
-// The pipelined 256-row shape (kernels_mfma16.hpp) keeps the V tile of the previous key tile alive while it works on
-// the K tile of the next one, so its ring is one slot deeper for the same prefetch distance (64 KB, two workgroups
+// The pipelined shapes (kernels_mfma16.hpp) keep the V tile of the previous key tile alive while they work on
+// the K tile of the next one, so their ring is one slot deeper for the same prefetch distance (64 KB, two workgroups
 // per CU).
 constexpr int kPipeSlots = 4;
 struct __attribute__((aligned(16))) SmemRingPipe {
@@ -235,20 +235,15 @@ __device__ __forceinline__ void store_rows(const FwdParams& p, const WorkItem& w
     }
 }
 
-// The 128-row shape: 32 rows per wavefront, three wavefronts per SIMD: half the softmax and half the matrix work per
-// tile and wavefront of the 256-row shape, i.e. a shorter chain per key tile, for calls with few query rows whose
-// time is the length of that chain (cached forms); it reads twice the LDS bytes per FLOP.
+// Key-split launches with at most 128 rows per workgroup: 32 rows per wavefront, three wavefronts per SIMD, a small kernel that
+// starts quickly.  Short chains, or workgroups with rows for two or three of their wavefronts, are faster here than on the
+// pipelined shape (rule and figures at the launch's plan).
 //
 // KV8: K and V come from the 8-bit cache and are widened to bf16 (exact) before they reach the matrix operands, by
 // every wavefront on the way of its own fragments out of LDS (SmemRing8); the feature order inside the first
 // product's contraction is then permuted (a 16-byte read serves two steps), the same way for K and Q.  The per-head
 // scales are folded into the softmax scale (K) and the final write (V), so the arithmetic between the operands is the
 // same as for a bf16 cache.
-//
-// EXACTQ: the forward of the training pair, which also writes the log-sum-exp the backward normalises with.  The
-// queries enter the first product as given, the scores are exact sums of products of the inputs, and the softmax
-// scale is applied to the fp32 scores (one multiply per score); the reference max is then kept in raw score units.
-// Without it the scale is folded into the query fragments (one more bf16 rounding of an input, no multiply).
 template <bool KV8>
 struct SmemOf {
     typedef typename std::conditional<KV8, SmemRing8, SmemRing>::type type;
@@ -256,7 +251,7 @@ struct SmemOf {
 
 // One work item (head, query tile, key split) from the first load to the final write.  Every wavefront of the
 // workgroup passes the same barriers and returns; the LDS ring may be reused after a workgroup barrier.
-template <bool KV8, bool EXACTQ>
+template <bool KV8>
 __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem& wi, typename SmemOf<KV8>::type& sm) {
     constexpr int PRIO = kMfmaPriority;
 
@@ -321,12 +316,8 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
         // the 16-byte chunk 2*(ks/2) + h, first or second half (ks % 2) - the order the K reads deliver
         const int d0 = KV8 ? 16 * (2 * (ks >> 1) + h) + 8 * (ks & 1) : 16 * ks + 8 * h;
         const bf16x8 raw = *(const bf16x8*)(qg + (int64_t)rc * kD + d0);
-        if constexpr (EXACTQ) {
-            qf[ks] = raw;
-        } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)raw[e] * c);
-        }
+        for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)raw[e] * c);
     }
     const bool wave_active = wave < n_blk;
 
@@ -335,8 +326,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o_acc[a][r] = 0.f;
-    float m_used = kNegBig;  // reference max (stale by design), in the units of the score accumulators: base-2 exponents,
-                             // or raw scores (exponent = c * score) with EXACTQ
+    float m_used = kNegBig;  // reference max (stale by design), in the units of the score accumulators: base-2 exponents
     float l_sum = 0.f;       // this lane's share of the row sum
 
     // ---- tile loads: one wave instruction fills 8 consecutive tile rows (1 KB); a wavefront owns
@@ -435,11 +425,6 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
         }
     }
 
-    // base-2 exponent of one score against a reference already in exponent units
-    auto to_exponent = [&](float s, float ref_exponent) {
-        if constexpr (EXACTQ) return __builtin_fmaf(s, c, -ref_exponent);
-        else return s - ref_exponent;
-    };
     auto tile_body = [&](int t, int slot) {
         const int j0 = t * kBN;
         {
@@ -531,7 +516,6 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
             float l_tile;
             auto form_p = [&]() {  // P = exp2(s - m_used) in bf16; row sums by plain fp32 adds (the
                                    // packed dot instruction shares the matrix pipe and would stall MFMAs)
-                const float mc = EXACTQ ? m_used * c : m_used;
                 float l = 0.f, l2 = 0.f;
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
@@ -539,8 +523,8 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                     for (int g = 0; g < 2; ++g)
 #pragma unroll
                         for (int jj = 0; jj < 4; ++jj) {
-                            const float p0 = __builtin_amdgcn_exp2f(to_exponent(s_acc[kb][8 * g + 2 * jj], mc));
-                            const float p1 = __builtin_amdgcn_exp2f(to_exponent(s_acc[kb][8 * g + 2 * jj + 1], mc));
+                            const float p0 = __builtin_amdgcn_exp2f(s_acc[kb][8 * g + 2 * jj] - m_used);
+                            const float p1 = __builtin_amdgcn_exp2f(s_acc[kb][8 * g + 2 * jj + 1] - m_used);
                             const f32x2 pp = {p0, p1};
                             const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
                             l += p0;
@@ -571,7 +555,7 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
                 for (int r = 1; r < 16; ++r) a = fmaxf(fmaxf(a, s_acc[0][r]), s_acc[1][r]);
                 a = fmaxf(a, __shfl_xor(a, 32));
                 const float m_new = fmaxf(a, m_used);
-                const float alpha = __builtin_amdgcn_exp2f(EXACTQ ? (m_used - m_new) * c : m_used - m_new);
+                const float alpha = __builtin_amdgcn_exp2f(m_used - m_new);
                 m_used = m_new;
                 l_sum *= alpha;
 #pragma unroll
@@ -632,17 +616,16 @@ __device__ __forceinline__ void attn_fwd_item(const FwdParams& p, const WorkItem
 #pragma unroll
             for (int r = 0; r < 16; ++r) o_acc[dt][r] *= vs;
     }
-    if constexpr (EXACTQ) m_used *= c;
     store_rows(p, wi, row, h, o_acc, l_sum, m_used);
 }
 
-template <bool KV8 = false, bool EXACTQ = false>
+template <bool KV8>
 __global__ void __launch_bounds__(kWaves * 64, 3)
 attn_fwd_bf16_d64(FwdParams p) {
     __shared__ typename SmemOf<KV8>::type sm;
     const WorkItem wi = decode_work(p);
     if (!wi.valid) return;  // whole workgroup leaves together
-    attn_fwd_item<KV8, EXACTQ>(p, wi, sm);
+    attn_fwd_item<KV8>(p, wi, sm);
 }
 
 // Merge the key-split partials of one query row: out = sum_s w_s O_s / sum_s w_s l_s with

@@ -1,7 +1,6 @@
-// The 256-row throughput shape of the forward kernel (64 query rows per wavefront), on the 16x16x32 shape of the bf16
-// matrix instruction.
+// The forward kernel on the 16x16x32 shape of the bf16 matrix instruction: 64, 48 or 32 query rows per wavefront.
 //
-// Same decomposition, tile ring, swizzle, mask handling and optimistic softmax as the shapes in kernels_mfma.hpp (read
+// Same decomposition, tile ring, swizzle, mask handling and optimistic softmax as the shape in kernels_mfma.hpp (read
 // its header first); what differs is the register layout, a software-pipelined tile loop, and row sums formed on
 // the matrix pipe.  v_mfma_f32_16x16x32_bf16: A[i][k] sits in lane i + 16 (k / 8), element k % 8;
 // B[k][j] in lane j + 16 (k / 8), element k % 8; D[i][j] in lane j + 16 (i / 4), element i % 4.  With lane = (j, g),
@@ -66,6 +65,12 @@ __device__ __forceinline__ void acc_mfma(f32x16& v, const bf16x8& a, const bf16x
 // NCQ: 16-query column blocks per wavefront.  4: 64 rows, the 32-row blocks `wave` and `wave + 4` of the workgroup's eight.
 // 3: 48 rows, the 32-row block `wave` and the 16-row block `wave` behind the first 128 rows: a workgroup of 192, for tiles of
 // six 32-row blocks (the rule and its figures are at the launch).  222 VGPRs, no spills.
+// 2: 32 rows, the block `wave`: a workgroup of 128, for launches as long as their longest chain of tiles.  Bound there by
+// the latency of one wavefront's stream of instructions: a tile takes 0.68 us with a CU to itself, 0.84 in the form on the
+// 32x32x16 instruction without a pipeline that it replaces (64 rows: 1.1); 1.1 with two workgroups per CU.  Fragments are read a
+// step ahead (in the step itself: 0.74 us), the slow path is laid out of line (0.71 us with it, 0.72 without), one vector
+// instruction per matrix instruction (two 0.71, three 0.73).  16 heads, one frame of 336 over 32: 30.7 -> 29.0 us; 12 heads, 11
+// frames of 247: 41 -> 33; 32 heads, 8 frames of 171: 25 -> 22.
 template <bool EXACTQ, bool KV8, int NCQ>
 __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkItem& wi, typename SmemPipeOf<KV8>::type& sm) {
     static_assert(!(EXACTQ && KV8), "training does not run over the 8-bit cache");
@@ -132,6 +137,10 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
             b0_blk[qt] = dead ? 0x40000000 : b0;
             kmin_blk[qt] = dead ? 0 : kmax_of_row(min(b0, p.Sq - 1), p.T, p.P);
             kmax_blk[qt] = dead ? 0 : kmax_of_row(min(b0 + 31, p.Sq - 1), p.T, p.P);
+        } else if constexpr (NCQ == 2) {
+            b0_blk[qt] = r0 + 32 * wave;
+            kmin_blk[qt] = kmax_of_row(min(b0_blk[qt], p.Sq - 1), p.T, p.P);
+            kmax_blk[qt] = kmax_of_row(min(b0_blk[qt] + 31, p.Sq - 1), p.T, p.P);
         } else {
             // a workgroup without this wavefront's second block: a duplicate of the last row, never stored, that runs
             // along with the first block (same bounds; the wavefront would wait at the barriers instead)
@@ -471,9 +480,6 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     // t+1 have landed and it no longer reads tile t-1; after Bar(t) tile t+1 is visible to all and every wavefront
     // requests tile t+3 into the slot of tile t-1.  The pipelined loop passes Bar(t) after its first step of tile t
     // (which still reads V of tile t-1), tile_body's loop at the top of tile t.
-    const int t_mid = wave_active ? max(t_begin, min(t_end, (kmax_blk[0] + kBN - 1) / kBN)) : t_begin;
-    int t_pipe = wave_active ? max(t_begin, min(t_mid, kmin_blk[0] / kBN)) : t_begin;
-    if (t_pipe - t_begin < 2) t_pipe = t_begin;
     // 8-bit cache: the bf16 ring has three slots, filled by widening.  After Bar(t) a wavefront widens its rows of tile t+2
     // into the slot of tile t-1 (Bar(t+1) makes them visible) and requests the codes of tile t+5 into the slot it read.
     auto bar = [&](int t, auto load_slot) {  // load_slot: the ring slot of tile t - 1 (an int or a compile-time constant)
@@ -515,6 +521,212 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     };
     __builtin_amdgcn_s_barrier();
 
+    // One row block per wavefront: units alternate between the two halves kb of a tile, u = 2 t + kb, and step u issues
+    // PV(u-1), QK(u+1) and SM(u).  They now share the block, hence its reference: where SM(u) moves it, the scores of
+    // u+1, formed against the old one, are moved too.  All tiles the wavefront sees run here; a unit that crosses a bound
+    // is masked before its softmax.
+    auto pipe_one_block = [&]() __attribute__((always_inline)) {
+        const int t_vis = wave_active ? max(t_begin, min(t_end, (kmax_blk[0] + kBN - 1) / kBN)) : t_begin;
+        f32x4 S[2][2][2];   // [kb][rb][cb]
+        f32x4 minit[2];
+        bf16x8 P[2][2];     // [kb][cb]
+        bf16x8 kf[2][2][2]; // [kb][rb][ks]
+        bf16x8 vf[2][4];    // [kb][fb]
+        int kmax_lane[2];
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            kmax_lane[cb] = kmax_lane_of(cb);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) minit[cb][e] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) P[1][cb][e] = (__bf16)0.f;
+        }
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vf[1][fb][e] = (__bf16)0.f;  // the first step's PV adds 0 . 0
+        auto read_k = [&](int slot, int kb) {
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) kf[kb][rb][ks] = lds_read_b128(sm.k[slot] + (32 * kb + 16 * rb) * kD + k_off[ks]);
+        };
+        auto read_v = [&](int slot, int kb) {
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb) vf[kb][fb] = read_v_frag(sm.v[slot], kb, fb);
+        };
+        auto qk = [&](int kb) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+                        S[kb][rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][rb][ks], qf[cb][ks], ks ? S[kb][rb][cb] : minit[cb], 0, 0, 0);
+        };
+        auto pv = [&](int kb) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                acc_mfma<0>(o_acc[cb], vf[kb][0], P[kb][cb]);
+                acc_mfma<1>(o_acc[cb], vf[kb][1], P[kb][cb]);
+                acc_mfma<2>(o_acc[cb], vf[kb][2], P[kb][cb]);
+                acc_mfma<3>(o_acc[cb], vf[kb][3], P[kb][cb]);
+            }
+        };
+        auto sums = [&](int kb) {
+            if constexpr (MSUM) {
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) l_sum[cb] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, P[kb][cb], zero, 0, 0, 0)[0];
+            }
+        };
+        auto softmax = [&](int kb, const float (&sub)[2], float (&lu)[2], bool subtract) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                float l = 0.f, l2 = 0.f;
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int e = 0; e < 4; e += 2) {
+                        float x0 = S[kb][rb][cb][e], x1 = S[kb][rb][cb][e + 1];
+                        if (subtract) { x0 -= sub[cb]; x1 -= sub[cb]; }
+                        if constexpr (EXACTQ) { x0 *= c; x1 *= c; }
+                        const float p0 = __builtin_amdgcn_exp2f(x0), p1 = __builtin_amdgcn_exp2f(x1);
+                        const f32x2 pp = {p0, p1};
+                        const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
+                        l += p0;
+                        l2 += p1;
+                        P[kb][cb][4 * rb + e] = pb[0];
+                        P[kb][cb][4 * rb + e + 1] = pb[1];
+                    }
+                lu[cb] = l + l2;
+            }
+        };
+        auto mask = [&](int j0, int kb) {  // unit kb of the tile at key j0
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const int left = kmax_lane[cb] - (j0 + 32 * kb + 4 * sg(g));
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (16 * rb + e >= left) S[kb][rb][cb][e] = -INFINITY;
+            }
+        };
+        auto settle = [&](int kb, float (&lu)[2], bool fresh) {
+            const bool bad = fresh || (MSUM ? any_big(P[kb][0], P[kb][1]) : !(lu[0] < kOptimisticLimit) || !(lu[1] < kOptimisticLimit));
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
+                float up[2];
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    float a = S[kb][0][cb][0];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a = fmaxf(a, fmaxf(S[kb][0][cb][e], S[kb][1][cb][e]));
+                    // the first reference is of the whole tile: the weight of the largest score, a power of two, rounds exactly, and the
+                    // larger it is the more that counts (short chains: 80 heads, 5 frames of 66: relative error 2.20e-3, of half a tile 2.25e-3)
+                    if (fresh)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) a = fmaxf(a, fmaxf(S[1 - kb][0][cb][e], S[1 - kb][1][cb][e]));
+                    a = fmaxf(a, __shfl_xor(a, 16));
+                    a = fmaxf(a, __shfl_xor(a, 32));
+                    // a row that sees nothing of the chain's first tile sees nothing of the others: any finite reference
+                    up[cb] = fresh ? (a == -INFINITY ? 0.f : a + kRefBias) : fmaxf(a + kRefBias, 0.f);
+                    const float alpha = fresh ? 0.f : __builtin_amdgcn_exp2f(EXACTQ ? -up[cb] * c : -up[cb]);
+                    l_sum[cb] *= alpha;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o_acc[cb][r] *= alpha;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) minit[cb][e] -= up[cb];
+#pragma unroll
+                    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) S[1 - kb][rb][cb][e] -= up[cb];
+                }
+                softmax(kb, up, lu, true);
+            }
+            if constexpr (!MSUM) {
+                l_sum[0] += lu[0];
+                l_sum[1] += lu[1];
+            }
+        };
+        const float no_sub[2] = {0.f, 0.f};
+        auto interleave = [&]() {
+#pragma unroll
+            for (int i = 0; i < (MSUM ? 18 : 16); ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x402, 1, 0);
+            }
+        };
+        auto tile_steps = [&](int t, auto slot, auto slot_next, auto slot_prev, bool first) __attribute__((always_inline)) {
+            const int j0 = t * kBN;
+            float lu[2];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the fragments of tile t-1 have left LDS
+            bar(t, slot_prev);
+            if (__builtin_expect(j0 + 32 > kmin_blk[0], 0)) mask(j0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            read_k((int)slot_next, 0);
+            read_v((int)slot, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            pv(1);
+            sums(1);
+            qk(1);
+            softmax(0, no_sub, lu, false);
+            interleave();
+            __builtin_amdgcn_sched_barrier(0);
+            if (__builtin_expect(j0 + 64 > kmin_blk[0], 0)) mask(j0, 1);
+            settle(0, lu, first);
+            __builtin_amdgcn_sched_barrier(0);
+            read_k((int)slot_next, 1);
+            read_v((int)slot, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            pv(0);
+            sums(0);
+            qk(0);  // of the next tile (a discarded product after the last)
+            softmax(1, no_sub, lu, false);
+            interleave();
+            __builtin_amdgcn_sched_barrier(0);
+            settle(1, lu, false);
+        };
+        typedef std::integral_constant<int, 0> I0;
+        typedef std::integral_constant<int, 1> I1;
+        typedef std::integral_constant<int, 2> I2;
+        typedef std::integral_constant<int, 3> I3;
+        int t = t_begin;
+        if (t < t_vis) {
+            read_k(0, 0);
+            qk(0);
+            read_k(0, 1);
+            // (chains of key-split launches are short: the unrolled ring would be fetched once per launch to run once, 0.5 us)
+            for (; p.n_splits == 1 && t + SLOTS <= t_vis; t += SLOTS) {
+                if constexpr (KV8) {
+                    tile_steps(t, I0{}, I1{}, I2{}, t == t_begin);
+                    tile_steps(t + 1, I1{}, I2{}, I0{}, false);
+                    tile_steps(t + 2, I2{}, I0{}, I1{}, false);
+                } else {
+                    tile_steps(t, I0{}, I1{}, I3{}, t == t_begin);
+                    tile_steps(t + 1, I1{}, I2{}, I0{}, false);
+                    tile_steps(t + 2, I2{}, I3{}, I1{}, false);
+                    tile_steps(t + 3, I3{}, I0{}, I2{}, false);
+                }
+            }
+            for (; t < t_vis; ++t) {
+                const int slot = ring(t - t_begin);
+                tile_steps(t, slot, ring(slot + 1), ring(slot + SLOTS - 1), t == t_begin);
+            }
+            pv(1);
+            sums(1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) m_used[cb] = -minit[cb][0];
+        }
+        for (; t < t_end; ++t) bar(t, ring(t - t_begin + SLOTS - 1));
+    };
+    if constexpr (NCQ == 2) {
+        pipe_one_block();
+    } else {
+    const int t_mid = wave_active ? max(t_begin, min(t_end, (kmax_blk[0] + kBN - 1) / kBN)) : t_begin;
+    int t_pipe = wave_active ? max(t_begin, min(t_mid, kmin_blk[0] / kBN)) : t_begin;
+    if (t_pipe - t_begin < 2) t_pipe = t_begin;
     if (t_pipe > t_begin) {
         f32x4 S[2][2][2];      // [qt][rb'][cb]: the unit in flight of each 32-row block
         f32x4 minit[NCQ];      // [cq]: minus the reference, the C operand of the first product
@@ -731,6 +943,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
     };
     run_rest(t_pipe, t_mid, std::integral_constant<int, 0>{});
     run_rest(t_mid, t_end, std::integral_constant<int, 1>{});
+    }
 
     // ---- final write: lane (j, g) holds, for query column cq, features 16 fb + 4 g + 0..3 (4 sg(g) with KV8) --------
     if (!wave_active) return;
@@ -753,7 +966,7 @@ __device__ __forceinline__ void attn_fwd_item16(const FwdParams& p, const WorkIt
         }
         const int row = row_of(cq);
         if (row >= p.Sq) continue;
-        const float m_exp = EXACTQ ? m_used[cq] * c : m_used[cq];
+        const float m_exp = NCQ == 2 && l_row == 0.f ? kNegBig : EXACTQ ? m_used[cq] * c : m_used[cq];
         if (p.n_splits == 1) {
             const float inv = 1.0f / l_row;
             __bf16* og = (__bf16*)p.out + ((int64_t)wi.bh * p.Sq + row) * kD;

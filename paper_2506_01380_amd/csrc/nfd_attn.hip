@@ -108,6 +108,86 @@ BwdForm bwd_form(int64_t BH, int64_t Sq, int64_t Sk, int T, int P, int num_cus) 
     return std::max(1.93 * ws + 0.5 * 0.97 * longest, 0.97 * longest) < merged ? BwdForm::kMergedSmall : BwdForm::kMerged;
 }
 
+// How the matrix-core forward is cut into workgroups: rows per workgroup (the 32-row blocks of a head dealt evenly to `count` of
+// them) and key splits.  A workgroup's time is its chain of 64-key tiles.  128-row workgroups have the shorter links, 256-row
+// ones (192 rows: tiles of six blocks) less work per row; launches that do not fill the chip for long are as long as their longest
+// chain and take short links.  Each choice is priced: links alone on a CU or sharing it, all work over two workgroups per CU plus
+// part of the longest chain where there is more than one round, write and merge of the partials.  Fitted to the times of
+// both shapes at 1 to 24 splits, 160 sizes over a bf16 cache and 70 over the 8-bit one (1 to 144 heads, 20 to 576 tokens a frame, 2
+// to 64 frames, 1 to 48 of them queries), within 8 %; the rule is then 1 % behind the better of the two on average, 18 % ahead of 256-row
+// tiles alone.  128-row workgroups take at most the splits that the older
+// model of equal chains (tile_splits) gives 256-row ones, usually fewer: a partial output is rounded once more.  Forward, 256-row
+// tiles unless they would fill less than a quarter of the CUs / this (us): 80 heads, 8 of 13 frames of 52 tokens 25.1 / 14.4; 24
+// heads, 16 frames of 121 38.7 / 27.1; 12 heads, 11 frames of 247 40 / 33; 64 heads, 16 frames of 336 the same kernel.
+struct FwdPrice {
+    double alone128, shared128, tail128;   // us a tile
+    double alone256, shared256, tail256;
+    double six;                            // tiles of six blocks (48 rows per wavefront) against the others of the 256-row kernel
+    double far;                            // without splits, K/V of all heads past the last-level cache: query tiles drift apart
+    double fixed, combine, combine_row;    // us; per row and split
+};
+constexpr FwdPrice kPrice16{0.653, 0.893, 0.501, 1.054, 1.412, 0.360, 0.896, 1.029, 5.8, 2.63, 0.930e-4};
+constexpr FwdPrice kPrice8{0.912, 1.098, 0.150, 1.173, 1.661, 0.373, 1.140, 1.0, 5.0, 2.97, 0.895e-4};
+constexpr double kLastLevelBytes = 192e6;  // of 256 MB: room for Q, O and partials
+
+struct RowRanges {
+    int count;             // per head
+    int64_t tiles, longest;  // key tiles: of a head's ranges together, of the longest
+};
+RowRanges row_ranges(int64_t Sq, int T, int P, int rows) {
+    const int blocks = (int)((Sq + 31) / 32);
+    RowRanges r{(blocks + rows / 32 - 1) / (rows / 32), 0, 0};
+    const int lo = blocks / r.count, hi = blocks % r.count;
+    for (int i = 0; i < r.count; ++i) {
+        int b0, nb;
+        nfd::mfma::q_tile_blocks(i, lo, hi, &b0, &nb);
+        const int r_last = (int)std::min<int64_t>(32 * (int64_t)(b0 + nb), Sq) - 1;
+        const int64_t t = (((int64_t)P + r_last / T + 1) * T + nfd::mfma::kBN - 1) / nfd::mfma::kBN;
+        r.tiles += t;
+        r.longest = std::max(r.longest, t);
+    }
+    return r;
+}
+double fwd_price(const FwdPrice& c, const RowRanges& r, int rows_per_wg, bool six, int64_t BH, int64_t Sq, double kv_bytes, int num_cus, int s) {
+    const double cus = num_cus, wgs = (double)BH * r.count * s, k = six ? c.six : 1.0;
+    const bool small = rows_per_wg == nfd::mfma::kBM / 2;
+    const double alone = small ? c.alone128 : c.alone256 * k, shared = small ? c.shared128 : c.shared256 * k;
+    const double longest = (double)((r.longest + s - 1) / s);
+    const double work = (double)BH * ((double)r.tiles + 0.5 * r.count * (s - 1));  // the last split of a range is shorter
+    // past one workgroup per CU: chains of one length end with those that share; of mixed lengths, the long ones start first and
+    // the short ones share with them
+    const double pairs = std::min(1.0, std::max(0.0, wgs / cus - 1.0));
+    const double even = std::max(0.0, 2.0 * (double)r.tiles / ((double)r.count * (double)r.longest) - 1.0);
+    double t = longest * (wgs > cus ? alone + (shared - alone) * (pairs + (1.0 - pairs) * even) : alone);
+    if (wgs > 2 * cus) t = std::max(t, work * shared / (2 * cus) + (small ? c.tail128 : c.tail256) * longest * shared);
+    if (s == 1 && r.count > 1 && kv_bytes > kLastLevelBytes) t *= c.far;
+    return t + c.fixed + (s > 1 ? c.combine + c.combine_row * (double)(BH * Sq) * s : 0.0);
+}
+// Key splits of a launch of 256-row tiles (128-row ones, `few`), only when the tiles alone cannot fill the chip (cached forms).  The
+// count minimises a small cost model in units of the time one workgroup needs for one key tile when
+// two workgroups share a CU: workgroups run in rounds of 2 (3) per CU; a workgroup that has its CU
+// to itself is about 1.2x faster (measured); every workgroup pays a fixed prologue/epilogue of
+// about three tiles; the combine pass costs a launch plus the write and read of the partials,
+// which grows with rows x splits (about one unit per 30000 row-partials of 136 bytes at HBM speed).
+int tile_splits(const RowRanges& r, bool few, int64_t BH, int64_t Sq, int num_cus, size_t workspace_limit) {
+    const int64_t slots = (int64_t)num_cus * (few ? 3 : 2), base = BH * r.count;
+    if (base >= slots) return 1;
+    const size_t per_split = (size_t)(BH * Sq) * kPartialRowBytes;
+    double best = 1e30;
+    int splits = 1;
+    for (int s = 1; s <= 64 && s <= std::max<int64_t>(1, r.longest / 2); ++s) {
+        if (s > 1 && per_split * s > workspace_limit) break;
+        const int64_t wgs = base * s;
+        const int64_t rounds = (wgs + slots - 1) / slots;
+        const double len = (double)((r.longest + s - 1) / s) + 3.0;
+        const double pace = wgs * 2 <= slots ? 0.83 : 1.0;
+        const double combine = s > 1 ? 1.0 + (double)s * (double)(BH * Sq) / 30000.0 : 0.0;
+        const double cost = rounds * len * pace + combine;
+        if (cost < best) { best = cost; splits = s; }
+    }
+    return splits;
+}
+
 // Whether the kernels that give every row a wavefront of its own beat the tile kernels on the general path.  Both are priced as
 // the time of one wavefront (one workgroup of four) times how often the chip is filled; the constants are fitted (least
 // regret) to both sides measured at 1705 sizes a direction: 1 to 4096 keys and 1 to 85 rows a head, 2 to 4096 heads, ten
@@ -212,9 +292,16 @@ int nfd_attn_check_args(nfd_dtype_t dtype, int B, int H, int F, int T, int D, in
     return NFD_OK;
 }
 
-int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames,
-                  int num_cus, size_t workspace_limit, nfd_attn_plan_t* plan) {
-    if (!plan) return NFD_ERR_NULL;
+// The schedule, and how the launch deals it out: the row ranges per head (the plan's query tiles, or more and smaller ones) and
+// whether the kernel for short key splits runs them.
+enum class FwdKind { kPlain, kLse, kFp8 };
+struct FwdDeal {
+    int ranges;
+    bool short_splits;
+};
+static int plan_impl(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames, int num_cus,
+                     size_t workspace_limit, FwdKind kind, nfd_attn_plan_t* plan, FwdDeal* deal) {
+    const bool kv8 = kind == FwdKind::kFp8;
     const int rc = nfd_attn_check_args(dtype, B, H, F, T, D, kv_frames, q_frames);
     if (rc != NFD_OK) return rc;
     if (num_cus <= 0) num_cus = 256;
@@ -225,65 +312,45 @@ int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_f
     if (dtype == NFD_BF16 && D == nfd::mfma::kD) {
         pl.kernel = 1;
         pl.block_n = nfd::mfma::kBN;
-        int64_t visited = 0, max_tiles = 0;
-        // The 32-row blocks of a head are dealt to the query tiles as evenly as they go (see the kernel).
-        const int64_t n_blocks = (Sq + 31) / 32;
-        auto tile_counts = [&](int block_m) {
-            pl.block_m = block_m;
-            pl.n_q_tiles = (int)((n_blocks + block_m / 32 - 1) / (block_m / 32));
-            visited = 0;
-            max_tiles = 0;
-            const int lo = (int)(n_blocks / pl.n_q_tiles), hi = (int)(n_blocks % pl.n_q_tiles);
-            for (int qt = 0; qt < pl.n_q_tiles; ++qt) {
-                int b0, nb;
-                nfd::mfma::q_tile_blocks(qt, lo, hi, &b0, &nb);
-                const int64_t r_last = std::min<int64_t>(32 * (int64_t)(b0 + nb), Sq) - 1;
-                const int64_t nt = (kmax_rows(r_last, T, P) + pl.block_n - 1) / pl.block_n;
-                visited += nt;
-                max_tiles = std::max(max_tiles, nt);
-            }
-        };
-        // 256-row workgroups (64 rows per wavefront, 2 workgroups per CU) are the throughput shape.  When
-        // there are very few query rows (single-frame decode of one sequence), the call's time is the
-        // length of a workgroup's chain of key tiles, and 128-row workgroups (32 rows per wavefront, 3 per
-        // CU) make the links of it shorter: measured -7 % at one frame of 336 queries x 16 heads, +-2 % at two
-        // frames, a loss from four frames on (twice the LDS traffic per FLOP).
-        tile_counts(nfd::mfma::kBM);
-        int wg_per_cu = 2;
-        if (BH * pl.n_q_tiles * 4 < (int64_t)num_cus) {
-            tile_counts(nfd::mfma::kBM / 2);
-            wg_per_cu = 3;
-        }
-        // Key splits: only when the query tiles alone cannot fill the chip (cached forms).  The count
-        // minimises a small cost model in units of the time one workgroup needs for one key tile when
-        // two workgroups share a CU: workgroups run in rounds of 2 per CU; a workgroup that has its CU
-        // to itself is about 1.2x faster (measured); every workgroup pays a fixed prologue/epilogue of
-        // about three tiles; the combine pass costs a launch plus the write and read of the partials,
-        // which grows with rows x splits (about one unit per 30000 row-partials of 136 bytes at HBM speed).
-        const int64_t slots = (int64_t)num_cus * wg_per_cu, base = BH * pl.n_q_tiles;
-        int splits = 1;
-        if (base < slots) {
-            const size_t per_split = (size_t)(BH * Sq) * kPartialRowBytes;
-            double best = 1e30;
-            for (int s = 1; s <= 64 && s <= std::max<int64_t>(1, max_tiles / 2); ++s) {
-                if (s > 1 && per_split * s > workspace_limit) break;
-                const int64_t wgs = base * s;
-                const int64_t rounds = (wgs + slots - 1) / slots;
-                const double len = (double)((max_tiles + s - 1) / s) + 3.0;
-                const double pace = wgs * 2 <= slots ? 0.83 : 1.0;
-                const double combine = s > 1 ? 1.0 + (double)s * (double)(BH * Sq) / 30000.0 : 0.0;
-                const double cost = rounds * len * pace + combine;
-                if (cost < best) { best = cost; splits = s; }
+        const FwdPrice& c = kv8 ? kPrice8 : kPrice16;
+        const double kv_bytes = (double)BH * kv_frames * T * nfd::mfma::kD * (kv8 ? 2.0 : 4.0);
+        const int64_t blocks = (Sq + 31) / 32, tiles256 = (blocks + 7) / 8;
+        const bool few = BH * tiles256 * 4 < (int64_t)num_cus;  // query tiles of 128 rows in the plan, too
+        pl.block_m = few ? nfd::mfma::kBM / 2 : nfd::mfma::kBM;
+        const RowRanges r = row_ranges(Sq, T, P, pl.block_m);
+        pl.n_q_tiles = r.count;
+        const int most = tile_splits(r, few, BH, Sq, num_cus, workspace_limit);
+        int splits = most;
+        *deal = {r.count, false};
+        // Few 128-row tiles, key splits: the small kernel on the 32x32x16 instruction, three workgroups per CU, unless the chains
+        // are long and nearly all wavefronts have rows.  Both at their best split count (us, small / pipelined): 24 heads, one
+        // frame of 40 tokens over 49 11.1 / 11.9; 16 heads, two of 105 over 4 10.2 / 10.7; 48 heads, 152 over 39 (five row blocks of
+        // eight) 25.3 / 27.1; 16 heads, 336 over 32 29.7 / 28.7; 11 heads, three of 294 over 9 24.8 / 23.4.  Over the 8-bit cache
+        // the small kernel: 16 heads, 336 over 32 32.6 / 33.9.
+        const bool full = blocks * 20 >= (int64_t)r.count * 4 * 17 && r.longest >= 8 * (int64_t)most;
+        if (few && most > 1 && kind != FwdKind::kLse && (kv8 || !full)) {
+            deal->short_splits = true;
+        } else if (few || BH * tiles256 < 4 * (int64_t)num_cus) {  // past two rounds the 256-row links are the cheaper ones
+            const bool six = (blocks + r.count - 1) / r.count == nfd::mfma::kBM48 / 32;
+            const RowRanges r128 = few ? r : row_ranges(Sq, T, P, nfd::mfma::kBM / 2);
+            // not for a tie; and splits for splits only where the price is clearly lower (the prices are within 8 %)
+            double best = few ? 1e300 : 0.98 * fwd_price(c, r, pl.block_m, six, BH, Sq, kv_bytes, num_cus, most);
+            for (int s = 1; s <= (kv8 ? 1 : most); ++s) {
+                const double t = fwd_price(c, r128, nfd::mfma::kBM / 2, false, BH, Sq, kv_bytes, num_cus, s) * (s > 1 && !few ? 1.08 : 1.0);
+                if (t < best) { best = t; splits = s; deal->ranges = r128.count; }
             }
         }
+        if (kv8 && splits > 1 && (blocks + deal->ranges - 1) / deal->ranges <= 4) deal->short_splits = true;
+        const int64_t visited = r.tiles;
         pl.n_splits = splits;
-        if (BH * pl.n_q_tiles * splits > (int64_t)0x7fffffff) return NFD_ERR_UNSUPPORTED;  // grid size
+        if (BH * deal->ranges * splits > (int64_t)0x7fffffff) return NFD_ERR_UNSUPPORTED;  // grid size
         pl.n_workgroups = (int)(BH * pl.n_q_tiles * splits);
         pl.key_tiles_visited = visited * BH;
         pl.key_tiles_dense = (int64_t)pl.n_q_tiles * (((int64_t)kv_frames * T + pl.block_n - 1) / pl.block_n) * BH;
         pl.workspace_bytes = splits > 1 ? (size_t)(BH * Sq) * splits * kPartialRowBytes : 0;
     } else {
         pl.kernel = 0;
+        *deal = {0, false};
         const bool rows = rows_pay_fwd(dtype, BH, Sq, (int64_t)kv_frames * T, D, num_cus);
         pl.block_m = rows ? nfd::rows::kRowsPerWorkgroup : 16 * nfd::general::cols_per_workgroup(Sq, BH, D, num_cus, true);
         pl.block_n = rows ? 64 : 16;
@@ -302,6 +369,25 @@ int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_f
     }
     *plan = pl;
     return NFD_OK;
+}
+
+int nfd_attn_plan(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames,
+                  int num_cus, size_t workspace_limit, nfd_attn_plan_t* plan) {
+    if (!plan) return NFD_ERR_NULL;
+    FwdDeal deal;
+    return plan_impl(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus, workspace_limit, FwdKind::kPlain, plan, &deal);
+}
+
+int nfd_attn_fwd_ranges(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames, int num_cus, int fp8kv,
+                        int* ranges, int* n_splits) {
+    if (!ranges || !n_splits) return NFD_ERR_NULL;
+    nfd_attn_plan_t pl;
+    FwdDeal deal;
+    const int rc = plan_impl(dtype, B, H, F, T, D, kv_frames, q_frames, num_cus, 0, fp8kv ? FwdKind::kFp8 : FwdKind::kPlain, &pl, &deal);
+    if (rc != NFD_OK) return rc;
+    *ranges = deal.ranges;
+    *n_splits = pl.n_splits;
+    return rc;
 }
 
 int nfd_attn_bwd_form(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int kv_frames, int q_frames, int num_cus, int* form) {
@@ -399,7 +485,9 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
     const bool kv8 = k_scale != nullptr;
     const bool append = k_new != nullptr;
     nfd_attn_plan_t pl;
-    const int rc = nfd_attn_plan(h->dtype, B, H, F, T, D, kv_frames, q_frames, h->num_cus, h->plan_limit, &pl);
+    FwdDeal deal;
+    const int rc = plan_impl(h->dtype, B, H, F, T, D, kv_frames, q_frames, h->num_cus, h->plan_limit,
+                             kv8 ? FwdKind::kFp8 : lse ? FwdKind::kLse : FwdKind::kPlain, &pl, &deal);
     if (rc != NFD_OK) return fail(h, rc, "invalid shape arguments");
     // A schedule that would write partials past the workspace must never reach the device.
     if (pl.workspace_bytes > h->workspace_bytes)
@@ -427,14 +515,17 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
     p.P = kv_frames - q_frames;
     p.D = D;
     p.n_q_tiles = pl.n_q_tiles;
-    {
+    unsigned workgroups = (unsigned)pl.n_workgroups;
+    if (pl.kernel == 1) {
         const int n_blocks = (p.Sq + 31) / 32;
-        p.blocks_lo = n_blocks / pl.n_q_tiles;
-        p.n_hi = n_blocks % pl.n_q_tiles;
+        p.n_q_tiles = deal.ranges;
+        p.blocks_lo = n_blocks / deal.ranges;
+        p.n_hi = n_blocks % deal.ranges;
+        workgroups = (unsigned)((int64_t)p.BH * deal.ranges * pl.n_splits);
     }
     p.n_splits = pl.n_splits;
-    // K and V of all heads against the 256 MB last-level cache (with room for Q, O and partials)
-    p.group_q_tiles = pl.n_splits > 1 ? (double)p.BH * p.Sk * nfd::mfma::kD * 2.0 * (kv8 ? 1.0 : 2.0) > 192e6
+    // K and V of all heads against the last-level cache
+    p.group_q_tiles = pl.n_splits > 1 ? (double)p.BH * p.Sk * nfd::mfma::kD * 2.0 * (kv8 ? 1.0 : 2.0) > kLastLevelBytes
                                       : nfd::mfma::head_group(p.BH);
     p.scale_log2e = scale * nfd::kLog2e;
     p.Snew0 = 0x7fffffff;
@@ -442,7 +533,7 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
         // In the matrix-core kernel the workgroups read the new rows where they are and copy them into the cache on
         // the side (at most four 16-byte vectors of each tensor per thread); otherwise a copy launch goes first.
         const int64_t n_vec = (int64_t)p.BH * p.Sq * (nfd::mfma::kD / 8);
-        if (pl.kernel == 1 && !kv8 && n_vec <= (int64_t)4 * pl.n_workgroups * nfd::mfma::kWaves * 64) {
+        if (pl.kernel == 1 && !kv8 && n_vec <= (int64_t)4 * workgroups * nfd::mfma::kWaves * 64) {
             p.k_new = k_new; p.v_new = v_new;
             p.Snew0 = p.P * T;
         } else {
@@ -459,30 +550,29 @@ static int fwd_impl(nfd_attn_t* h, const void* q, const void* k, const void* v, 
     hipStream_t st = (hipStream_t)stream;
 
     if (pl.kernel == 1) {
-        const dim3 grid(pl.n_workgroups), block(nfd::mfma::kWaves * 64);
+        const dim3 grid(workgroups), block(nfd::mfma::kWaves * 64);
         auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, p); };
         using namespace nfd::mfma;
-        // Which kernel runs a 256-row tile depends on the 32-row blocks the largest one holds.  Measured: 8 sequences of 16
+        // Which kernel runs a range depends on the 32-row blocks the largest one holds.  Measured: 8 sequences of 16
         // heads, one frame over 40 cached ones (forward / with log-sum-exp / 8-bit cache, us).
+        //   1..4  one block per wavefront (which of the two such kernels: see the plan)
         //   six   48 rows per wavefront, all wavefronts with the same work: 59.9 / 62.3 / 59.3, against 65.4 / 69.0 / 70.5 with
         //         two wavefronts of 64 rows and two of 32 (which lack the pipelined loop) at the same barriers; one frame of 576
         //         tokens over 64: 750 -> 685.  At five blocks 48 rows take 49.6 against 48.5, and splitting 42 blocks into
         //         seven tiles of six instead of six of seven 75.6 against 76.5 (90.1 against 85.9 over the 8-bit cache).
         //   five  over the 8-bit cache also 48 rows: 8 sequences of 16 heads, one frame of 150 over 63: 71.8, with 64 rows 76.0 (76.3 of the
         //         kernel before); 12 such sizes take 0.93 to 1.02 of what 64 rows take.
-        //   1..4  one block per wavefront: the 128-row kernel, three workgroups per CU: with log-sum-exp 13.0 against 14.8 us
-        //         (one block), 34.1 against 35.1 (four); over the 8-bit cache 34.8 against 40.9 (48 rows).  Not for
-        //         the plain forward, whose row sums are of the rounded weights that the output is formed from: the 128-row
-        //         kernel's are not, and its error is up to 0.2 % larger.
         const int tile_blocks = p.blocks_lo + (p.n_hi > 0);
-        if (pl.block_m == kBM / 2 || (tile_blocks <= 4 && (kv8 || lse))) {
-            if (kv8) go(attn_fwd_bf16_d64<true>);
-            else if (lse) go(attn_fwd_bf16_d64<false, true>);  // training pair: scores from the queries as given
-            else go(attn_fwd_bf16_d64<false>);
+        if (tile_blocks <= 4) {
+            if (deal.short_splits && kv8) go(attn_fwd_bf16_d64<true>);
+            else if (deal.short_splits) go(attn_fwd_bf16_d64<false>);
+            else if (kv8) go(attn_fwd_bf16_d64_m16<false, true, 2>);
+            else if (lse) go(attn_fwd_bf16_d64_m16<true, false, 2>);  // training pair: scores from the queries as given
+            else go(attn_fwd_bf16_d64_m16<false, false, 2>);
         } else if (!(tile_blocks == kBM48 / 32 || (kv8 && tile_blocks == 5))) {
-            if (kv8) go(attn_fwd_bf16_d64_m16<false, true>);
-            else if (lse) go(attn_fwd_bf16_d64_m16<true>);
-            else go(attn_fwd_bf16_d64_m16<false>);
+            if (kv8) go(attn_fwd_bf16_d64_m16<false, true, 4>);
+            else if (lse) go(attn_fwd_bf16_d64_m16<true, false, 4>);
+            else go(attn_fwd_bf16_d64_m16<false, false, 4>);
         } else {
             if (kv8) go(attn_fwd_bf16_d64_m16<false, true, 3>);
             else if (lse) go(attn_fwd_bf16_d64_m16<true, false, 3>);
