@@ -144,10 +144,23 @@ def _addr(x):
     return int(x)
 
 
+_torch = None       # imported with the first tensor or stream that needs it: the host-only helpers run without
+_raw_stream = None  # (device index) -> address of its current stream
+
+
+def _bind_torch():
+    global _torch, _raw_stream
+    import torch
+    # the address itself: a torch.cuda.Stream around it costs 2.5 us of a call's 14 (one launch: 4)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+    _torch = torch
+    return torch
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        torch = _torch or _bind_torch()
+        return _raw_stream(torch.cuda.current_device())
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream
     return int(stream)
@@ -348,7 +361,7 @@ class Attention:
         self.h = nfd_attn_create(self.dtype, device, workspace_bytes)
 
     def _want(self):
-        import torch
+        torch = _torch or _bind_torch()
         return torch.bfloat16 if self.dtype == NFD_BF16 else torch.float32
 
     def _tensors(self, *ts):
@@ -361,34 +374,35 @@ class Attention:
     def _geometry(self, q, k, v, T, kv_frames, q_frames):
         """Checks q [B,H,q_frames*T,D] against k, v [B,H,F*T,D]; returns (B, H, F, D, kv_frames, q_frames)."""
         self._tensors(q, k, v)
-        B, H, Sq, D = q.shape
-        if T < 1 or Sq % T or k.shape[2] % T:
+        (B, H, Sq, D), ks = q.shape, k.shape
+        Bk, Hk, Sk, Dk = ks
+        if T < 1 or Sq % T or Sk % T:
             raise ValueError("sequence lengths must be multiples of T")
-        F = k.shape[2] // T
+        F = Sk // T
         q_frames = Sq // T if q_frames is None else q_frames
         kv_frames = F if kv_frames is None else kv_frames
-        if Sq != q_frames * T or k.shape != v.shape or tuple(k.shape[:2]) != (B, H) or k.shape[3] != D:
+        if Sq != q_frames * T or ks != v.shape or Bk != B or Hk != H or Dk != D:
             raise ValueError("shape mismatch between q and k, v")
         return B, H, F, D, kv_frames, q_frames
 
     def _new_frames(self, k_cache, v_cache, k_new, v_new, T, *like_new):
         """Checks the caches [B,H,F*T,D] against the new frames [B,H,n*T,D]; returns (B, H, F, D, n_frames)."""
         self._tensors(k_cache, v_cache, k_new, v_new, *like_new)
-        B, H, Sc, D = k_cache.shape
-        if T < 1 or Sc % T or k_new.shape[2] % T:
+        cs, ns = k_cache.shape, k_new.shape
+        (B, H, Sc, D), (Bn, Hn, Sn, Dn) = cs, ns
+        if T < 1 or Sc % T or Sn % T:
             raise ValueError("sequence lengths must be multiples of T")
-        if v_cache.shape != k_cache.shape or v_new.shape != k_new.shape or tuple(k_new.shape[:2]) != (B, H) or k_new.shape[3] != D:
+        if v_cache.shape != cs or v_new.shape != ns or Bn != B or Hn != H or Dn != D:
             raise ValueError("shape mismatch between the caches and the new frames")
         for t in like_new:
-            if t.shape != k_new.shape:
+            if t.shape != ns:
                 raise ValueError("shape mismatch between q and the new frames")
-        return B, H, Sc // T, D, k_new.shape[2] // T
+        return B, H, Sc // T, D, Sn // T
 
     def forward(self, q, k, v, T, kv_frames=None, q_frames=None, out=None, scale=0.0, stream=None):
-        import torch
         B, H, F, D, kv_frames, q_frames = self._geometry(q, k, v, T, kv_frames, q_frames)
         if out is None:
-            out = torch.empty_like(q)
+            out = _torch.empty_like(q)
         else:
             self._tensors(out)
             if out.shape != q.shape:
@@ -398,8 +412,8 @@ class Attention:
 
     def forward_lse(self, q, k, v, T, kv_frames=None, q_frames=None, scale=0.0, stream=None):
         """Forward that also returns the per-row log-sum-exp (fp32) for the backward call."""
-        import torch
         B, H, F, D, kv_frames, q_frames = self._geometry(q, k, v, T, kv_frames, q_frames)
+        torch = _torch
         out = torch.empty_like(q)
         lse = torch.empty((B, H, q.shape[2]), dtype=torch.float32, device=q.device)
         nfd_block_causal_attn_fwd_lse(self.h, q, k, v, out, lse, B, H, F, T, D, kv_frames, q_frames, scale, stream)
@@ -407,8 +421,8 @@ class Attention:
 
     def backward(self, q, k, v, out, dout, lse, T, kv_frames=None, q_frames=None, scale=0.0, stream=None):
         """Gradients (dq, dk, dv); dk, dv have the shape of k, v (rows past kv_frames*T are zero)."""
-        import torch
         B, H, F, D, kv_frames, q_frames = self._geometry(q, k, v, T, kv_frames, q_frames)
+        torch = _torch
         self._tensors(out, dout)
         if out.shape != q.shape or dout.shape != q.shape:
             raise ValueError("out and dout must have the shape of q")
@@ -432,10 +446,9 @@ class Attention:
                     t_offset=0, q_out=None, stream=None):
         """Rotate q and k_new (3D rotary embedding), write rotated keys and values into the caches.
         Returns the rotated queries (q itself when q_out is q)."""
-        import torch
         B, H, F, D, n_frames = self._new_frames(k_cache, v_cache, k_new, v_new, T, q)
         if q_out is None:
-            q_out = torch.empty_like(q)
+            q_out = _torch.empty_like(q)
         else:
             self._tensors(q_out)
             if q_out.shape != q.shape:
