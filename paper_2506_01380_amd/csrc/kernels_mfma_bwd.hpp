@@ -68,9 +68,21 @@ __device__ __forceinline__ BwdItem decode_bwd(int BH, int n_items) {
 
 // One wavefront's share of a 64-row tile pair (a_rows from tensor a, b_rows from tensor b) into the
 // ring: rows 8*wave + 32*pass + lane/8, each lane fetching the chunk that belongs at its swizzled
-// position.  Rows past row_limit - 1 are clamped (their results are masked or never stored).
+// position.  Whole tiles go by a scalar base and one lane offset in bytes per pass, formed before the loop (a clamped row and a
+// 64-bit address per lane and load are 27 vector instructions a tile, of 290 in the dk/dv kernel).  In the last tile rows past
+// row_limit - 1 are clamped (their results are masked or never stored).
 __device__ __forceinline__ void dma_tile_pair(const __bf16* a, const __bf16* b, int row0, int row_limit,
-                                              unsigned lds_a, unsigned lds_b, int ld_row, int ld_chunk) {
+                                              unsigned lds_a, unsigned lds_b, int ld_row, int ld_chunk, const unsigned (&voff)[2]) {
+    if (row0 + 64 <= row_limit) {
+        const __bf16* at = a + (int64_t)row0 * kD;
+        const __bf16* bt = b + (int64_t)row0 * kD;
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff[pass]), "s"(at), "s"(lds_a + pass * 4096) : "memory", "m0");
+            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff[pass]), "s"(bt), "s"(lds_b + pass * 4096) : "memory", "m0");
+        }
+        return;
+    }
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const int r = min(row0 + 32 * pass + ld_row, row_limit - 1);
@@ -163,11 +175,12 @@ __device__ __forceinline__ void bwd_dq_item(const BwdParams& p, const BwdItem& w
     const float c = p.scale_log2e;
 
     const int ld_row = 8 * wave + (lane >> 3);
-    const int ld_chunk = (lane & 7) ^ chunk_swizzle(ld_row);
+    const int ld_chunk = (lane & 7) ^ chunk_swizzle(ld_row);  // rows + 32: the same swizzle
+    const unsigned ld_voff[2] = {(unsigned)(ld_row * kD + ld_chunk * 8) * 2u, (unsigned)((ld_row + 32) * kD + ld_chunk * 8) * 2u};
     const unsigned lds_k0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.k[0][0]) + wave * 1024;
     const unsigned lds_v0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.v[0][0]) + wave * 1024;
     auto load_tile = [&](int t, int slot) {
-        dma_tile_pair(kg, vg, t * kBN, p.Sk, lds_k0 + slot * kTileElems * 2, lds_v0 + slot * kTileElems * 2, ld_row, ld_chunk);
+        dma_tile_pair(kg, vg, t * kBN, p.Sk, lds_k0 + slot * kTileElems * 2, lds_v0 + slot * kTileElems * 2, ld_row, ld_chunk, ld_voff);
     };
     // per-lane fragment offsets (elements) under the swizzle; blocks at + 16, + 32, + 48 rows have the same swizzle
     const int a_row = 4 * sg(j >> 2) + (j & 3);
@@ -386,15 +399,16 @@ __device__ __forceinline__ void bwd_dkdv_item(const BwdParams& p, const BwdItem&
     const float c = p.scale_log2e;
 
     const int ld_row = 8 * wave + (lane >> 3);
-    const int ld_chunk = (lane & 7) ^ chunk_swizzle(ld_row);
+    const int ld_chunk = (lane & 7) ^ chunk_swizzle(ld_row);  // rows + 32: the same swizzle
+    const unsigned ld_voff[2] = {(unsigned)(ld_row * kD + ld_chunk * 8) * 2u, (unsigned)((ld_row + 32) * kD + ld_chunk * 8) * 2u};
     const unsigned lds_q0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.q[0][0]) + wave * 1024;
     const unsigned lds_g0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.g[0][0]) + wave * 1024;
     const unsigned lds_ld0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)(&sm.ld[0][0][0]) + wave * 256;
     const float* row_vec = (wave & 1) ? dl_g : lse_g;  // wavefronts 0, 2 fetch lse log2(e), 1, 3 -delta
     auto load_tile = [&](int t, int slot) {  // five loads per wavefront and tile
-        dma_tile_pair(qg, gg, t * 64, p.Sq, lds_q0 + slot * kTileElems * 2, lds_g0 + slot * kTileElems * 2, ld_row, ld_chunk);
-        const int r = min(t * 64 + lane, p.Sq - 1);
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" ::"v"(row_vec + r), "s"(lds_ld0 + slot * 1024) : "memory", "m0");
+        dma_tile_pair(qg, gg, t * 64, p.Sq, lds_q0 + slot * kTileElems * 2, lds_g0 + slot * kTileElems * 2, ld_row, ld_chunk, ld_voff);
+        const unsigned r = 4u * (unsigned)min(t * 64 + lane, p.Sq - 1);  // bytes: fewer than 2^32 (2^30 rows)
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(r), "s"(row_vec), "s"(lds_ld0 + slot * 1024) : "memory", "m0");
     };
     // per-lane fragment offsets (elements) under the swizzle; blocks at + 16, + 32, + 48 rows have the same swizzle
     const int a_row = 4 * sg(j >> 2) + (j & 3);
