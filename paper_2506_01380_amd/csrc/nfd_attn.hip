@@ -324,10 +324,9 @@ static int plan_impl(nfd_dtype_t dtype, int B, int H, int F, int T, int D, int k
         *deal = {r.count, false};
         // Few 128-row tiles, key splits: the small kernel on the 32x32x16 instruction, three workgroups per CU, unless the chains
         // are long and nearly all wavefronts have rows.  Both at their best split count (us, small / pipelined): 24 heads, one
-        // frame of 40 tokens over 49 11.1 / 11.9; 16 heads, two of 105 over 4 10.2 / 10.7; 48 heads, 152 over 39 (five row blocks of
-        // eight) 25.3 / 27.1; 16 heads, 336 over 32 (eleven of
-        // twelve) 29.7 / 28.7, two of 336 over 32 (21 of 24) 46.4 / 46.8.  Over the 8-bit cache
-        // the small kernel: 16 heads, 336 over 32 32.6 / 33.9.
+        // frame of 40 tokens over 49 11.1 / 11.9; 16 heads, two of 105 over 4 10.2 / 10.7; 48 heads, 152 over 39 (five row blocks
+        // of eight) 25.3 / 27.1; 16 heads, two of 336 over 32 (21 of 24) 46.4 / 46.8, one (eleven of twelve) 29.7 / 28.7.  Over
+        // the 8-bit cache the small kernel: 16 heads, one of 336 over 32 32.6 / 33.9.
         const bool full = blocks * 10 >= (int64_t)r.count * 4 * 9 && r.longest >= 8 * (int64_t)most;
         if (few && most > 1 && kind != FwdKind::kLse && (kv8 || !full)) {
             deal->short_splits = true;
